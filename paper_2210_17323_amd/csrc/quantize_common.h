@@ -31,151 +31,32 @@ __device__ __forceinline__ void grid_from_range(int grid, float maxq, float lo, 
     }
 }
 
-// ---- the stream of U values ------------------------------------------------------------------------------
-// Row j of the block of U is needed from the aligned chunk of 16 floats that holds column j: the diagonal
-// element and the elements right of it.  A chunk sits in ONE register: lane l holds element l % 16 (the same
-// 16 values in each of the wavefront's four rows of 16 lanes), and the multiply-add that needs element c reads
-// it from lane c of its own row through the DPP row broadcast -- v_fmac_f32_dpp ... row_newbcast:c -- so a value
-// of U reaches all 64 lanes inside the instruction that uses it.  (Reading each value into every lane with
-// 16-byte LDS reads cost as many issue cycles per value as the multiply-add itself.)
-// All rows' chunks, in the order of their use, form one stream; it is read from LDS through a ring of RING
-// registers: the chunk at stream position t + RING is requested right after the one at position t has been used,
-// so a request runs well over a thousand cycles ahead of its use, also across the serial arithmetic at a column.
-// Rows, chunks and ring slots are template parameters: every register index is a constant by construction.
-namespace ustream {
-constexpr int RING = 8;
-constexpr int CHUNK = 16;
-constexpr int first_chunk(int j) { return j / CHUNK; }
-constexpr int chunks(int j) { return QB / CHUNK - first_chunk(j); }
-constexpr int start(int j) { int s = 0; for (int i = 0; i < j; ++i) s += chunks(i); return s; }
-constexpr int TOTAL = start(QB);
-constexpr int row_at(int t) { int j = 0; while (t >= chunks(j)) { t -= chunks(j); ++j; } return j; }
-}  // namespace ustream
-
-typedef const __attribute__((address_space(3))) float* lds_floats;
-typedef const volatile __attribute__((address_space(3))) float* lds_floats_ordered;
-
-template <typename WT> struct WeightRegs {                  // float32 weights: one register each
-    float v[QB];
-    template <int J> __device__ __forceinline__ float get() const { return v[J]; }
-};
-template <> struct WeightRegs<_Float16> {                    // 16-bit weights stay packed two to a register
-    uint32_t v[QB / 2];
-    template <int J> __device__ __forceinline__ float get() const {
-        return (float)__builtin_bit_cast(_Float16, (uint16_t)(v[J / 2] >> (16 * (J & 1))));
-    }
-};
-template <> struct WeightRegs<__bf16> {
-    uint32_t v[QB / 2];
-    template <int J> __device__ __forceinline__ float get() const {
-        return __builtin_bit_cast(float, (J & 1) ? (v[J / 2] & 0xffff0000u) : (v[J / 2] << 16));
-    }
-};
-
-
-// Volatile on purpose: volatile accesses and volatile asm statements (the multiply-adds below) keep their
-// program order, which is what places each request RING chunks ahead of its use.  An ordinary load has no such
-// order: with the whole column loop one straight line, the compiler either hoists all requests to the top or
-// sinks each one down to its use and then waits for it.  `ubl` is the block in LDS offset by lane % 16.
-template <int T, class St>
-__device__ __forceinline__ void request_chunk(St& st, lds_floats ubl) {
-    if constexpr (T < ustream::TOTAL) {
-        constexpr int j = ustream::row_at(T), q = ustream::first_chunk(j) + (T - ustream::start(j));
-        st.ring[T % ustream::RING] = *static_cast<lds_floats_ordered>(ubl + j * QB + ustream::CHUNK * q);
-    }
-}
-
-template <class St, int... T>
-__device__ __forceinline__ void request_first(St& st, lds_floats ubl, std::integer_sequence<int, T...>) {
-    (request_chunk<T>(st, ubl), ...);
-}
-
-// w[k] += ne * (element C of the chunk in `u`), for all lanes.  The s_nop covers the two wait states a DPP read
-// needs after a vector-ALU write of the same register, should the compiler ever have moved the chunk there.
-template <int C, bool FIRST>
-__device__ __forceinline__ void fma_bcast(float& w, float u, float ne) {
-    if constexpr (FIRST)
-        asm volatile("s_nop 1\n\tv_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(w) : "v"(u), "v"(ne), "n"(C));
-    else
-        asm volatile("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(w) : "v"(u), "v"(ne), "n"(C));
-}
-
-template <int J, int K0, class St, int... C>
-__device__ __forceinline__ void update_chunk_columns(St& st, float u, float ne, std::integer_sequence<int, C...>) {
-    // columns K0 + C right of J; the first one issued carries the s_nop
-    constexpr int first = (J >= K0) ? J - K0 + 1 : 0;
-    ((K0 + C > J ? fma_bcast<C, C == first>(st.acc()[K0 + C], u, ne) : (void)0), ...);
-}
-
-// w[k] -= e * U[J][k] for the columns of chunk Q right of J, then the request that refills the slot
-template <int J, int Q, class St>
-__device__ __forceinline__ void update_chunk(St& st, lds_floats ubl, float ne) {
-    constexpr int t = ustream::start(J) + Q, k0 = ustream::CHUNK * (ustream::first_chunk(J) + Q);
-    update_chunk_columns<J, k0>(st, st.ring[t % ustream::RING], ne, std::make_integer_sequence<int, ustream::CHUNK>{});
-    request_chunk<t + ustream::RING>(st, ubl);
-}
-
-template <int J, class St, int... Q>
-__device__ __forceinline__ void update_row(St& st, lds_floats ubl, float ne, std::integer_sequence<int, Q...>) {
-    (update_chunk<J, Q>(st, ubl, ne), ...);
-}
-
-// The 128 x 128 diagonal block of an upper-triangular matrix M (U, or the factor R) into LDS:
-// ubs[j][k] = M[j0+j][j0+k] for k >= j, zero below the diagonal, identity outside the matrix.  The whole workgroup
-// (256 threads) calls it: 16 independent 16-byte loads per thread (in PARTS passes of 16 / PARTS, for callers short
-// of registers), then one barrier.
-template <int PARTS = 1>
-__device__ __forceinline__ void stage_diag_block(float* ubs, const float* M, int64_t ldm, int64_t j0, int64_t n) {
-    const int tid = threadIdx.x;
-    constexpr int PER = 16 / PARTS;
-#pragma unroll
-    for (int part = 0; part < PARTS; ++part) {
-    float4 in[PER];
-#pragma unroll
-    for (int tt = 0; tt < PER; ++tt) {
-        const int t = part * PER + tt;
-        const int q = tid + 256 * t, j = q >> 5, k = (q & 31) * 4;
-        const int64_t gj = j0 + j, gk = j0 + k;
-        const float* src = M + gj * ldm + gk;
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (gj < n && gk + 4 <= n) v = *reinterpret_cast<const float4*>(src);
-        else if (gj < n && gk < n) { v.x = src[0]; if (gk + 1 < n) v.y = src[1]; if (gk + 2 < n) v.z = src[2]; }
-        in[tt] = v;
-    }
-#pragma unroll
-    for (int tt = 0; tt < PER; ++tt) {
-        const int t = part * PER + tt;
-        const int q = tid + 256 * t, j = q >> 5, k = (q & 31) * 4;
-        const int64_t gj = j0 + j, gk = j0 + k;
-        float e[4] = {in[tt].x, in[tt].y, in[tt].z, in[tt].w};
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const bool inside = gj < n && gk + c < n;
-            e[c] = inside ? (k + c >= j ? e[c] : 0.f) : (k + c == j ? 1.f : 0.f);
-        }
-        *reinterpret_cast<float4*>(&ubs[j * QB + k]) = make_float4(e[0], e[1], e[2], e[3]);
-    }
-    }
-    __syncthreads();
-}
-
-// ---- the factor form with grids taken inside a block: arguments and launchers (quantize_groups.hip) ----
-struct HybridArgs {
-    const void* W; int64_t ldw;     // original weights, type WT
-    const float* T; int64_t ldt;    // this block's 128 columns of the accumulators, which hold S[:, block] U_bb
-    const float* Ub;                // U_bb, dense 128 x 128 (identity outside a short last block)
-    int64_t r, n, j0; int nbk;
+// ---- the walk of one outer block (quantize_strip.hip) ----
+constexpr size_t STRIP_DIAG_BYTES = 51200;             // a packed diagonal block
+constexpr size_t STRIP_PAIR_BYTES = 28 * 65536;        // the packed tiles above the diagonal blocks of an outer block
+constexpr int STRIP_PACK_OUTER = 4;                    // outer blocks packed at a time (9 MB): one launch for every four strips
+constexpr size_t STRIP_PACK_DIAG_BYTES = STRIP_PACK_OUTER * 8 * STRIP_DIAG_BYTES;
+constexpr size_t STRIP_PACK_BYTES = STRIP_PACK_DIAG_BYTES + STRIP_PACK_OUTER * STRIP_PAIR_BYTES;
+struct StripArgs {
+    const float* S; int64_t lds_;   // working values [r x n]: weights (U form) or accumulators (R and hybrid forms); null: all zero
+    const void* W; int64_t ldw; int wdtype; int w_vec;     // original weights (R and hybrid forms); w_vec: four at a time are aligned
+    const float* diag; const float* pairs;                  // this outer block of the packed factor
+    int64_t r, n, o0, o1;           // this outer block's columns
     int grid; int maxq;
-    float* scales; int32_t* zeros; int64_t ngroups;
+    float* scales; int32_t* zeros; int64_t ngroups, group;
+    int in_group;                   // group size if groups lie inside a block, else 0
+    int64_t wide_group;             // group size if groups span 2, 4 or 8 blocks of an outer block, else 0
     uint8_t* codes; int64_t ldc;
-    uint8_t* cstage;
-    float* D; int64_t ldd;
+    float* E; int64_t lde;          // out: -e (U form) or d = w - q of this outer block [r x 1024]; null: not wanted
     double* half_e2;
-    int first_block;
 };
-
-// Launches the walk of one block for group in {32, 64, 128} and wdtype in {GPTQ_F16, GPTQ_BF16, GPTQ_F32}.
-int launch_quant_block_hybrid(int64_t group, int wdtype, unsigned workgroups, const HybridArgs& h, hipStream_t s);
+// Packs the outer blocks from column j_first on (a multiple of STRIP_PACK_OUTER * 1024) into STRIP_PACK_BYTES bytes: diagonal
+// blocks first, the tiles of the outer blocks STRIP_PACK_DIAG_BYTES later.  M: what the later blocks of an outer block are
+// updated with; D: the triangular blocks that are walked -- M's own (diag_dense = false) or dense 128 x 128 ones.
+// with_pairs = false: outer blocks of one block.
+int launch_pack_factor(const float* M, int64_t ldm, const float* D, int64_t ldd, bool diag_dense, int64_t n, int64_t j_first, bool with_pairs,
+                       float* packed, hipStream_t s);
+int launch_alg1_strip(bool rf, bool hybrid, const StripArgs& g, hipStream_t s);
 // Ub[b] = R_bb^-1 for every 128 x 128 diagonal block of R (dense, identity outside a short last block).
 int launch_invert_diag_blocks(const float* R, int64_t ldr, int64_t n, float* Ub, hipStream_t s);
 // Rt[0:j0, block] = R[0:j0, block] U_bb for every column block (the part above the diagonal blocks; the rest of Rt is
