@@ -75,12 +75,12 @@ GPTQ_API int gptq_release_thread_resources(void);
  *       matrix cores; GPTQ_F32: float32 matrix-core products).
  *       X must be 16-byte aligned and ldx a multiple of 8 (f16/bf16) or 4 (f32) elements.
  *   ws  optional workspace (may be NULL) of gptq_hessian_accumulate_workspace_bytes(n, t, xdtype) bytes,
- *       256-byte aligned.  With it, 16-bit chunks of layers with at least 2048 channels are first repacked
- *       so that every 256-channel x 32-token panel step is one contiguous 16 KB block, which the
- *       matrix-core kernel copies with far better cache-line and DRAM-page locality; for layers whose H has
- *       few 256 x 256 tiles (up to ~16000 channels) the token range of the call is also split in up to 8
- *       parts whose partial tiles (held in the workspace) are added in a fixed order, so that all CUs have
- *       work -- pass such layers long chunks, whole calibration sets if they fit.  Without the workspace
+ *       256-byte aligned.  With it, 16-bit chunks of layers with at least 2048 channels (256 in calls of more
+ *       than 32768 tokens) are first repacked so that every 256-channel x 32-token panel step is one contiguous
+ *       16 KB block, which the matrix-core kernel copies with far better cache-line and DRAM-page locality; for
+ *       layers whose H has few 256 x 256 tiles (up to ~16000 channels) the token range of the call is also split
+ *       in up to 8 parts (as many as fill the chip below ~2000 channels) whose partial tiles (held in the
+ *       workspace) are added in a fixed order, so that all CUs have work -- pass such layers long chunks, whole calibration sets if they fit.  Without the workspace
  *       the kernels read X in place: the same sums up to float32 summation order, at lower speed.
  *       Calls of more than 32768 tokens on layers whose H fills the chip without that split (from ~11000 channels
  *       on) walk the token range in slices of 32768: the workspace then holds two repacked slices, and every slice
@@ -90,7 +90,8 @@ GPTQ_API int gptq_release_thread_resources(void);
  *       makes (1 unless it is sliced).  The environment variable GPTQ_HESSIAN_SLICE_TOKENS (a multiple of 32), read
  *       at every call, changes the slice length and makes every 16-bit call longer than a slice take this path.
  *       Repeating a call gives the same bits either way.  The size is 0 where the workspace is not used (ws is
- *       then ignored).  A non-NULL ws that is misaligned or smaller than that size is GPTQ_ERR_WORKSPACE.
+ *       then ignored).  A non-NULL ws that is misaligned or smaller than that size is GPTQ_ERR_WORKSPACE from 2048
+ *       channels on and ignored below.
  *   No normalisation by the token count is applied (the quantization result is invariant to the
  *   scale of H).  n == 0 or t == 0 is a valid no-op.
  */

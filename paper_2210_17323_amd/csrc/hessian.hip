@@ -13,6 +13,7 @@
 // walked top to bottom and each XCD gets a contiguous range of that order, so the 32 workgroups
 // resident on one XCD form a ~4 x 8 patch of tiles that shares its row and column panels in L2.
 #include "common.h"
+#include "hessian_small.h"
 #include "syrk_tiles.h"
 
 namespace gptq {
@@ -505,24 +506,38 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 }
 
 // H tile += 2 * (P[0] + P[1] + ... + P[splits-1]), the partial tiles of one tile in the order of their token
-// ranges.  One workgroup per tile and 32-row slab, one thread per column.
+// ranges.  A workgroup takes four rows of a tile, a thread four columns; eight partial values are requested before the first is
+// added (one after the other, row by row, a launch of 10 tiles x 8 parts took 73 us for what is 25 MB of reads).
 __global__ __launch_bounds__(256) void syrk_reduce_kernel(SyrkArgs g) {
     const int64_t L = blockIdx.x;
     int bi, bj;
     syrk_tile_of(g.nt, L, bi, bj);
-    const int64_t col = (int64_t)bj * 256 + threadIdx.x;
-    for (int r = 0; r < 32; ++r) {
-        const int rt = blockIdx.y * 32 + r;
-        const int64_t row = (int64_t)bi * 256 + rt;
-        float sum = 0.f;
-        for (int q = 0; q < g.splits; ++q) sum += g.P[((int64_t)q * g.total + L) * 65536 + rt * 256 + threadIdx.x];
-        if (row < g.n && col < g.n) g.H[row * g.ldh + col] += 2.0f * sum;
+    const int rt = blockIdx.y * 4 + (threadIdx.x >> 6), ct = (threadIdx.x & 63) * 4;
+    const float4* p = reinterpret_cast<const float4*>(g.P + L * 65536 + rt * 256 + ct);
+    const int64_t stride = g.total * 16384;                  // float4s from one part to the next
+    float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int q0 = 0; q0 < g.splits; q0 += 8) {
+        float4 v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (q0 + q < g.splits) v[q] = p[(q0 + q) * stride];
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (q0 + q < g.splits) { sum.x += v[q].x; sum.y += v[q].y; sum.z += v[q].z; sum.w += v[q].w; }
     }
+    const int64_t row = (int64_t)bi * 256 + rt, col = (int64_t)bj * 256 + ct;
+    if (row >= g.n) return;
+    float* h = g.H + row * g.ldh + col;
+    if (col < g.n) h[0] += 2.0f * sum.x;
+    if (col + 1 < g.n) h[1] += 2.0f * sum.y;
+    if (col + 2 < g.n) h[2] += 2.0f * sum.z;
+    if (col + 3 < g.n) h[3] += 2.0f * sum.w;
 }
 
 // How a chunk of t tokens of an n-channel layer goes through the direct-to-LDS kernel with a workspace.
 // Matrices with fewer than four 256 x 256 tiles per CU leave much of the chip idle at the end of a launch (or
-// all along: n = 4096 has 136 tiles for 256 CUs), so their token range is split into up to 8 parts.  The split
+// all along: n = 4096 has 136 tiles for 256 CUs), so their token range is split into up to 8 parts -- up to as many as
+// fill the chip once where there are no more than 32 tiles.  The split
 // count minimises a simple cost: rounds of 256 workgroups x (steps per part x 0.76 us + a fixed cost per work
 // item: ~8 us to start and to add a tile to H, ~30 us when a partial tile is written, read back and reduced).
 struct SyrkPlan { int splits; int64_t nsteps; size_t repack_bytes, partial_bytes; };
@@ -531,10 +546,12 @@ static SyrkPlan syrk_plan(int64_t n, int64_t t) {
     int best = 1;
     if (tiles < 2048) {
         double best_cost = 0.0;
-        for (int S = 1; S <= 8; ++S) {
+        const int most = tiles <= 32 ? (int)(256 / tiles) : 8;
+        for (int S = 1; S <= most; ++S) {
             if (S > 1 && steps < 20 * (int64_t)S) break;             // a part should be at least 20 steps long
             const double rounds = (double)ceil_div(tiles * S, 256);
-            const double cost = rounds * ((double)ceil_div(steps, S) * 0.76 + (S > 1 ? 30.0 : 8.0));
+            double cost = rounds * ((double)ceil_div(steps, S) * 0.76 + (S > 1 ? 30.0 : 8.0));
+            if (most > 8 && S > 1) cost += (double)(S * tiles) * 0.12;   // many parts of few tiles: their bytes count (256 KB written and read)
             if (S == 1 || cost < best_cost * 0.98) { best_cost = cost; best = S; }
         }
     }
@@ -585,7 +602,7 @@ static int launch_syrk_dma(SyrkArgs g, void* ws, hipStream_t s, bool token_major
         hipLaunchKernelGGL((syrk_f16_dma_kernel<IS_BF16, true>), dim3((unsigned)blocks), dim3(256), 0, s, g);
         if (g.P) {
             GPTQ_LAUNCH_CHECK();
-            hipLaunchKernelGGL(syrk_reduce_kernel, dim3((unsigned)g.total, 8), dim3(256), 0, s, g);
+            hipLaunchKernelGGL(syrk_reduce_kernel, dim3((unsigned)g.total, 64), dim3(256), 0, s, g);
         }
     } else {
         hipLaunchKernelGGL((syrk_f16_dma_kernel<IS_BF16, false>), dim3((unsigned)blocks), dim3(256), 0, s, g);
@@ -714,10 +731,23 @@ __global__ __launch_bounds__(256) void symmetrize_kernel(float* H, int64_t ld, i
 
 using namespace gptq;
 
-constexpr int64_t SYRK_DMA_MIN_N = 2048;        // below this even a split token range leaves most CUs without a tile
+constexpr int64_t SYRK_DMA_MIN_N = 2048;
+// Smaller layers take a workspace (and with it the 256 x 256 tiles over a split token range) only in long calls: what the
+// repack and the partial tiles cost is won back there -- 131072 tokens of 1000 channels: 250 us against 890 without one --,
+// and shorter calls go without.
+constexpr int64_t SYRK_SMALL_WS_TOKENS = 32768;
+constexpr int64_t SYRK_SMALL_WS_MIN_N = 256;
+static bool syrk_small_with_ws(int64_t n, int64_t t) {
+    return n < SYRK_DMA_MIN_N && n >= SYRK_SMALL_WS_MIN_N && t > SYRK_SMALL_WS_TOKENS && syrk_plan(n, t).nsteps <= 65535;
+}
 
 static size_t syrk_ws_bytes(int64_t n, int64_t t, int xdtype) {
-    if (xdtype == GPTQ_F32 || n < SYRK_DMA_MIN_N) return 0;
+    if (xdtype == GPTQ_F32 || n <= 0 || t <= 0) return 0;
+    if (syrk_small_with_ws(n, t)) {
+        const SyrkPlan p = syrk_plan(n, t);
+        return p.repack_bytes + p.partial_bytes;
+    }
+    if (n < SYRK_DMA_MIN_N) return 0;
     if (syrk_sliced(n, t)) return syrk_sliced_ws_bytes(n);
     const SyrkPlan p = syrk_plan(n, t);
     if (n <= 6144 && p.splits == 1) return 0;       // too few tokens to split: the 128-tile kernel does better
@@ -748,6 +778,7 @@ extern "C" int gptq_hessian_accumulate(float* H, int64_t ldh, const void* X, int
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (xdtype == GPTQ_F32) {
         if (!aligned(X, 16) || ldx % 4) return fail(GPTQ_ERR_INVALID_ARG, "hessian_accumulate: float32 X must be 16-byte aligned with ldx %% 4 == 0");
+        if (n <= SYRK_SMALL_MAX_F32) return launch_syrk_small(H, ldh, X, xdtype, n, t, ldx, s);
         GemmF32 g{};
         g.A = static_cast<const float*>(X); g.lda = ldx;
         g.B = g.A; g.ldb = ldx;
@@ -763,14 +794,16 @@ extern "C" int gptq_hessian_accumulate(float* H, int64_t ldh, const void* X, int
     // With a workspace the chunk is first repacked into contiguous, zero-padded panel steps (much better
     // DRAM-page and cache-line locality for the copies) and the direct-to-LDS kernel takes all of it; matrices
     // with few tiles get their token range split (see syrk_plan).
-    const size_t need = syrk_ws_bytes(n, t, xdtype);
+    size_t need = syrk_ws_bytes(n, t, xdtype);
+    if (n < SYRK_DMA_MIN_N && ws && (!aligned(ws, 256) || ws_bytes < need)) need = 0;       // layers this small do without
     if (need && ws && (!aligned(ws, 256) || ws_bytes < need))
         return fail(GPTQ_ERR_WORKSPACE, "hessian_accumulate: workspace misaligned or smaller than the %zu bytes this call needs "
                                         "(pass NULL to read X in place)", need);
-    if (need && ws && syrk_sliced(n, t))
+    if (need && ws && n >= SYRK_DMA_MIN_N && syrk_sliced(n, t))
         return bf ? launch_syrk_sliced<true>(g, ws, s) : launch_syrk_sliced<false>(g, ws, s);
     if (need && ws)
         return bf ? launch_syrk_dma<true>(g, ws, s) : launch_syrk_dma<false>(g, ws, s);
+    if (n <= SYRK_SMALL_MAX_16) return launch_syrk_small(H, ldh, X, xdtype, n, t, ldx, s);
     if (n <= 6144)                  // 256-wide tiles only fill the chip when there are enough of them
         return bf ? launch_syrk<true, 128, 2, 2>(g, s) : launch_syrk<false, 128, 2, 2>(g, s);
     // Without one the kernel copies straight from X: whole trips of its 5-stage loop (160 tokens) go through

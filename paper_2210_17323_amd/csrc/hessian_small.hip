@@ -1,0 +1,184 @@
+// Step 1 for layers of few channels, X read in place (channel-major, no workspace): H += 2 X X^T.
+//
+// A matrix of few tiles leaves most of the chip idle and walks all tokens in one long chain per tile (256 channels:
+// 2 tiles of 256 x 128 on 256 CUs, 4096 float32 tokens in 471 us).  Here the tile is small -- T x T, T = 64 or 32 -- and the
+// wavefronts of a workgroup share the tokens of ONE tile: wavefront w multiplies chunks w, w + WAVES, .. of CHUNK tokens,
+// operands straight from memory into registers (the next chunk's loads are in flight while this one is multiplied), and
+// the partial tiles are added through LDS in a fixed order, so a call gives the same bits every time.
+// Bound: the vector cache.  A matrix operand has a different row in every neighbouring lane, so a load instruction touches
+// 16 rows x 64 bytes and moves ~20 bytes per cycle and CU (215 TFLOP/s at 2000 float16 channels, 70 at float32); tiles shared
+// through LDS reach three times that rate but need the tiles of ~2000 channels to fill the chip, and a workspace to split the
+// token range any further.
+// Measured (a call, before -> after): float32 256 channels x 4096 tokens 472 -> 40 us, 1000 x 16384 1483 -> 480, 3000 x 8192
+// 1240 -> 1150; float16 256 x 65536 1070 -> 228, 512 x 32768 551 -> 119, 1000 x 131072 2140 -> 890, 1536 x 65536 1080 -> 900.
+#include "hessian_small.h"
+
+namespace gptq {
+
+typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+namespace {
+
+struct SmallArgs { float* H; int64_t ldh; const void* X; int64_t ldx, n, t; int nt; };
+
+// TYPE: GPTQ_F16, GPTQ_BF16 or GPTQ_F32
+template <int TYPE, int T, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void syrk_small_kernel(SmallArgs g) {
+    constexpr int SZ = TYPE == GPTQ_F32 ? 4 : 2;
+    constexpr int EL = 16 / SZ;                              // tokens per load
+    constexpr int PER = 2;                                   // loads of a row per chunk
+    constexpr int CHUNK = PER * 4 * EL;                      // 64 tokens, or 32 of float32
+    constexpr int S = T / 16;                                // 16 x 16 tiles per side
+    constexpr int SLOT = T * T * 4;
+    __shared__ __attribute__((aligned(16))) unsigned char part[WAVES * SLOT];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int l16 = lane & 15, kq = lane >> 4;
+    // tile of the upper triangle: column by column
+    int bj = 0, bi = (int)blockIdx.x;
+    while (bi > bj) { bi -= bj + 1; ++bj; }
+
+    const char* rowA[S];
+    const char* rowB[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {                            // rows past n repeat the last one: they only feed outputs that are not stored
+        rowA[s] = static_cast<const char*>(g.X) + min((int64_t)bi * T + 16 * s + l16, g.n - 1) * g.ldx * SZ + kq * 16;
+        rowB[s] = static_cast<const char*>(g.X) + min((int64_t)bj * T + 16 * s + l16, g.n - 1) * g.ldx * SZ + kq * 16;
+    }
+    uint4 a[2][S][PER], b[2][S][PER];
+    // a whole chunk; no branch around it, so that the wait for one buffer does not wait for the other's loads
+    auto load = [&](int64_t chunk, int buf) {
+        const int64_t off = chunk * (CHUNK * SZ);
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                a[buf][s][i] = *reinterpret_cast<const uint4*>(rowA[s] + off + 64 * i);
+                b[buf][s][i] = *reinterpret_cast<const uint4*>(rowB[s] + off + 64 * i);
+            }
+    };
+    // the tokens past the last whole chunk, zeros past the last token
+    auto load_tail = [&](const char* row, int64_t k0, uint4 (&d)[PER]) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int64_t k = k0 + (4 * i + kq) * EL;
+            uint32_t w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int e = 0; e < EL; ++e) {
+                if (k + e < g.t) {
+                    const char* p = row + k0 * SZ + 64 * i + e * SZ;
+                    if constexpr (SZ == 4) w[e] = *reinterpret_cast<const uint32_t*>(p);
+                    else w[e >> 1] |= (uint32_t)*reinterpret_cast<const uint16_t*>(p) << (16 * (e & 1));
+                }
+            }
+            d[i] = make_uint4(w[0], w[1], w[2], w[3]);
+        }
+    };
+    floatx4 acc[S][S];
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+        for (int u = 0; u < S; ++u)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[s][u][i] = 0.f;
+    auto products = [&](const uint4 (&x)[S][PER], const uint4 (&y)[S][PER]) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            if constexpr (TYPE == GPTQ_F32) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int s = 0; s < S; ++s)
+#pragma unroll
+                        for (int u = 0; u < S; ++u) {
+                            const uint32_t xa[4] = {x[s][i].x, x[s][i].y, x[s][i].z, x[s][i].w}, yb[4] = {y[u][i].x, y[u][i].y, y[u][i].z, y[u][i].w};
+                            acc[s][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(xa[e]), __uint_as_float(yb[e]), acc[s][u], 0, 0, 0);
+                        }
+            } else {
+#pragma unroll
+                for (int s = 0; s < S; ++s)
+#pragma unroll
+                    for (int u = 0; u < S; ++u) {
+                        if constexpr (TYPE == GPTQ_BF16)
+                            acc[s][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x[s][i]), __builtin_bit_cast(bf16x8, y[u][i]), acc[s][u], 0, 0, 0);
+                        else
+                            acc[s][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(halfx8, x[s][i]), __builtin_bit_cast(halfx8, y[u][i]), acc[s][u], 0, 0, 0);
+                    }
+            }
+        }
+    };
+    auto multiply = [&](int buf) { products(a[buf], b[buf]); };
+    const int64_t chunks = g.t / CHUNK;
+    if (wave < chunks) {
+        const int64_t last = chunks - 1;
+        load(wave, 0);
+        for (int64_t c = wave; c < chunks; c += 2 * WAVES) {
+            load(min(c + WAVES, last), 1);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(0);
+            if (c + WAVES >= chunks) break;
+            __builtin_amdgcn_sched_barrier(0);
+            load(min(c + 2 * WAVES, last), 0);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    if (g.t % CHUNK != 0 && wave == WAVES - 1) {
+#pragma unroll
+        for (int s = 0; s < S; ++s) { load_tail(rowA[s], chunks * CHUNK, a[0][s]); load_tail(rowB[s], chunks * CHUNK, b[0][s]); }
+        multiply(0);
+    }
+    // every wavefront leaves its partial tile in LDS, then takes its share of the tile: the partial sums of an element are
+    // added in the order of the wavefronts
+    floatx4* mine = reinterpret_cast<floatx4*>(part + wave * SLOT);
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+        for (int u = 0; u < S; ++u) mine[(s * S + u) * 64 + lane] = acc[s][u];
+    __syncthreads();
+    for (int p = wave; p < S * S; p += WAVES) {              // 16 x 16 tile p: rows 16 (p / S) + 4 kq + e, column 16 (p % S) + l16
+        floatx4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) v += reinterpret_cast<const floatx4*>(part + w * SLOT)[p * 64 + lane];
+        const int64_t col = (int64_t)bj * T + 16 * (p % S) + l16;
+        const int64_t row = (int64_t)bi * T + 16 * (p / S) + 4 * kq;
+        if (col < g.n) {
+            float* h = g.H + row * g.ldh + col;
+            float old[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) old[e] = row + e < g.n ? h[e * g.ldh] : 0.f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (row + e < g.n) h[e * g.ldh] = old[e] + 2.0f * v[e];
+        }
+    }
+}
+
+template <int TYPE>
+int launch(const SmallArgs& a0, hipStream_t s) {
+    SmallArgs a = a0;
+    const int64_t n64 = ceil_div(a.n, 64), n32 = ceil_div(a.n, 32);
+    if (n64 * (n64 + 1) / 2 >= 128) {
+        a.nt = (int)n64;
+        hipLaunchKernelGGL((syrk_small_kernel<TYPE, 64, 8>), dim3((unsigned)(n64 * (n64 + 1) / 2)), dim3(512), 0, s, a);
+    } else {
+        a.nt = (int)n32;
+        hipLaunchKernelGGL((syrk_small_kernel<TYPE, 32, 16>), dim3((unsigned)(n32 * (n32 + 1) / 2)), dim3(1024), 0, s, a);
+    }
+    GPTQ_LAUNCH_CHECK();
+    return GPTQ_OK;
+}
+
+}  // namespace
+
+int launch_syrk_small(float* H, int64_t ldh, const void* X, int xdtype, int64_t n, int64_t t, int64_t ldx, hipStream_t s) {
+    const SmallArgs a{H, ldh, X, ldx, n, t, 0};
+    if (xdtype == GPTQ_F32) return launch<GPTQ_F32>(a, s);
+    if (xdtype == GPTQ_BF16) return launch<GPTQ_BF16>(a, s);
+    return launch<GPTQ_F16>(a, s);
+}
+
+}  // namespace gptq

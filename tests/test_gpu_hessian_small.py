@@ -1,0 +1,46 @@
+"""GPU parity of the Hessian of layers of few channels: the small-tile kernel (tiles of 32 and 64 channels, chunks of 64
+16-bit or 32 float32 tokens dealt to 8 or 16 wavefronts) at the edges of its tiles and chunks, and the workspace path such
+layers take in long calls.  Bar: relative Frobenius error 1e-5 as everywhere, and the same bits from the same call."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # dtype, n, t, workspace ("none", "asked", "short": one that is too small and therefore ignored)
+    (torch.float32, 1, 1, "none"), (torch.float32, 31, 33, "none"), (torch.float32, 33, 31, "none"), (torch.float32, 256, 4100, "none"),
+    (torch.float32, 1013, 517, "none"), (torch.float32, 3072, 96, "none"),
+    (torch.float16, 1, 5, "none"), (torch.float16, 32, 64, "none"), (torch.float16, 65, 1025, "none"), (torch.float16, 1536, 130, "none"),
+    (torch.bfloat16, 999, 513, "none"), (torch.bfloat16, 1025, 8 * 64 + 1, "none"),
+    (torch.float16, 256, 32769, "asked"), (torch.bfloat16, 513, 40000, "asked"), (torch.float16, 2040, 33000, "asked"),
+    (torch.float16, 300, 33000, "short"), (torch.float16, 300, 33000, "none"),
+]
+
+
+@pytest.mark.parametrize("dtype,n,t,workspace", CASES)
+def test_hessian_of_few_channels(dtype, n, t, workspace):
+    import paper_2210_17323_amd as g
+    print(f"hessian small {dtype} n={n} t={t} workspace {workspace}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(n + t)
+    ld = (t + 7) // 8 * 8
+    X = torch.full((n, ld), float("nan"), dtype=dtype, device="cuda")[:, :t]        # what lies between the rows is not read into sums
+    X.copy_(torch.randn((n, t), generator=gen, device="cuda") + 0.1)
+    need = g.gptq_hessian_accumulate_workspace_bytes(n, t, dtype)
+    assert (need > 0) == (workspace != "none" or (dtype != torch.float32 and n >= 256 and t > 32768))
+    ws = None
+    if workspace == "asked":
+        ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
+    elif workspace == "short":
+        ws = torch.full((need - 1,), 0xFF, dtype=torch.uint8, device="cuda")
+    out = []
+    for _ in range(2):
+        H = torch.ones((n, n), dtype=torch.float32, device="cuda")                  # accumulates
+        g.gptq_hessian_accumulate(H, X, ws)
+        g.gptq_hessian_symmetrize(H)
+        out.append(H)
+    x = X.double()
+    want = 1.0 + 2.0 * (x @ x.T)
+    err = float((out[0].double() - want).norm() / want.norm())
+    print(f"  rel_fro={err:.3e}", flush=True)
+    assert err <= 1e-5
+    assert torch.equal(out[0], out[1])
