@@ -261,8 +261,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 3))) voi
     else          gemm_tile<B_IS_NK, true>(g, m0, n0, As, Bs);
 }
 
-// ---- large-tile variants: 256 x 128 or 256 x 256 tile, operands copied global -> LDS directly, 4 stages ----
-// Used when M % 256 == 0, N % 128 == 0 (256 for the wide tile) and K % 64 == 0.  8 wavefronts, each 64 x 64 = 2 x 2 MFMA tiles.
+// ---- direct-to-LDS variants: 256 x 128, 256 x 256 or 128 x 128 tile, operands copied global -> LDS, 4 stages ----
+// Used when M is a multiple of the tile height and K of 64; N may end inside a tile (B's last columns, or rows, are read again
+// in the place of those past the end, and what comes of them is not stored).  8 wavefronts, each 64 x 64 = 2 x 2 MFMA tiles
+// (128 x 64 of the wide tile); 4 wavefronts and half the LDS for the small tile, so that two workgroups share a CU.
 // A stage holds 16 values of K: the A panel as [256 rows][16 floats] and, for B given as [N x K], the B
 // panel as [128 rows][16 floats]; rows are 64 bytes = 4 chunks of 16 bytes, and global_load_lds_dwordx4
 // lays 16 such rows down per instruction with the chunk index XOR-swizzled by (row / 4) % 4 on the global
@@ -276,17 +278,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 3))) voi
 // k+2 is in flight and step k+3 is being issued; one bare s_barrier per step.
 constexpr int LM = 256, LN = 128, LK = 16;
 constexpr int WIDE_MIN_TILES = 512;
-constexpr int LA_BYTES = LM * LK * 4;
+constexpr int SMALL_MAX_LARGE_TILES = 256;
 
-// WIDE: the tile is 256 x 256 and a wavefront owns 128 x 64 (4 x 2 MFMA tiles): a third fewer copy instructions and
-// a quarter fewer LDS reads per flop, and half as many tile prologues and C read-modify-writes per flop.
-template <bool B_IS_NK, bool WIDE>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_f32_dma_kernel(GemmArgs g) {
+// TILE_WIDE: a wavefront owns 128 x 64 (4 x 2 MFMA tiles): a third fewer copy instructions and a quarter fewer LDS reads per
+// flop, and half as many tile prologues and C read-modify-writes per flop.  TILE_SMALL: four times as many workgroups for
+// products that do not fill the chip (a 3072 x 1024 x 1024 product is 96 tiles of 256 x 128, 131 us each at the peak rate).
+enum { TILE_TALL = 0, TILE_WIDE = 1, TILE_SMALL = 2 };
+
+template <bool B_IS_NK, int TILE>
+__global__ __launch_bounds__(TILE == TILE_SMALL ? 256 : 512) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_f32_dma_kernel(GemmArgs g) {
+    constexpr bool WIDE = TILE == TILE_WIDE;
+    constexpr int TM_ = TILE == TILE_SMALL ? 128 : LM;    // tile rows
     constexpr int TN_ = WIDE ? 256 : LN;                  // tile columns
     constexpr int SM = WIDE ? 4 : 2;                      // 32-row MFMA tiles per wavefront
-    constexpr int NB = TN_ / 128;                         // B copies per wavefront per step
+    constexpr int NB = TILE == TILE_TALL ? 1 : 2;         // B copies per wavefront per step
     constexpr int CP = 2 + NB;                            // copies per wavefront per step
-    constexpr int LB_ = TN_ * LK * 4, LSTAGE_ = LA_BYTES + LB_;
+    constexpr int LA_ = TM_ * LK * 4, LB_ = TN_ * LK * 4, LSTAGE_ = LA_ + LB_;
     __shared__ __attribute__((aligned(16))) unsigned char st0[LSTAGE_];
     __shared__ __attribute__((aligned(16))) unsigned char st1[LSTAGE_];
     __shared__ __attribute__((aligned(16))) unsigned char st2[LSTAGE_];
@@ -297,7 +304,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // them are slots of its own XCD's share.
     for (int64_t wslot = blockIdx.x; wslot < g.slots; wslot += gridDim.x) {
     int64_t m0, n0;
-    if (!TileOrder::origin(g, wslot, LM, TN_, m0, n0)) continue;
+    if (!TileOrder::origin(g, wslot, TM_, TN_, m0, n0)) continue;
 
     // 8 wavefronts (two per SIMD, so one can issue MFMAs while the other waits on LDS or the barrier);
     // wavefront (wm, wn) owns rows wm*32*SM.., columns wn*64.. of the tile: SM x 2 MFMA tiles.
@@ -305,13 +312,21 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int wm = WIDE ? wave >> 2 : wave >> 1, wn = WIDE ? wave & 3 : wave & 1;
     const int l32 = lane & 31, lhi = lane >> 5;
 
-    // copies: A panel = 16 instructions of 16 rows (2 per wavefront); B panel = 8 or 16 instructions (NB per wavefront):
-    // for B given as [N x K] 16 rows each, for [K x N] 1 KB of consecutive n (two k rows of 128, or one of 256)
+    // copies: A panel = one instruction per 16 rows (2 per wavefront); B panel = 8 or 16 instructions (NB per wavefront): for B
+    // given as [N x K] 16 rows each, for [K x N] 1 KB of consecutive n (two k rows of 128, or one of 256).  Past the last
+    // column the last row of B, or the 16 bytes that hold its last column, are read again (rows are a multiple of 16 bytes apart).
     const int crow = lane >> 2, cchunk = (lane & 3) ^ ((lane >> 4) & 3);
     const float* srcA = g.A + (m0 + wave * 32 + crow) * g.lda + cchunk * 4;              // + i*16 rows, + k0
-    const float* srcB = B_IS_NK ? g.B + (n0 + wave * 16 * NB + crow) * g.ldb + cchunk * 4  // + i*16 rows, + k0
-                      : WIDE    ? g.B + (int64_t)(wave * 2) * g.ldb + n0 + lane * 4        // + i k-rows, + k0*ldb
-                                : g.B + (int64_t)(wave * 2 + lhi) * g.ldb + n0 + l32 * 4;  // + k0*ldb
+    constexpr int NSRC = TILE == TILE_SMALL ? 2 : 1;         // the wide tile's second copy is one row on (its columns are whole)
+    const float* srcB[NSRC];
+#pragma unroll
+    for (int i = 0; i < NSRC; ++i) {
+        if (B_IS_NK) srcB[i] = g.B + min(n0 + (wave * NB + i) * 16 + crow, g.N - 1) * g.ldb + cchunk * 4;                              // + k0
+        else {
+            const int64_t col = min(n0 + (WIDE ? lane : l32) * 4, (g.N - 1) & ~(int64_t)3);
+            srcB[i] = g.B + (int64_t)(WIDE ? wave * 2 + i : (wave * NB + i) * 2 + lhi) * g.ldb + col;                                   // + k0*ldb
+        }
+    }
     auto issue_copies = [&](unsigned char* stage, int64_t k0) {
 #pragma unroll
         for (int i = 0; i < 2; ++i)
@@ -319,9 +334,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                                              (__attribute__((address_space(3))) void*)(stage + (wave * 2 + i) * 1024), 16, 0, 0);
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
-            const float* sb = B_IS_NK ? srcB + (int64_t)i * 16 * g.ldb + k0 : srcB + (k0 + i) * g.ldb;
+            const float* sb = TILE == TILE_SMALL ? (B_IS_NK ? srcB[i % NSRC] + k0 : srcB[i % NSRC] + k0 * g.ldb)
+                                                 : (B_IS_NK ? srcB[0] + (int64_t)i * 16 * g.ldb + k0 : srcB[0] + (k0 + i) * g.ldb);
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)sb,
-                                             (__attribute__((address_space(3))) void*)(stage + LA_BYTES + (wave * NB + i) * 1024), 16, 0, 0);
+                                             (__attribute__((address_space(3))) void*)(stage + LA_ + (wave * NB + i) * 1024), 16, 0, 0);
         }
     };
 
@@ -334,9 +350,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             for (int i = 0; i < 16; ++i) acc[s][t][i] = 0.f;
 
     const int rowA = (wm * 32 * SM + l32) * 64;                  // + s * 2048
-    const int rowB = LA_BYTES + (wn * 64 + l32) * 64;            // NK: + t * 2048
+    const int rowB = LA_ + (wn * 64 + l32) * 64;                 // NK: + t * 2048
     const int swz = (l32 >> 2) & 3;
-    const int colB = LA_BYTES + (wn * 64 + l32) * 4;             // KN: + t * 128 + krow * TN_ * 4
+    const int colB = LA_ + (wn * 64 + l32) * 4;                  // KN: + t * 128 + krow * TN_ * 4
     // One 16-deep step out of `cur`.  The fragments of its first 8 k are already in registers (fetched at the
     // end of the previous step); those of the second 8 are read from LDS while the first half's MFMAs run, and
     // the first fragments of the next step (`nxt`, whose copies have landed) while the second half's run.
@@ -420,6 +436,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int s = 0; s < SM; ++s)
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
+            if (n0 + wn * 64 + t * 32 + l32 >= g.N) continue;       // a lane past the last column
             float* cbase = g.C + (m0 + wm * 32 * SM + s * 32 + 4 * lhi) * g.ldc + n0 + wn * 64 + t * 32 + l32;
             float cv[16];
             if (!g.overwrite) {
@@ -448,7 +465,11 @@ int launch_gemm_f32(const GemmF32& p, hipStream_t s) {
     g.overwrite = p.overwrite; g.upper_only = p.upper_only; g.crow0 = p.crow0; g.ccol0 = p.ccol0;
     g.a_upper_tri = p.a_upper_tri;
     g.b_upper_tri = p.b_upper_tri && !p.b_is_nk;
-    const bool large = (p.M % LM == 0) && (p.N % LN == 0) && (g.K % (4 * LK) == 0) && g.K > 0 && aligned(p.C, 4);
+    // Direct-to-LDS kernels: whole tile rows and K steps.  The rows decide the tile height; the columns may end inside a tile
+    // (not in a triangular launch, whose tiles are numbered by whole ones).
+    const bool whole_k = (g.K % (4 * LK) == 0) && g.K > 0 && aligned(p.C, 4);
+    const bool n_ok = p.N % LN == 0 || (p.N > LN && !p.upper_only && !p.b_upper_tri);
+    const bool large = (p.M % LM == 0) && n_ok && whole_k;
     // 256 x 256 tiles when they still give every CU a couple of tiles (measured: 3-8 % faster on large rectangular
     // and symmetric-update launches; not on the skinny triangular products, whose tiles differ in K length)
     bool wide = large && !p.a_upper_tri && (p.N % 256 == 0) && (p.M / LM) * (p.N / 256) >= WIDE_MIN_TILES;
@@ -461,12 +482,17 @@ int launch_gemm_f32(const GemmF32& p, hipStream_t s) {
         const double en = 0.77 * (double)tn_ / (double)(ceil_div(tn_, 256) * 256);
         wide = ew > en;
     }
-    const int64_t tm = large ? p.M / LM : ceil_div(p.M, TM), tn = wide ? p.N / 256 : (large ? p.N / LN : ceil_div(p.N, TN));
+    // 128 x 128 tiles where the larger ones leave CUs without any, and for row counts that are only whole tiles of 128
+    const bool small = whole_k && n_ok && (p.M % 128 == 0) && !p.max_workgroups &&
+                       (!large || (p.M / LM) * ceil_div(p.N, LN) < SMALL_MAX_LARGE_TILES);
+    if (small) wide = false;
+    const bool dma = large || small;
+    const int64_t th = small ? 128 : (large ? LM : TM), tw = wide ? 256 : (dma ? LN : TN);      // tile height and width
+    const int64_t tm = ceil_div(p.M, th), tn = ceil_div(p.N, tw);
     if (tm * tn > 0x7ffffff0LL) return fail(GPTQ_ERR_UNSUPPORTED, "gemm_f32: too many tiles");
     g.tiles_m = (int)tm; g.tiles_n = (int)tn;
     g.total = tm * tn;
     g.tri_ratio = 0;
-    const int64_t th = large ? LM : TM, tw = wide ? 256 : (large ? LN : TN);      // tile height and width
     if (p.upper_only && p.M == p.N && p.crow0 == p.ccol0 && th % tw == 0 && tn >= tm * (th / tw)) {
         g.tri_ratio = (int)(th / tw);
         g.total = TileOrder::triangle_total(g.tiles_m, g.tiles_n, g.tri_ratio);
@@ -476,14 +502,13 @@ int launch_gemm_f32(const GemmF32& p, hipStream_t s) {
     int64_t wgs = g.slots;
     if (large && p.max_workgroups >= NXCD && wgs > p.max_workgroups) wgs = p.max_workgroups / NXCD * NXCD;
     dim3 grid((unsigned)wgs);
-    if (large) {
-        if (wide) {
-            if (p.b_is_nk) hipLaunchKernelGGL((gemm_f32_dma_kernel<true, true>), grid, dim3(512), 0, s, g);
-            else           hipLaunchKernelGGL((gemm_f32_dma_kernel<false, true>), grid, dim3(512), 0, s, g);
-        } else {
-            if (p.b_is_nk) hipLaunchKernelGGL((gemm_f32_dma_kernel<true, false>), grid, dim3(512), 0, s, g);
-            else           hipLaunchKernelGGL((gemm_f32_dma_kernel<false, false>), grid, dim3(512), 0, s, g);
-        }
+    if (dma) {
+        const int tile = small ? TILE_SMALL : (wide ? TILE_WIDE : TILE_TALL);
+#define GPTQ_GEMM(T)                                                                                                        \
+        if (p.b_is_nk) hipLaunchKernelGGL((gemm_f32_dma_kernel<true, T>), grid, dim3(T == TILE_SMALL ? 256 : 512), 0, s, g);   \
+        else           hipLaunchKernelGGL((gemm_f32_dma_kernel<false, T>), grid, dim3(T == TILE_SMALL ? 256 : 512), 0, s, g)
+        if (tile == TILE_SMALL) { GPTQ_GEMM(TILE_SMALL); } else if (tile == TILE_WIDE) { GPTQ_GEMM(TILE_WIDE); } else { GPTQ_GEMM(TILE_TALL); }
+#undef GPTQ_GEMM
     } else {
         if (p.b_is_nk) hipLaunchKernelGGL(gemm_f32_kernel<true>, grid, dim3(256), 0, s, g);
         else           hipLaunchKernelGGL(gemm_f32_kernel<false>, grid, dim3(256), 0, s, g);

@@ -126,13 +126,19 @@ static_assert(QOB == SPLIT_K, "the split products take exactly one outer block a
 // workgroup) when rows and columns come in whole tiles and the launch fills the chip well (split_pays).
 static bool split_shapes_ok(int64_t r, int64_t n) { return r >= 256 && r % 256 == 0 && n % 256 == 0 && n >= 2 * QOB; }
 
-struct QuantWs { size_t wk, e, pk, ub, rt, pa, pb, pr, total; int64_t ldk; bool split; };
+// Rows of the working matrix and of the error panels in the workspace: whole tiles of the deferred updates, so that a layer
+// of any row count takes the large-tile kernels (3000 rows x 5120 columns: 190-250 us an update through the guarded
+// kernel, 60-110 so).  The rows past r are never written by anything but these updates and never read by anything else.
+static int64_t padded_rows(int64_t r) { return r >= 64 ? (int64_t)round_up((size_t)r, 256) : std::max<int64_t>(r, 1); }
+
+struct QuantWs { size_t wk, e, pk, ub, rt, pa, pb, pr, total; int64_t ldk, rows; bool split; };
 static QuantWs quant_ws_layout(int64_t r, int64_t n, int64_t group) {
     QuantWs l;
     l.ldk = (int64_t)round_up((size_t)std::max<int64_t>(n, 1), 4);
+    l.rows = padded_rows(r);
     l.wk = 0;
-    size_t off = round_up((size_t)std::max<int64_t>(r, 1) * l.ldk * sizeof(float), 256);
-    l.e = off; off += 2 * round_up((size_t)std::max<int64_t>(r, 1) * QOB * sizeof(float), 256);   // two error panels (look-ahead)
+    size_t off = round_up((size_t)l.rows * l.ldk * sizeof(float), 256);
+    l.e = off; off += 2 * round_up((size_t)l.rows * QOB * sizeof(float), 256);   // two error panels (look-ahead)
     l.pk = off; off += round_up(STRIP_PACK_BYTES, 256);                                             // four outer blocks of the factor as the strip kernel reads them
     const bool inner_groups = group != 0 && factor_form_group_supported(group);
     l.ub = off;                                                                                       // factor form with groups: every U_bb
@@ -140,10 +146,10 @@ static QuantWs quant_ws_layout(int64_t r, int64_t n, int64_t group) {
     l.rt = off;                                                                                       // ... and R with its column blocks scaled by them
     if (inner_groups) off += round_up((size_t)std::max<int64_t>(n, 1) * l.ldk * sizeof(float), 256);
     // split products (gemm_split.hip): the bf16 pieces of an error panel, of the next outer block's rows of U and of all rows beyond
-    l.split = split_shapes_ok(r, n);
+    l.split = split_shapes_ok(l.rows, n);
     l.pa = l.pb = l.pr = off;
     if (l.split) {
-        l.pa = off; off += round_up(split_planes_bytes(r), 256);
+        l.pa = off; off += round_up(split_planes_bytes(l.rows), 256);
         l.pb = off; off += round_up(split_planes_bytes(QOB), 256);
         l.pr = off; off += round_up(split_planes_bytes(n), 256);
     }
@@ -210,7 +216,8 @@ static int alg1_run(bool rf, const void* W, int wdtype, int64_t ldw, int64_t r, 
     char* base = static_cast<char*>(ws);
     float* Wk = reinterpret_cast<float*>(base + lay.wk);
     float* Ebuf[2] = {reinterpret_cast<float*>(base + lay.e),
-                      reinterpret_cast<float*>(base + lay.e + round_up((size_t)r * QOB * sizeof(float), 256))};
+                      reinterpret_cast<float*>(base + lay.e + round_up((size_t)lay.rows * QOB * sizeof(float), 256))};
+    const int64_t rows = lay.rows;
     const int maxq = (grid == GPTQ_GRID_TERNARY) ? 2 : ((1 << bits) - 1);
     const int64_t ngroups = group ? n / group : 1;
     const int want_grid = group == 0;
@@ -308,18 +315,18 @@ static int alg1_run(bool rf, const void* W, int wdtype, int64_t ldw, int64_t r, 
             rest_done = nullptr;
             const float alpha = 1.f;                 // the U form's panel holds -e
             const bool full = lay.split && ob == QOB && o1 - o0 == QOB;
-            const bool split_strip = full && o2 - o1 == QOB && split_pays((r / 256) * (QOB / 256));
-            const bool split_rest = full && o2 < n && split_pays((r / 256) * ((n - o2) / 256));
+            const bool split_strip = full && o2 - o1 == QOB && split_pays((rows / 256) * (QOB / 256));
+            const bool split_rest = full && o2 < n && split_pays((rows / 256) * ((n - o2) / 256));
             SplitGemm sg{};
-            sg.A_planes = Pa; sg.A_zero = split_zero_block(Pa, r); sg.a_panel0 = 0;
-            sg.ldc = lay.ldk; sg.alpha = alpha; sg.tiles_m = (int)(r / 256);
+            sg.A_planes = Pa; sg.A_zero = split_zero_block(Pa, rows); sg.a_panel0 = 0;
+            sg.ldc = lay.ldk; sg.alpha = alpha; sg.tiles_m = (int)(rows / 256);
             GemmF32 g{};
             g.A = E; g.lda = QOB; g.B = Bm + o0 * ldb + o1; g.ldb = ldb; g.C = Wk + o1; g.ldc = lay.ldk;
-            g.M = r; g.N = o2 - o1; g.K = o1 - o0; g.alpha = alpha; g.b_is_nk = false; g.overwrite = false;
+            g.M = rows; g.N = o2 - o1; g.K = o1 - o0; g.alpha = alpha; g.b_is_nk = false; g.overwrite = false;
             if (split_strip) {
                 // the pieces of the error panel are made here, for both parts (the helper stream's last reader of the
                 // buffer is what the wait above was for); those of U's rows for the next outer block's columns as well
-                if (int rc = launch_split_rows(E, QOB, r, Pa, s)) return rc;
+                if (int rc = launch_split_rows(E, QOB, rows, Pa, s)) return rc;
                 if (int rc = launch_split_cols(Bm + o0 * ldb + o1, ldb, QOB, Pb, s)) return rc;
                 if (int rc = ts.mark(s, &quantized)) return rc;
                 sg.B_planes = Pb; sg.B_zero = split_zero_block(Pb, QOB); sg.b_panel0 = 0;
@@ -336,7 +343,7 @@ static int alg1_run(bool rf, const void* W, int wdtype, int64_t ldw, int64_t r, 
                 }
                 if (int rc = ts.wait(s2, quantized)) return rc;
                 if (split_rest) {
-                    if (!split_strip) { if (int rc = launch_split_rows(E, QOB, r, Pa, s2)) return rc; }
+                    if (!split_strip) { if (int rc = launch_split_rows(E, QOB, rows, Pa, s2)) return rc; }
                     sg.B_planes = Pr; sg.B_zero = split_zero_block(Pr, n - o2); sg.b_panel0 = 0;
                     sg.C = Wk + o2; sg.tiles_n = (int)((n - o2) / 256);
                     if (int rc = launch_gemm_split(sg, s2)) return rc;
