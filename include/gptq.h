@@ -53,7 +53,7 @@ GPTQ_API int gptq_version(void);
 GPTQ_API const char* gptq_last_error(void);
 
 /*
- * The only state the library keeps between calls: three helper streams (default priority, non-blocking) and 32 events per
+ * The only state the library keeps between calls: two helper streams (default priority, non-blocking) and 32 events per
  * host thread and device, created by the first call of gptq_damp_cholesky* / gptq_quantize_layer* on that thread and
  * device and used by the later ones (two caller streams of one thread therefore share them: their calls are correct
  * but do not overlap each other's helper work).  gptq_release_thread_resources waits for the calling thread's helper
@@ -145,7 +145,7 @@ GPTQ_API int gptq_damp_cholesky_inverse(float* H_U, int64_t ld, int64_t n, float
  * Step 2 for callers that cannot allocate device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc) and therefore cannot bring a workspace: the same kernels and the same
  * result as gptq_damp_cholesky_inverse, with the scratch space in a fixed device array that is part of the
- * library image (float32 kernels only; about 51 MiB, resident on every GPU the library runs on until the process ends).
+ * library image (float32 kernels only; about 55 MiB, resident on every GPU the library runs on until the process ends).
  *
  *   n <= GPTQ_NOALLOC_MAX_N (gptq_noalloc_max_n() returns it); a larger n is GPTQ_ERR_UNSUPPORTED and nothing is
  *   enqueued.  H_U, ld, percdamp, info_dev and the result are as for gptq_damp_cholesky_inverse.

@@ -12,7 +12,7 @@
 //           loses the panel's products;
 //   inverse X_pc = L_pp^-1 X_pc, then X_ic -= L_ip X_pc for the rows below, X = L^-1 in accumulators too.
 // Three barriers a panel.  What bounds it is the chain of 128 pivots, ~150 cycles each, then latency of 8 x 3 barriers and of the
-// load.  Measured: 27 us a block; 37 us when the blocks were 32 x 32 with their columns handed round through LDS.
+// load.  Measured: 28 us a block; 37 us when the blocks were 32 x 32 with their columns handed round through LDS.
 #include "chol_diag.h"
 
 #include <utility>
@@ -40,29 +40,37 @@ __device__ __forceinline__ void fma_bcast16(float& w, float u, float m) {
 }
 
 template <int J, int... K>
-__device__ __forceinline__ void update_right(float (&dx)[PB], float (&px)[PB], float dl, float pl, std::integer_sequence<int, K...>) {
+__device__ __forceinline__ void update_right(float (&dx)[PB], float (&px)[PB], float col, float du, float pu, std::integer_sequence<int, K...>) {
     // columns J + 1 + K: the next pivot's column first
-    ((fma_bcast16<J + 1 + K>(dx[J + 1 + K], dl, dl), fma_bcast16<J + 1 + K>(px[J + 1 + K], dl, pl)), ...);
+    ((fma_bcast16<J + 1 + K>(dx[J + 1 + K], col, du), fma_bcast16<J + 1 + K>(px[J + 1 + K], col, pu)), ...);
 }
 
-// Pivot J: dx[J] and px[J] become the column of L.  A pivot that is not positive leaves NaN on the diagonal of L.
+// Pivot J: dx[J] and px[J] become the column of L.  The update multiplies the column as it stands with the row's entry over the
+// pivot, so that an element loses one product with two roundings; 1 / sqrt(pivot) is the hardware's estimate with one Newton
+// step whose residual 1 - pivot * inv^2 is taken without the rounding of pivot * inv (half an ulp in all: the first digit
+// the whole factorisation loses).  `mine` keeps the pivot of this lane's row.
 template <int J>
-__device__ __forceinline__ void pivot(float (&dx)[PB], float (&px)[PB]) {
+__device__ __forceinline__ void pivot(float (&dx)[PB], float (&px)[PB], float& mine, int l16) {
     asm volatile("s_nop 1" : "+v"(dx[J]));              // last written by a statement the compiler cannot see into
     const float dd = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, dx[J]), 0x150 + J, 0xf, 0xf, true));     // row_newbcast
-    float inv = __frsqrt_rn(dd);
-    inv = inv * fmaf(-0.5f * dd * inv, inv, 1.5f);      // one Newton step: 1 / sqrt(dd) to an ulp
+    const float est = __builtin_amdgcn_rsqf(dd);
+    const float t = dd * est;
+    const float e = fmaf(-fmaf(dd, est, -t), est, fmaf(-t, est, 1.f));
+    const float inv = fmaf(0.5f * est, e, est);
+    mine = l16 == J ? dd : mine;
+    float col = dx[J];
     dx[J] *= inv;
     px[J] *= inv;
     if constexpr (J + 1 < PB) {
-        asm volatile("s_nop 1" : "+v"(dx[J]), "+v"(px[J]));          // the wait states between a vector write and a DPP read
-        update_right<J>(dx, px, dx[J], px[J], std::make_integer_sequence<int, PB - 1 - J>{});
+        const float du = dx[J] * inv, pu = px[J] * inv;
+        asm volatile("s_nop 1" : "+v"(col));            // the wait states between a vector write and a DPP read
+        update_right<J>(dx, px, col, du, pu, std::make_integer_sequence<int, PB - 1 - J>{});
     }
 }
 
 template <int... J>
-__device__ __forceinline__ void pivots(float (&dx)[PB], float (&px)[PB], std::integer_sequence<int, J...>) {
-    (pivot<J>(dx, px), ...);
+__device__ __forceinline__ void pivots(float (&dx)[PB], float (&px)[PB], float& mine, int l16, std::integer_sequence<int, J...>) {
+    (pivot<J>(dx, px, mine, l16), ...);
 }
 
 __device__ __forceinline__ void barrier_lds() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
@@ -134,20 +142,19 @@ __global__ __launch_bounds__(64 * WAVES) void diag_block_kernel(float* Hblk, int
                     px[4 * q + e] = own ? (l16 == 4 * q + e ? 1.f : 0.f) : x[e];
                 }
             }
-            pivots(dx, px, std::make_integer_sequence<int, PB>{});
+            float mine = 0.f;
+            pivots(dx, px, mine, l16, std::make_integer_sequence<int, PB>{});
             {
-                float mine = dx[0];                      // L[l16][l16]
-#pragma unroll
-                for (int k = 1; k < PB; ++k) mine = l16 == k ? dx[k] : mine;
                 const uint32_t bad = (uint32_t)__ballot(!(mine > 0.f)) & 0xffffu;
                 if (bad && bad_col < 0) bad_col = PB * p + __builtin_ctz(bad);
             }
+            const float root = __fsqrt_rn(mine);         // the diagonal of L
             if (row >= PB * p) {
                 // R: row 127 - row, columns 127 - 16 p - 15 .. 127 - 16 p
                 const int a = DB - 1 - row, b0 = DB - 1 - PB * p - 15;
                 float v[PB];
 #pragma unroll
-                for (int k = 0; k < PB; ++k) v[k] = own ? (k <= l16 ? dx[k] : 0.f) : px[k];
+                for (int k = 0; k < PB; ++k) v[k] = own ? (k < l16 ? dx[k] : (k == l16 ? root : 0.f)) : px[k];
                 if (a < nbk) {
                     float* dst = Hblk + (int64_t)a * ld + b0;
 #pragma unroll
@@ -178,8 +185,10 @@ __global__ __launch_bounds__(64 * WAVES) void diag_block_kernel(float* Hblk, int
             if (cc[s] > p) {
                 const floatx4 a = *reinterpret_cast<const floatx4*>(&pn[(PB * ci[s] + l16) * PP + 4 * kq]);
                 const floatx4 b = *reinterpret_cast<const floatx4*>(&pn[(PB * cc[s] + l16) * PP + 4 * kq]);
+                floatx4 v = {0.f, 0.f, 0.f, 0.f};        // the panel's 16 products, subtracted at once: one by one, each would
 #pragma unroll
-                for (int e = 0; e < 4; ++e) ch[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(-a[e], b[e], ch[s], 0, 0, 0);
+                for (int e = 0; e < 4; ++e) v = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], v, 0, 0, 0);      // be rounded at the size of the element
+                ch[s] -= v;
             }
         if (wave < p) {
             floatx4 x = {0.f, 0.f, 0.f, 0.f};            // X_p,wave = L_pp^-1 X_p,wave, in place
@@ -195,8 +204,10 @@ __global__ __launch_bounds__(64 * WAVES) void diag_block_kernel(float* Hblk, int
         for (int s = 0; s < XT; ++s)
             if (xi[s] > p && xc[s] <= p) {
                 const floatx4 a = *reinterpret_cast<const floatx4*>(&pn[(PB * xi[s] + l16) * PP + 4 * kq]);
+                floatx4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int e = 0; e < 4; ++e) xt[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(-a[e], xr[(4 * kq + e) * XP + PB * xc[s] + l16], xt[s], 0, 0, 0);
+                for (int e = 0; e < 4; ++e) v = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], xr[(4 * kq + e) * XP + PB * xc[s] + l16], v, 0, 0, 0);
+                xt[s] -= v;
             }
         {
             const int m = tid >> 5, b = (tid & 31) * 4;  // row of the block, first of four columns of R^-1

@@ -1,0 +1,353 @@
+// Step 2, products with the triangular 1024 x 1024 diagonal block of one outer block (Section 3, Step 3), a strip of 16 RT
+// rows per workgroup and launch.  Rows are independent in both of them:
+//   STRIP_INVERSE  the rows of U_oo = R_oo^-1:           for b first .. last:  U_b = X_b R_bb^-1,    X_c -= U_b R[b, c]   (X = identity)
+//   STRIP_PANEL    the rows above the block:             for b last .. first:  P_b = X_b R_bb^-T,    X_c -= P_b R[c, b]^T (X = H[row, o])
+// X lives in registers as accumulators of v_mfma_f32_16x16x4_f32, of every block of 128 columns wavefront w owns columns 32 w
+// .. 32 w + 31; the current block goes through LDS to become the A operand, first of the product with the inverse of the
+// diagonal block, then -- replaced by its result -- of the products into the blocks still to come, whose B operands come
+// straight from memory, packed once per outer block (launch_pack_triangle).  As launches of their own these were a
+// product of 17 to 50 us per block of 128 columns, one behind the other.  What bounds a strip is its own chain, 8 blocks of up to
+// 8 products [16 RT x 128] x [128 x 128] on one CU; rows per strip grow only once every CU has one (launch_triangle_panel).
+#include "chol_strip.h"
+
+namespace gptq {
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+
+namespace {
+
+constexpr int CB = 128, SB = 8, PW = CB + 4, TILE_WORDS = CB * CB;
+constexpr int PAIRS = SB * (SB - 1) / 2;
+static_assert(TRIANGLE_WORDS == (size_t)(SB + PAIRS) * TILE_WORDS, "chol_strip.h states this size");
+
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// B operand order of a 128 x 128 tile: [wavefront: 32 columns][16 k][even, odd columns][lane][4 k].
+// Tiles: SB inverses of diagonal blocks, then the pairs (s, s'), s < s', of positions in the order of the walk.
+// Workgroup: one half (64 k) of one tile of one outer block.
+__global__ __launch_bounds__(256) void pack_triangle_kernel(const float* R, int64_t ld, int64_t n, const float* dinv, int64_t o_first, int panel, float* out) {
+    __shared__ float tile[CB][65];                       // [k or column][...]: see below
+    const int tid = threadIdx.x;
+    const int64_t o0 = (o_first + blockIdx.y) * (int64_t)(SB * CB);
+    const int nb = (int)((min((int64_t)(SB * CB), n - o0) + CB - 1) / CB);
+    int t = (int)blockIdx.x >> 1;
+    const int h = (int)blockIdx.x & 1;
+    float* dst = out + blockIdx.y * (int64_t)TRIANGLE_WORDS + (int64_t)t * TILE_WORDS;
+    const float* src;
+    int64_t lds_;
+    int64_t rows, cols;                                  // of the source tile that exist
+    if (t < SB) {
+        if (t >= nb) return;
+        const int b = panel ? nb - 1 - t : t;
+        src = dinv + (o0 / CB + b) * (int64_t)TILE_WORDS; lds_ = CB; rows = cols = CB;
+    } else {
+        int q = t - SB, s = 0;
+        for (int left = SB - 1; q >= left; --left) { q -= left; ++s; }
+        const int s2 = s + 1 + q;
+        if (s2 >= nb) return;
+        const int64_t r0 = o0 + (panel ? nb - 1 - s2 : s) * CB, c0 = o0 + (panel ? nb - 1 - s : s2) * CB;
+        src = R + r0 * ld + c0; lds_ = ld; rows = min((int64_t)CB, n - r0); cols = min((int64_t)CB, n - c0);
+    }
+    // B[k][n] = source[k][n], or source[n][k] for the panel (transposed); k in [64 h, 64 h + 64)
+    for (int i = tid; i < CB * 64; i += 256) {
+        int rr, cc;
+        if (panel) { rr = i >> 6; cc = 64 * h + (i & 63); }          // row n, column k
+        else       { rr = 64 * h + (i >> 7); cc = i & 127; }         // row k, column n
+        const float v = (rr < rows && cc < cols) ? src[rr * lds_ + cc] : 0.f;
+        if (panel) tile[rr][cc - 64 * h] = v; else tile[cc][rr - 64 * h] = v;            // tile[n][k]
+    }
+    __syncthreads();
+    for (int i = tid; i < 64 * 32; i += 256) {
+        const int lane = i & 63, ct = (i >> 6) & 1, tt = (i >> 7) & 3, w = i >> 9;
+        const int col = 32 * w + 2 * (lane & 15) + ct, k = 16 * tt + 4 * (lane >> 4);
+        *reinterpret_cast<floatx4*>(dst + (((w * 8 + 4 * h + tt) * 2 + ct) * 64 + lane) * 4) = floatx4{tile[col][k], tile[col][k + 1], tile[col][k + 2], tile[col][k + 3]};
+    }
+}
+
+struct StripTriArgs {
+    float* X; int64_t ldx;              // panel: the rows above the outer block, in place (points at its first column)
+    float* U;                           // inverse: U_oo of the first outer block [1024 x 1024], one after the other
+    const float* packed;                // TRIANGLE_WORDS per outer block
+    int64_t n, o_first, rows;           // panel: o_first is the outer block, rows the rows of the strip range
+};
+
+template <bool PANEL, int RT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void tri_strip_kernel(StripTriArgs g) {
+    constexpr int ROWS = 16 * RT;
+    __shared__ __attribute__((aligned(16))) float ebuf[ROWS * PW];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int l16 = lane & 15, kq = lane >> 4;
+    const int wcol = 32 * wave + 2 * l16;
+    const int64_t o = g.o_first + blockIdx.y, o0 = o * (int64_t)(SB * CB);
+    const int ow = (int)min((int64_t)(SB * CB), g.n - o0);
+    const int nb = (ow + CB - 1) / CB;
+    const int64_t row0 = (int64_t)blockIdx.x * ROWS;     // panel: row of the matrix; inverse: row of the outer block
+    if (!PANEL && row0 >= ow) return;
+    const int s0 = PANEL ? 0 : (int)(row0 / CB);         // position of the first block that is not zero
+    const float* packed = g.packed + blockIdx.y * (int64_t)TRIANGLE_WORDS;
+    auto block_of = [&](int s) { return PANEL ? nb - 1 - s : s; };
+
+    floatx4 acc[SB][RT][2];
+#pragma unroll
+    for (int i = 0; i < SB; ++i) {
+        const int b = block_of(s0 + i);
+        if (PANEL && s0 + i < nb) {
+            const int left = ow - b * CB;                // columns of the block that exist
+            const bool in0 = wcol < left, in1 = wcol + 1 < left;
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float* p = g.X + min(row0 + 16 * rt + 4 * kq + e, g.rows - 1) * g.ldx + b * CB;
+                    floatx2 v = {0.f, 0.f};
+                    if (left >= CB) v = *reinterpret_cast<const floatx2*>(p + wcol);
+                    else { const float v0 = p[in0 ? wcol : 0], v1 = p[in1 ? wcol + 1 : 0]; v = floatx2{in0 ? v0 : 0.f, in1 ? v1 : 0.f}; }
+                    acc[i][rt][0][e] = v[0];
+                    acc[i][rt][1][e] = v[1];
+                }
+        } else {
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int r = (int)(row0 % CB) + 16 * rt + 4 * kq + e;
+                    acc[i][rt][0][e] = (!PANEL && i == 0 && r == wcol) ? 1.f : 0.f;
+                    acc[i][rt][1][e] = (!PANEL && i == 0 && r == wcol + 1) ? 1.f : 0.f;
+                }
+        }
+    }
+    // d = (A in ebuf) * (tile), the tile's halves requested ahead
+    const float* arow = &ebuf[l16 * PW + 4 * kq];
+    floatx4 bf[2][4][2];
+    auto request = [&](const float* p, int h, floatx4 (&dst)[4][2]) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int ct = 0; ct < 2; ++ct) dst[t][ct] = *reinterpret_cast<const floatx4*>(p + wave * (8 * 2 * 256) + lane * 4 + ((4 * h + t) * 2 + ct) * 256);
+    };
+    auto multiply = [&](int h, const floatx4 (&src)[4][2], floatx4 (&d)[RT][2]) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            floatx4 a[RT];
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) a[rt] = *reinterpret_cast<const floatx4*>(arow + 16 * rt * PW + 64 * h + 16 * t);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                    for (int ct = 0; ct < 2; ++ct)
+                        d[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[rt][e], src[t][ct][e], (h == 0 && t == 0 && e == 0) ? floatx4{0.f, 0.f, 0.f, 0.f} : d[rt][ct], 0, 0, 0);
+        }
+    };
+    auto to_lds = [&](const floatx4 (&x)[RT][2], float sign) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                *reinterpret_cast<floatx2*>(&ebuf[(16 * rt + 4 * kq + e) * PW + wcol]) = floatx2{sign * x[rt][0][e], sign * x[rt][1][e]};
+    };
+#pragma unroll 1
+    for (int s = s0; s < nb; ++s) {
+        const int b = block_of(s), later = nb - 1 - s;
+        const float* dtile = packed + (int64_t)s * TILE_WORDS;
+        const float* ptile = packed + (int64_t)(SB + s * (2 * SB - 1 - s) / 2) * TILE_WORDS;         // pair (s, s + 1)
+        request(dtile, 0, bf[0]);
+        to_lds(acc[0], 1.f);
+        lds_barrier();
+        floatx4 out[RT][2];
+        request(dtile, 1, bf[1]);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(0, bf[0], out);
+        __builtin_amdgcn_sched_barrier(0);
+        request(later > 0 ? ptile : dtile, 0, bf[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(1, bf[1], out);
+        lds_barrier();                                   // everybody has read the block
+        to_lds(out, -1.f);                               // as the A operand of what is subtracted
+        lds_barrier();
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int64_t row = row0 + 16 * rt + 4 * kq + e;
+                if (PANEL ? row >= g.rows : row >= ow) continue;
+                float* p = PANEL ? g.X + row * g.ldx + b * CB + wcol : g.U + (o * (int64_t)(SB * CB) + row) * (SB * CB) + b * CB + wcol;
+                const int left = ow - b * CB - wcol;
+                if (left >= 2) *reinterpret_cast<floatx2*>(p) = floatx2{out[rt][0][e], out[rt][1][e]};
+                else if (left == 1) p[0] = out[rt][0][e];
+            }
+#pragma unroll
+        for (int i = 1; i < SB; ++i) {
+            if (i <= later) {
+                const float* p = ptile + (int64_t)(i - 1) * TILE_WORDS;
+                request(p, 1, bf[1]);
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(0, bf[0], acc[i - 1]);
+                __builtin_amdgcn_sched_barrier(0);
+                request(i < later ? p + TILE_WORDS : p, 0, bf[0]);
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(1, bf[1], acc[i - 1]);
+                // the block's products are summed on their own and added once: one by one, each would be rounded at the size of X
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt) { acc[i - 1][rt][0] += acc[i][rt][0]; acc[i - 1][rt][1] += acc[i][rt][1]; }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        lds_barrier();                                   // ... before the next block takes its place
+    }
+}
+
+// ---- one step of the chain inside an outer block: block column b (at j0, nbk columns) after its diagonal block -----------
+//   P = H[o0:j0, b] R_bb^-T  (to `panel`, the final R[o0:j0, b]),   H[o0:j0, o0:j0] -= P P^T  on the 64 x 64 tiles that touch the
+// upper triangle, in ONE launch: a workgroup makes the two 64-row pieces of P that its tile needs itself, from H and the
+// inverse, instead of waiting for another launch to have made them.  That is two more products of 64 x 128 x 64 per tile
+// (6 us of matrix-core time in all), where the launch between two dependent kernels costs 10 to 15.  P goes to a buffer of
+// its own because other workgroups still read H[o0:j0, b]; copy_panel_kernel puts it in its place at the end of the chain.
+struct StepArgs { float* H; int64_t ld; const float* dinv; float* panel; int64_t o0, j0; int m, nbk; };     // panel: [1024 x 1024], column j0 - o0
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) void chol_step_kernel(StepArgs g) {
+    __shared__ __attribute__((aligned(16))) float pi[64 * PW];
+    __shared__ __attribute__((aligned(16))) float pk[64 * PW];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int l16 = lane & 15, kq = lane >> 4;
+    int bk = 0, bi = (int)blockIdx.x;                    // tile (bi, bk), bi <= bk, column by column
+    while (bi > bk) { bi -= bk + 1; ++bk; }
+    // the tile of H this workgroup updates: requested first, used last
+    float* ctile = g.H + (g.o0 + 64 * bi + 4 * kq) * g.ld + g.o0 + 64 * bk + 16 * wave + l16;
+    float cv[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) cv[q] = ctile[(int64_t)(16 * (q >> 2) + (q & 3)) * g.ld];
+    // H[rows of the tile, b] and H[columns of the tile, b]
+    floatx4 hi[8], hk[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        const int q = tid + 256 * t, rr = q >> 5, c = (q & 31) * 4;
+        const float* p = g.H + (g.o0 + 64 * bi + rr) * g.ld + g.j0 + c;
+        const float* r = g.H + (g.o0 + 64 * bk + rr) * g.ld + g.j0 + c;
+        hi[t] = hk[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+        if (c + 4 <= g.nbk) { hi[t] = *reinterpret_cast<const floatx4*>(p); hk[t] = *reinterpret_cast<const floatx4*>(r); }
+        else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) if (c + e < g.nbk) { hi[t][e] = p[e]; hk[t][e] = r[e]; }
+        }
+    }
+    // R_bb^-T as the B operand: B[k][n] = dinv[n][k], zero for k < n; this wavefront's two column tiles 16 ct .. 16 ct + 15
+    const int ct[2] = {wave, 7 - wave};
+    floatx4 bd[2][8];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int t = 0; t < 8; ++t)
+            bd[u][t] = *reinterpret_cast<const floatx4*>(g.dinv + (16 * ct[u] + l16) * CB + 16 * max(t, ct[u]) + 4 * kq);
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        const int q = tid + 256 * t, rr = q >> 5, c = (q & 31) * 4;
+        *reinterpret_cast<floatx4*>(&pi[rr * PW + c]) = hi[t];
+        *reinterpret_cast<floatx4*>(&pk[rr * PW + c]) = hk[t];
+    }
+    lds_barrier();
+    floatx4 xi[2][4], xk[2][4];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+#pragma unroll
+        for (int rt = 0; rt < 4; ++rt) xi[u][rt] = xk[u][rt] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            if (t < ct[u]) continue;                     // the same for the whole wavefront
+#pragma unroll
+            for (int rt = 0; rt < 4; ++rt) {
+                const floatx4 ai = *reinterpret_cast<const floatx4*>(&pi[(16 * rt + l16) * PW + 16 * t + 4 * kq]);
+                const floatx4 ak = *reinterpret_cast<const floatx4*>(&pk[(16 * rt + l16) * PW + 16 * t + 4 * kq]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    xi[u][rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(ai[e], bd[u][t][e], xi[u][rt], 0, 0, 0);
+                    xk[u][rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(ak[e], bd[u][t][e], xk[u][rt], 0, 0, 0);
+                }
+            }
+        }
+    }
+    lds_barrier();                                       // everybody has read H's pieces
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int rr = 16 * rt + 4 * kq + e, c = 16 * ct[u] + l16;
+                pi[rr * PW + c] = xi[u][rt][e];
+                pk[rr * PW + c] = xk[u][rt][e];
+                if (bi == bk && c < g.nbk) g.panel[(int64_t)(64 * bi + rr) * (SB * CB) + (g.j0 - g.o0) + c] = xi[u][rt][e];
+            }
+    lds_barrier();
+    floatx4 acc[4];
+#pragma unroll
+    for (int rt = 0; rt < 4; ++rt) acc[rt] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        const floatx4 b = *reinterpret_cast<const floatx4*>(&pk[(16 * wave + l16) * PW + 16 * t + 4 * kq]);
+#pragma unroll
+        for (int rt = 0; rt < 4; ++rt) {
+            const floatx4 a = *reinterpret_cast<const floatx4*>(&pi[(16 * rt + l16) * PW + 16 * t + 4 * kq]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[rt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], acc[rt], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 16; ++q) ctile[(int64_t)(16 * (q >> 2) + (q & 3)) * g.ld] = cv[q] - acc[q >> 2][q & 3];
+}
+
+// H[o0 + row, o0 + col] = panel[row][col] for the columns of the blocks right of the row's own, ow of them
+__global__ __launch_bounds__(256) void copy_panel_kernel(float* H, int64_t ld, int64_t o0, int ow, const float* panel) {
+    const int row = blockIdx.x, c = threadIdx.x * 4;
+    if (c < (row / CB + 1) * CB || c >= ow) return;
+    const float* src = panel + (int64_t)row * (SB * CB) + c;
+    float* dst = H + (o0 + row) * ld + o0 + c;
+    if (c + 4 <= ow) *reinterpret_cast<floatx4*>(dst) = *reinterpret_cast<const floatx4*>(src);
+    else for (int e = 0; c + e < ow; ++e) dst[e] = src[e];
+}
+
+}  // namespace
+
+int launch_pack_triangle(const float* R, int64_t ld, int64_t n, const float* dinv, int64_t o_first, int64_t count, bool panel, float* packed, hipStream_t s) {
+    hipLaunchKernelGGL(pack_triangle_kernel, dim3(2 * (SB + PAIRS), (unsigned)count), dim3(256), 0, s, R, ld, n, dinv, o_first, (int)panel, packed);
+    GPTQ_LAUNCH_CHECK();
+    return GPTQ_OK;
+}
+
+int launch_triangle_inverse(const float* packed, int64_t n, int64_t o_first, int64_t count, float* Uoo, hipStream_t s) {
+    StripTriArgs g{nullptr, 0, Uoo, packed, n, o_first, 0};
+    hipLaunchKernelGGL((tri_strip_kernel<false, 1>), dim3(SB * CB / 16, (unsigned)count), dim3(256), 0, s, g);
+    GPTQ_LAUNCH_CHECK();
+    return GPTQ_OK;
+}
+
+int launch_triangle_panel(float* X, int64_t ldx, int64_t rows, const float* packed, int64_t n, int64_t o, hipStream_t s) {
+    if (rows <= 0) return GPTQ_OK;
+    StripTriArgs g{X, ldx, nullptr, packed, n, o, rows};
+    if (rows <= 16 * 256) hipLaunchKernelGGL((tri_strip_kernel<true, 1>), dim3((unsigned)ceil_div(rows, 16)), dim3(256), 0, s, g);
+    else if (rows <= 32 * 256) hipLaunchKernelGGL((tri_strip_kernel<true, 2>), dim3((unsigned)ceil_div(rows, 32)), dim3(256), 0, s, g);
+    else hipLaunchKernelGGL((tri_strip_kernel<true, 3>), dim3((unsigned)ceil_div(rows, 48)), dim3(256), 0, s, g);
+    GPTQ_LAUNCH_CHECK();
+    return GPTQ_OK;
+}
+
+int launch_chol_step(float* H, int64_t ld, int64_t o0, int64_t j0, int nbk, const float* dinv_b, float* panel, hipStream_t s) {
+    const int m = (int)(j0 - o0), t = m / 64;
+    if (t == 0) return GPTQ_OK;
+    const StepArgs g{H, ld, dinv_b, panel, o0, j0, m, nbk};
+    hipLaunchKernelGGL(chol_step_kernel, dim3((unsigned)(t * (t + 1) / 2)), dim3(256), 0, s, g);
+    GPTQ_LAUNCH_CHECK();
+    return GPTQ_OK;
+}
+
+int launch_copy_panel(float* H, int64_t ld, int64_t o0, int ow, const float* panel, hipStream_t s) {
+    const int rows = (ow - 1) / CB * CB;                 // the last block of rows has nothing right of it
+    if (rows == 0) return GPTQ_OK;
+    hipLaunchKernelGGL(copy_panel_kernel, dim3((unsigned)rows), dim3(256), 0, s, H, ld, o0, ow, panel);
+    GPTQ_LAUNCH_CHECK();
+    return GPTQ_OK;
+}
+
+}  // namespace gptq

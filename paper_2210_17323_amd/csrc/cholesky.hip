@@ -11,17 +11,21 @@
 //
 // Factorisation, outer blocks o last .. first, inner blocks b last .. first:
 //     R_bb = reverse-Cholesky of the 128 x 128 diagonal block (one workgroup, chol_diag.hip), R_bb^-1 kept
-//     R[0:j0, b] = H[0:j0, b] R_bb^-T                                  (the panel of R above the block, in place)
-//     H[0:j0, outer block's columns left of b] -= R[0:j0, b] R[.., b]^T   (rank 128, confined to the outer block)
-//   after the outer block: H[0:o0, 0:o0] -= R[0:o0, o] R[0:o0, o]^T   (rank 1024, carries the flops)
-//   one step behind, on a stream of its own (only when the inverse is wanted): the row blocks of U_oo = R_oo^-1,
-//     U[b, right] = -R_bb^-1 (R[b, right] U[right, right]), kept dense for the inverse.
+//     P = R[o0:j0, b] = H[o0:j0, b] R_bb^-T ;  H[o0:j0, o0:j0] -= P P^T    (one launch, inside the outer block only)
+//   after the outer block: R[0:o0, o] = H[0:o0, o] R_oo^-T              (strips of rows, one launch, chol_strip.hip)
+//                          H[0:o0, 0:o0] -= R[0:o0, o] R[0:o0, o]^T     (rank 1024, carries the flops)
+// The chain of an outer block is 8 x (27 us diagonal block + 15 us step).  With the panel and the update as products of
+// their own over all rows above it was 8 x (37 + 17 to 50 + 20 to 60 us): 11.5 ms at n = 12288 where this route takes 8.9.
+//
+//   one outer block behind, on a stream of its own (only when the inverse is wanted): U_oo = R_oo^-1, kept dense for the
+//     inverse (chol_strip.hip).
 //
 // Triangular inverse (right-looking, outer block columns k first .. last), with the U_kk kept from the factorisation:
 //     T = -U_kk R[k, right of k] ;  U[above k, right of k] += U[above k, k] T ;  row block k <- T
 //     U[above k, k] <- U[above k, k] U_kk ;  diagonal block <- U_kk
 // Every long product has K = 1024 and an output of (rows above) x (columns to the right): many tiles at every k.
 #include "chol_diag.h"
+#include "chol_strip.h"
 #include "common.h"
 
 #include <mutex>
@@ -89,7 +93,7 @@ static_assert(OB == SPLIT_K, "the split products take exactly one outer block as
 // A rank-1024 update goes through the split-operand kernel (bf16 matrix cores, 256 x 256 tiles) when its tiles fill the
 // chip well (split_pays): the strip of the next outer block has 4 tile columns, the square rest t (t + 1) / 2 tiles.
 
-struct CholWs { float* dinv; float* T; float* T2; int64_t ld2; float* Uoo; float* tmp; unsigned char* planes; unsigned char* planes2; size_t total; };
+struct CholWs { float* dinv; float* T; float* T2; int64_t ld2; float* Uoo; float* tri; float* tri2; unsigned char* planes; unsigned char* planes2; size_t total; };
 CholWs chol_ws_layout(void* ws, int64_t n, bool with_split = true) {
     const size_t n1 = (size_t)std::max<int64_t>(n, 1);
     const size_t nblk = (size_t)ceil_div((int64_t)n1, NB), nouter = (size_t)ceil_div((int64_t)n1, OB);
@@ -103,7 +107,8 @@ CholWs chol_ws_layout(void* ws, int64_t n, bool with_split = true) {
     l.T = static_cast<float*>(at(n1 * OB * sizeof(float)));                  // a column panel [n x 1024]
     l.T2 = static_cast<float*>(at((size_t)OB * l.ld2 * sizeof(float)));      // a row panel [1024 x n]
     l.Uoo = static_cast<float*>(at(nouter * OB * OB * sizeof(float)));       // U_oo of every outer block, dense
-    l.tmp = static_cast<float*>(at((size_t)NB * OB * sizeof(float)));        // one row block of a product
+    l.tri = static_cast<float*>(at(TRIANGLE_WORDS * sizeof(float)));         // an outer block of R packed for its inverse
+    l.tri2 = static_cast<float*>(at(TRIANGLE_WORDS * sizeof(float)));        // ... and for the rows above it
     if (with_split && (int64_t)n1 >= 2 * OB) {                               // split products: bf16 pieces of a column panel
         l.planes = static_cast<unsigned char*>(at(split_planes_bytes((int64_t)n1)));
         l.planes2 = static_cast<unsigned char*>(at(split_planes_bytes((int64_t)n1)));      // ... and of a row block (the inverse)
@@ -144,13 +149,13 @@ static int chol_run(float* H, int64_t ld, int64_t n, float percdamp, void* ws, i
     GPTQ_LAUNCH_CHECK();
 
     // C (+)= alpha A op(B) on stream st
-    struct Opt { bool nk = false, overwrite = false, upper = false, atri = false, btri = false; int64_t crow0 = 0, ccol0 = 0; int cap = 0; };
+    struct Opt { bool nk = false, overwrite = false, upper = false, atri = false, btri = false; int64_t crow0 = 0, ccol0 = 0; };
     auto gemm_on = [&](hipStream_t st, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc,
                        int64_t M, int64_t N, int64_t K, float alpha, const Opt& o) -> int {
         GemmF32 g{};
         g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.C = C; g.ldc = ldc; g.M = M; g.N = N; g.K = K; g.alpha = alpha;
         g.b_is_nk = o.nk; g.overwrite = o.overwrite; g.upper_only = o.upper; g.crow0 = o.crow0; g.ccol0 = o.ccol0;
-        g.a_upper_tri = o.atri; g.b_upper_tri = o.btri; g.max_workgroups = o.cap;
+        g.a_upper_tri = o.atri; g.b_upper_tri = o.btri;
         return launch_gemm_f32(g, st);
     };
     auto copy2d = [&](hipStream_t st, float* dst, int64_t ld_dst, const float* src, int64_t ld_src, int64_t rows, int64_t cols) -> int {
@@ -168,8 +173,7 @@ static int chol_run(float* H, int64_t ld, int64_t n, float percdamp, void* ws, i
     TwoStreams ts;
     if (int rc = ts.open(s, lookahead)) return rc;
     hipStream_t s2 = ts.side;       // long products: panels through U_oo and rank-1024 updates
-    hipStream_t s3 = ts.side2;      // (joined below; carries nothing here)
-    hipStream_t s4 = ts.side3;      // trails the factorisation's chain: the rows of U_oo
+    hipStream_t s3 = ts.side2;      // one outer block behind the factorisation's chain: U_oo and its product
 
     // ---- H + lambda I = R R^T, from the last column backwards.  Two levels: inside an outer block of 1024 columns the
     //      rank-128 updates touch only that block's columns; the rest of the matrix gets one rank-1024 update per block.
@@ -177,51 +181,37 @@ static int chol_run(float* H, int64_t ld, int64_t n, float percdamp, void* ws, i
     for (int64_t o = nouter - 1; o >= 0; --o) {
         const int64_t o0 = o * OB, o1 = std::min<int64_t>(o0 + OB, n), ow = o1 - o0;
         float* Ublk = w.Uoo + o * (int64_t)OB * OB;      // U_oo = R_oo^-1 [ow x ow], leading dimension OB, for the inverse
-        if (want_inverse) {                              // zeros below the diagonal are relied on by the products that read it
-            hipLaunchKernelGGL(fill_zero_kernel, dim3(256), dim3(256), 0, s4, reinterpret_cast<float4*>(Ublk), (int64_t)OB * OB / 4);
-            GPTQ_LAUNCH_CHECK();
-        }
         for (int64_t j0 = (ceil_div(ow, NB) - 1) * NB + o0; j0 >= o0; j0 -= NB) {
             const int nbk = (int)std::min<int64_t>(NB, n - j0);
-            const int64_t j1 = j0 + nbk;
             float* dinv_b = dinv + (j0 / NB) * NB * NB;
             if (int rc = launch_diag_block(H + j0 * ld + j0, ld, nbk, dinv_b, info_dev, (int)j0, s)) return rc;
-            if (j0 > 0) {
-                // R[0:j0, b] = H[0:j0, b] R_bb^-T, the panel of R above the block.  In place: there is a single tile column,
-                // and a workgroup reads all of its own rows before it writes them.
-                Opt po; po.nk = true; po.overwrite = true;
-                if (int rc = gemm_on(s, H + j0, ld, dinv_b, NB, H + j0, ld, j0, nbk, nbk, 1.f, po)) return rc;
-            }
-            if (want_inverse) {
-                // One step behind, on its own stream: the row block of U_oo,
-                // U[b, b] = R_bb^-1,  U[b, right] = -R_bb^-1 (R[b, right] U[right, right])  (U[right, right] upper triangular)
-                hipEvent_t step = nullptr;
-                if (int rc = ts.mark(s, &step)) return rc;
-                if (int rc = ts.wait(s4, step)) return rc;
-                const int64_t d = j0 - o0;               // position of the row block inside U_oo
-                hipLaunchKernelGGL(copy_block_kernel, dim3(64), dim3(256), 0, s4, Ublk + d * OB + d, (int64_t)OB, (const float*)dinv_b, (int64_t)NB, (int64_t)nbk, nbk, 1);
-                GPTQ_LAUNCH_CHECK();
-                if (j1 < o1) {
-                    Opt a; a.overwrite = true; a.btri = true;
-                    if (int rc = gemm_on(s4, H + j0 * ld + j1, ld, Ublk + (d + nbk) * OB + (d + nbk), OB, w.tmp, OB, nbk, o1 - j1, o1 - j1, 1.f, a)) return rc;
-                    Opt c; c.overwrite = true;
-                    if (int rc = gemm_on(s4, dinv_b, NB, w.tmp, OB, Ublk + d * OB + (d + nbk), OB, nbk, o1 - j1, nbk, -1.f, c)) return rc;
-                }
-            }
-            if (j0 > o0) {
-                // H[0:j0, o0:j0] -= R[0:j0, b] R[o0:j0, b]^T (columns of this outer block only; tiles below the diagonal
-                // skipped).  Right-looking: many short tiles, which keeps this serial chain short.
-                Opt uo; uo.nk = true; uo.upper = true; uo.ccol0 = o0;
-                if (int rc = gemm_on(s, H + j0, ld, H + o0 * ld + j0, ld, H + o0, ld, j0, j0 - o0, nbk, -1.f, uo)) return rc;
-            }
+            // inside the outer block: the panel above the diagonal block and the update of what is left, in one launch
+            if (int rc = launch_chol_step(H, ld, o0, j0, nbk, dinv_b, w.T, s)) return rc;
         }
-        if (want_inverse && o1 < n) {
-            // Still on the stream that trails the chain: R[o, right] <- -U_oo R[o, right], which is what the inverse below
-            // needs of this row block.  R[o, right] is final here, no later step of the factorisation reads or writes it,
-            // and the product depends on nothing the inverse computes, so it is taken off the inverse's serial path.
-            Opt a; a.overwrite = true; a.atri = true;
-            if (int rc = gemm_on(s4, Ublk, OB, H + o0 * ld + o1, ld, w.T2, w.ld2, ow, n - o1, ow, -1.f, a)) return rc;
-            if (int rc = copy2d(s4, H + o0 * ld + o1, ld, w.T2, w.ld2, ow, n - o1)) return rc;
+        if (int rc = launch_copy_panel(H, ld, o0, (int)ow, w.T, s)) return rc;
+        if (o0 > 0) {
+            // The rows above the outer block: R[0:o0, o] = H[0:o0, o] R_oo^-T, a strip of rows per workgroup through all of its
+            // blocks in one launch (chol_strip.hip).
+            if (int rc = launch_pack_triangle(H, ld, n, dinv, o, 1, true, w.tri2, s)) return rc;
+            if (int rc = launch_triangle_panel(H + o0, ld, o0, w.tri2, n, o, s)) return rc;
+        }
+        if (want_inverse) {
+            // One outer block behind, on its own stream: U_oo = R_oo^-1, dense with zeros below the diagonal (the products that
+            // read it rely on them), and R[o, right] <- -U_oo R[o, right], which is what the inverse below needs of this row
+            // block.  Both are final here, no later step of the factorisation reads or writes them, and the product
+            // depends on nothing the inverse computes, so it is taken off the inverse's serial path.
+            hipEvent_t chain = nullptr;
+            if (int rc = ts.mark(s, &chain)) return rc;
+            hipLaunchKernelGGL(fill_zero_kernel, dim3(256), dim3(256), 0, s3, reinterpret_cast<float4*>(Ublk), (int64_t)OB * OB / 4);
+            GPTQ_LAUNCH_CHECK();
+            if (int rc = ts.wait(s3, chain)) return rc;
+            if (int rc = launch_pack_triangle(H, ld, n, dinv, o, 1, false, w.tri, s3)) return rc;
+            if (int rc = launch_triangle_inverse(w.tri, n, o, 1, w.Uoo, s3)) return rc;
+            if (o1 < n) {
+                Opt a; a.overwrite = true; a.atri = true;
+                if (int rc = gemm_on(s3, Ublk, OB, H + o0 * ld + o1, ld, w.T2, w.ld2, ow, n - o1, ow, -1.f, a)) return rc;
+                if (int rc = copy2d(s3, H + o0 * ld + o1, ld, w.T2, w.ld2, ow, n - o1)) return rc;
+            }
         }
         // H[0:o0, 0:o0] -= R[0:o0, o] R[0:o0, o]^T (rank 1024, upper tiles), with look-ahead: the columns [p0, o0) of the next
         // outer block are updated first, on the caller's stream, which then goes on to factor that block (short, serial
@@ -272,7 +262,7 @@ static int chol_run(float* H, int64_t ld, int64_t n, float percdamp, void* ws, i
         }
     }
     // everything back on the caller's stream
-    for (hipStream_t st : {s2, s3, s4}) {
+    for (hipStream_t st : {s2, s3}) {
         hipEvent_t done = nullptr;
         if (int rc = ts.mark(st, &done)) return rc;
         if (int rc = ts.wait(s, done)) return rc;
@@ -359,7 +349,7 @@ namespace {
 constexpr int64_t NOALLOC_MAX_N = GPTQ_NOALLOC_MAX_N;
 constexpr size_t NOALLOC_BYTES = (size_t)(NOALLOC_MAX_N / NB) * NB * NB * sizeof(float)      // inverses of the 128 x 128 diagonal blocks
                                  + 3 * (size_t)NOALLOC_MAX_N * OB * sizeof(float)            // a column panel, a row panel, the U_oo blocks
-                                 + (size_t)NB * OB * sizeof(float) + 2048;                   // one row block of a product
+                                 + 2 * TRIANGLE_WORDS * sizeof(float) + 2048;                // an outer block of R, packed twice
 static __device__ __align__(256) unsigned char scratch[NOALLOC_BYTES];
 
 constexpr int MAXDEV = 64;

@@ -28,7 +28,7 @@ struct GemmArgs {
     int b_upper_tri;
     int tiles_m, tiles_n;
     int64_t per_xcd, total;
-    int64_t slots;      // tile slots of the launch: per_xcd * 8 (the large-tile kernels may run them on fewer workgroups)
+    int64_t slots;      // tile slots of the launch: per_xcd * 8
     int tri_ratio;      // > 0: exactly the upper tiles of a square C are enumerated; value = tile rows / tile columns
 };
 
@@ -299,12 +299,8 @@ __global__ __launch_bounds__(TILE == TILE_SMALL ? 256 : 512) __attribute__((amdg
     __shared__ __attribute__((aligned(16))) unsigned char st2[LSTAGE_];
     __shared__ __attribute__((aligned(16))) unsigned char st3[LSTAGE_];
 
-    // The launch may hold fewer workgroups than tiles (a caller that wants CUs left free for other streams): a
-    // workgroup then walks the tile slots w, w + gridDim.x, ...; gridDim.x is a multiple of the XCD count, so all of
-    // them are slots of its own XCD's share.
-    for (int64_t wslot = blockIdx.x; wslot < g.slots; wslot += gridDim.x) {
     int64_t m0, n0;
-    if (!TileOrder::origin(g, wslot, TM_, TN_, m0, n0)) continue;
+    if (!TileOrder::origin(g, blockIdx.x, TM_, TN_, m0, n0)) return;
 
     // 8 wavefronts (two per SIMD, so one can issue MFMAs while the other waits on LDS or the barrier);
     // wavefront (wm, wn) owns rows wm*32*SM.., columns wn*64.. of the tile: SM x 2 MFMA tiles.
@@ -449,8 +445,6 @@ __global__ __launch_bounds__(TILE == TILE_SMALL ? 256 : 512) __attribute__((amdg
                 cbase[(int64_t)(8 * (i >> 2) + (i & 3)) * g.ldc] = g.overwrite ? v : (cv[i] + v);
             }
         }
-    __syncthreads();        // the next tile's first copies overwrite the stages this tile's wavefronts still read
-    }
 }
 
 int launch_gemm_f32(const GemmF32& p, hipStream_t s) {
@@ -483,7 +477,7 @@ int launch_gemm_f32(const GemmF32& p, hipStream_t s) {
         wide = ew > en;
     }
     // 128 x 128 tiles where the larger ones leave CUs without any, and for row counts that are only whole tiles of 128
-    const bool small = whole_k && n_ok && (p.M % 128 == 0) && !p.max_workgroups &&
+    const bool small = whole_k && n_ok && (p.M % 128 == 0) &&
                        (!large || (p.M / LM) * ceil_div(p.N, LN) < SMALL_MAX_LARGE_TILES);
     if (small) wide = false;
     const bool dma = large || small;
@@ -499,9 +493,7 @@ int launch_gemm_f32(const GemmF32& p, hipStream_t s) {
     }
     g.per_xcd = ceil_div(g.total, NXCD);
     g.slots = g.per_xcd * NXCD;
-    int64_t wgs = g.slots;
-    if (large && p.max_workgroups >= NXCD && wgs > p.max_workgroups) wgs = p.max_workgroups / NXCD * NXCD;
-    dim3 grid((unsigned)wgs);
+    dim3 grid((unsigned)g.slots);
     if (dma) {
         const int tile = small ? TILE_SMALL : (wide ? TILE_WIDE : TILE_TALL);
 #define GPTQ_GEMM(T)                                                                                                        \
