@@ -6,7 +6,7 @@
 //     v_mfma_f32_16x16x4_f32: of every block of 128 columns wavefront w owns columns 32 w .. 32 w + 31.  The update of the
 //     later blocks, acc[later] += E_b M[b, later], reads E_b from LDS (A operand) and M straight from memory (B operand:
 //     a workgroup uses every element of M once, so LDS would add nothing); acc[i] of one block becomes acc[i - 1] of
-//     the next in the matrix instruction itself.
+//     the next, where its products are summed.
 //   * A block is walked by one wavefront per 16 rows: the 16 lanes of a DPP row are 16 weight rows, the four DPP rows
 //     share the columns of those 16 rows, DPP row c holding columns 4 i + c in register i.  Four columns at a time
 //     (a "quad", register i of the four DPP rows) are broadcast to all lanes and walked there redundantly -- grid value,
@@ -544,7 +544,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
                     for (int rt = 0; rt < RT; ++rt) af[t][rt] = *reinterpret_cast<const floatx4*>(arow + 16 * rt * PW + 16 * t);
             }
-            auto multiply = [&](int half_, const floatx4 (&src)[4][2], const floatx4 (&c)[RT][2], floatx4 (&d)[RT][2]) {
+            auto multiply = [&](int half_, const floatx4 (&src)[4][2], floatx4 (&d)[RT][2]) {
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
                     floatx4 a[RT];
@@ -559,7 +559,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
                             for (int ct = 0; ct < 2; ++ct)
-                                d[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[rt][e], src[t][ct][e], (t == 0 && e == 0) ? c[rt][ct] : d[rt][ct], 0, 0, 0);
+                                d[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[rt][e], src[t][ct][e], (half_ == 0 && t == 0 && e == 0) ? floatx4{0.f, 0.f, 0.f, 0.f} : d[rt][ct], 0, 0, 0);
                 }
             };
             // The fences keep every request ahead of the products it runs beside (left alone, the compiler moves the loads
@@ -576,11 +576,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                     const int h = 2 * (i - 1);
                     request(h + AHEAD - 1, bf[(h + AHEAD - 1) % AHEAD]);
                     __builtin_amdgcn_sched_barrier(0);
-                    multiply(0, bf[h % AHEAD], acc[i], acc[i - 1]);
+                    multiply(0, bf[h % AHEAD], acc[i - 1]);
                     __builtin_amdgcn_sched_barrier(0);
                     request(h + AHEAD, bf[h % AHEAD]);
                     __builtin_amdgcn_sched_barrier(0);
-                    multiply(1, bf[(h + 1) % AHEAD], acc[i - 1], acc[i - 1]);
+                    multiply(1, bf[(h + 1) % AHEAD], acc[i - 1]);
+                    // The block's 128 products are summed on their own, in the place the block moves to, and added once.  Taken one by
+                    // one, each is rounded at the size of the running value: the error sums E driven by U were 3.4 times as far
+                    // from 64 bits, for 1 % (four row tiles, which then spill: 2 to 7 %) of the time.
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt) { acc[i - 1][rt][0] += acc[i][rt][0]; acc[i - 1][rt][1] += acc[i][rt][1]; }
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
