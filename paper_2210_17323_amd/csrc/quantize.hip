@@ -119,7 +119,7 @@ static bool group_supported(int64_t group) {
 // worth instantiating (32, 64, 128).
 static bool factor_form_group_supported(int64_t group) { return group == 0 || group == 32 || group == 64 || group == 128; }
 
-constexpr int QOB = 1024;   // outer block: trailing updates beyond it are deferred and applied as one rank-1024 GEMM
+// Trailing updates beyond an outer block are deferred and applied as one rank-1024 GEMM.
 static_assert(QOB == SPLIT_K, "the split products take exactly one outer block as K");
 
 // The deferred rank-1024 updates go through the split-operand kernel (bf16 matrix cores, 256 x 256 tiles, one per
@@ -264,9 +264,7 @@ static int alg1_run(bool rf, const void* W, int wdtype, int64_t ldw, int64_t r, 
     // Lazy batching at two levels (Section 3, Step 2 applied twice): inside an outer block of 1024 columns
     // each 128-column block updates only the rest of the outer block (rank 128, inside the strip kernel); the columns
     // beyond it get one rank-1024 update per outer block.  Same sums as Alg. 1, associated differently.
-    // A group grid must see fully updated weights at its first column, so an outer block may only end
-    // where a group ends: groups that neither divide 1024 nor are multiples of it fall back to one level.
-    const int64_t ob = (group >= QB && (QOB % group) && (group % QOB)) ? QB : QOB;
+    const int64_t ob = alg1_outer_block(group);
     // Look-ahead: after an outer block is quantized, the columns of the next outer block are updated first, on
     // the caller's stream, which goes straight on to quantize them (short, serial kernels); all columns
     // beyond are updated on the helper stream meanwhile.  The two updates and the next block's kernels touch

@@ -3,12 +3,11 @@
 // stream of a 128 x 128 triangular block through LDS and the DPP row broadcast, the rank-1 update of a column.
 #pragma once
 #include "common.h"
+#include "rules.h"
 
 #include <utility>
 
 namespace gptq {
-
-constexpr int QB = 128;
 
 // ---- W (f16 / bf16 / f32) -> float32 working copy; optionally the per-row grid from the original row.
 template <typename T> __device__ __forceinline__ float to_f32(T v);

@@ -325,7 +325,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int nblocks = (int)((g.o1 - g.o0 + QB - 1) / QB);
 
     // ---- the strip's working values of all blocks: lane (l16, kq) of wavefront w holds columns 32 w + 2 l16 + {0, 1} of
-    //      rows 16 rt + 4 kq + e.  Rows past r repeat the last one and are never stored; columns past n are zero.
+    //      rows 16 rt + 4 kq + e.  Rows past r repeat the last one and are never stored; columns past the outer block are zero.
     floatx4 acc[STRIP_BLOCKS][RT][2];
     const int wcol = 32 * wave + 2 * l16;
     {
@@ -341,7 +341,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         const char* base = reinterpret_cast<const char*>(g.S + row0 * g.lds_ + g.o0);
 #pragma unroll
         for (int i = 0; i < STRIP_BLOCKS; ++i) {
-            const int64_t left = g.n - (g.o0 + i * QB);          // columns from this block's first on
+            const int64_t left = strip_block_columns(g.o0, g.o1, i);
             if (!g.S || left <= 0) {
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt) acc[i][rt][0] = acc[i][rt][1] = floatx4{0.f, 0.f, 0.f, 0.f};
