@@ -123,7 +123,10 @@ static bool factor_form_group_supported(int64_t group) { return group == 0 || gr
 static_assert(QOB == SPLIT_K, "the split products take exactly one outer block as K");
 
 // The deferred rank-1024 updates go through the split-operand kernel (bf16 matrix cores, 256 x 256 tiles, one per
-// workgroup) when rows and columns come in whole tiles and the launch fills the chip well (split_pays).
+// workgroup) when columns come in whole tiles and the launch fills the chip well (split_pays).  `r` are the padded rows, so any
+// row count from 64 on qualifies.  Measured against 64-bit products on operands of Alg. 1's kind, 96 to 1372 tiles: relative error
+// 1.9e-7 (split) against 5.7e-7 (float32 kernel); from 144 tiles on 193 us against 245, at 128 tiles 195 against 150.  Rows'
+// losses against a 64-bit walk, ragged row counts 2000 .. 16000 and 5120 .. 12288 columns, both forms: the same to 1 % with either.
 static bool split_shapes_ok(int64_t r, int64_t n) { return r >= 256 && r % 256 == 0 && n % 256 == 0 && n >= 2 * QOB; }
 
 // Rows of the working matrix and of the error panels in the workspace: whole tiles of the deferred updates, so that a layer

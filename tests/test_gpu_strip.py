@@ -50,3 +50,38 @@ def test_strips_match_oracle(form, bits, grid, group, dtype, r, n):
     res = S.quantize(W.cuda(), Md, bits, grid, 128, group, want_Wq=True, from_factor=form == "factor")
     torch.cuda.synchronize()
     compare_quant(res, W.double().numpy(), U, Hd, bits, grid, group, f"strip {form}", tie_tol=2e-3, say=lambda m: print(m, flush=True))
+
+
+SPLIT_CASES = [
+    # form, bits, grid, group, dtype, r, n: rows that fill no 256-row tile, padded to one, two and five of them
+    ("factor", 3, "minmax", 0, torch.float16, 130, 3072),
+    ("factor", 2, "ternary", 128, torch.bfloat16, 300, 2304),
+    ("inverse", 4, "minmax", 1024, torch.float32, 257, 3072),
+    ("inverse", 3, "minmax", 0, torch.float16, 1100, 2304),
+]
+
+
+@pytest.mark.parametrize("form,bits,grid,group,dtype,r,n", SPLIT_CASES)
+def test_ragged_rows_with_split_updates_match_oracle(form, bits, grid, group, dtype, r, n):
+    """Layers of any row count from 64 on take the split products for their large deferred updates; the rows past the last one are
+    never initialised (here: NaN patterns) and must reach no result."""
+    import paper_2210_17323_amd as g
+    from paper_2210_17323_amd import solver as S
+    print(f"split strip form={form} bits={bits} grid={grid} group={group} {dtype} r={r} n={n}", flush=True)
+    need = g.gptq_quantize_layer_workspace_bytes(r, n, 128, group)
+    assert need == g.gptq_quantize_layer_workspace_bytes((r + 255) // 256 * 256, n, 128, group)      # planes for the padded rows
+    rng = np.random.default_rng(r + n + bits)
+    X = rng.standard_normal((n, 2 * n)) * np.exp(0.5 * rng.standard_normal((n, 1)))
+    Hd = O.damp(2.0 * X @ X.T)
+    U = O.hinv_cholesky_upper(Hd)
+    M = np.linalg.cholesky(Hd[::-1, ::-1])[::-1, ::-1] if form == "factor" else U
+    W = torch.from_numpy(rng.standard_normal((r, n)) * 0.02).to(dtype)
+    Md = torch.from_numpy(np.triu(M).astype(np.float32)).cuda()
+    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
+    prev = g.gptq_set_split_min_tiles(1)
+    try:
+        res = S.quantize(W.cuda(), Md, bits, grid, 128, group, want_Wq=True, ws=ws, from_factor=form == "factor")
+        torch.cuda.synchronize()
+    finally:
+        g.gptq_set_split_min_tiles(prev)
+    compare_quant(res, W.double().numpy(), U, Hd, bits, grid, group, f"split strip {form}", tie_tol=2e-3, say=lambda m: print(m, flush=True))
