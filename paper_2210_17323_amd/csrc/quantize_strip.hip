@@ -53,31 +53,39 @@ enum { FORM_U = 0, FORM_R = 1, FORM_HYBRID = 2 };
 
 // A row's grid, ready for the decision  code = clamp(rint(x / scale) + zero, 0, maxq).
 //   x / scale is the rounded quotient: scale = sn * 2^-es with sn in [0.5, 1), rs = 1 / sn, one correction step with the exact
-//   remainder.  (From |x / scale| = 2^126 on this is not finite where the division would be; such a row is lost anyway.)
+//   remainder.  The estimate is held within FAR, far outside every code, so that an infinite quotient meets a finite product in the
+//   remainder and keeps its sign; what is NaN takes code 0 (a median with NaN is the smallest of the others).
 //   rint is the rounding of an addition: a float in [2^23, 2^24) has no fraction bits, and MAGIC is even, so ties go to
 //   the even quotient.  Clamped there, between MAGIC - zero and MAGIC - zero + maxq (what lies outside the binade is
-//   outside these bounds on the same side), the sum's low byte is 16 + code - zero: MAGIC is 16 past a multiple of 256.
-constexpr float MAGIC = 12582912.f + 16.f;
+//   outside these bounds on the same side), the sum's low byte is OFF + code - zero: MAGIC is OFF past a multiple of 256.
+//   zero is at most 22: -lo / scale exceeds maxq only where the scale is a denormal of few bits, 1.5 times at most.  Where the
+//   range is so small that the scale itself is 0, every quotient is infinite, or NaN for a weight of 0: the zero point
+//   (2^31 - 1) is stored but shifts nothing.
+constexpr int OFF = 64;
+constexpr float MAGIC = 12582912.f + (float)OFF;
+constexpr float FAR = 1073741824.f;
 struct RowGrid {
     float scale, sn, rs, lo, hi;
-    int es;
+    int es, zero;
     uint32_t bias;                      // what four packed low bytes exceed the four codes by
-    __device__ __forceinline__ void set(float s, int zero, float maxq) {
+    __device__ __forceinline__ void set(float s, int z, float maxq) {
         scale = s;
-        const bool finite = s < INFINITY;                    // an infinite scale (infinite weights): every quotient is 0 or NaN
-        es = finite ? -__builtin_amdgcn_frexp_expf(s) : 0;
-        sn = finite ? __builtin_amdgcn_frexp_mantf(s) : 1.f;
+        zero = z;
+        const bool finite = s < INFINITY, none = s == 0.f;   // an infinite scale (infinite weights): every quotient is 0 or NaN
+        es = none ? 300 : (finite ? -__builtin_amdgcn_frexp_expf(s) : 0);
+        sn = none || !finite ? 1.f : __builtin_amdgcn_frexp_mantf(s);
         float r = __builtin_amdgcn_rcpf(sn);
         r = fmaf(fmaf(-sn, r, 1.f), r, r);
-        rs = finite ? r : 0.f;
-        lo = MAGIC - (float)zero;
+        rs = finite ? r : (s == INFINITY ? 0.f : s);          // NaN stays NaN
+        const int shift = none ? 0 : z;
+        lo = MAGIC - (float)shift;
         hi = lo + maxq;
-        bias = (uint32_t)(16 - zero) * 0x01010101u;
+        bias = (uint32_t)(OFF - shift) * 0x01010101u;
     }
     // the clamped, rounded quotient of x, as MAGIC + (code - zero)
     __device__ __forceinline__ float decide(float x) const {
         const float xs = ldexpf(x, es);
-        const float x0 = xs * rs;
+        const float x0 = __builtin_amdgcn_fmed3f(xs * rs, -FAR, FAR);
         return __builtin_amdgcn_fmed3f(fmaf(fmaf(-x0, sn, xs), rs, x0) + MAGIC, lo, hi);
     }
 };
@@ -176,7 +184,7 @@ __device__ __forceinline__ void walk_quad(Walk<FORM>& s, int in_group, int kind,
             if (start && 4 * I < nbk && s.writer && go.scales) {
                 const int gi = (4 * I) / in_group;
                 go.scales[gi] = s.grid.scale;
-                go.zeros[gi] = (int32_t)(MAGIC - s.grid.lo);
+                go.zeros[gi] = s.grid.zero;
             }
         }
     }

@@ -85,3 +85,72 @@ def test_ragged_rows_with_split_updates_match_oracle(form, bits, grid, group, dt
     finally:
         g.gptq_set_split_min_tiles(prev)
     compare_quant(res, W.double().numpy(), U, Hd, bits, grid, group, f"split strip {form}", tie_tol=2e-3, say=lambda m: print(m, flush=True))
+
+
+def _rtn32(w, maxq, ternary, group):
+    """Alg. 1 in float32 with a diagonal factor of ones: round to nearest, except that an error that is not finite makes every
+    later weight of its row NaN (0 times it is added to them).  code = clamp(rint(w / scale) + zero, 0, maxq), NaN to code 0."""
+    f = np.float32
+    r, n = w.shape
+    gsz = group or n
+    codes, scales, zeros = np.zeros((r, n), np.int64), np.zeros((r, n // gsz), f), np.zeros((r, n // gsz), np.int64)
+    for i in range(r):
+        poisoned = False
+        for j in range(n):
+            if j % gsz == 0:
+                cur = np.full(gsz, np.nan, f) if poisoned else w[i, j:j + gsz]
+                cur = cur[~np.isnan(cur)]
+                if ternary:
+                    s, z = (np.abs(cur).max() if cur.size else f(np.nan)), 1
+                    s = f(1) if s == 0 else s
+                else:
+                    lo, hi = (min(cur.min(), f(0)), max(cur.max(), f(0))) if cur.size else (f(0), f(0))
+                    s = f(1) if hi == lo else f(hi - lo) / f(maxq)
+                    z = f(0) if hi == lo else np.rint(-lo / s)
+                    z = 0 if np.isnan(z) else int(min(float(z), 2.0 ** 31 - 1))
+                scales[i, j // gsz], zeros[i, j // gsz] = s, z
+            x = f(np.nan) if poisoned else w[i, j]
+            c = np.rint(x / s) + f(z)
+            c = f(0) if np.isnan(c) else min(max(c, f(0)), f(maxq))
+            codes[i, j] = int(c)
+            poisoned = poisoned or not np.isfinite(x - s * (c - f(z)))
+    return codes, scales, zeros
+
+
+@pytest.mark.parametrize("form,group", [("inverse", 0), ("factor", 0), ("inverse", 32), ("factor", 32), ("inverse", 256)])
+@pytest.mark.parametrize("bits,grid", [(4, "minmax"), (3, "minmax"), (2, "minmax"), (2, "ternary")])
+def test_rows_at_the_ends_of_the_float_range(form, group, bits, grid):
+    """Codes stay within 0 .. maxq where a range is so small that -lo / scale exceeds maxq or the scale rounds to 0, where it
+    overflows, and where weights are infinite or NaN."""
+    from paper_2210_17323_amd import solver as S
+    n, unit = 256, np.float32(2.0 ** -149)
+    rng = np.random.default_rng(bits)
+    rows = [unit * rng.integers(a, b + 1, n).astype(np.float32) for a, b in
+            ((-22, 0), (-21, 0), (-10, 0), (-4, 0), (-7, 0), (0, 7), (-3, 4), (-1, 0), (0, 1), (-30, 25), (-300, 10))]
+    rows += [np.float32(10.0 ** e) * rng.standard_normal(n).astype(np.float32) for e in (-44, -40, -37, 0, 30)]
+    rows.append(np.float32(3e38) * np.sign(rng.standard_normal(n)).astype(np.float32))      # hi - lo overflows
+    for bad in (np.inf, -np.inf, np.nan):
+        row = rng.standard_normal(n).astype(np.float32)
+        row[40] = bad
+        rows.append(row)
+    W = np.stack(rows).astype(np.float32)
+    with np.errstate(all="ignore"):
+        codes, scales, zeros = _rtn32(W, O.grid_maxq(bits, grid), grid == "ternary", group)
+    res = S.quantize(torch.from_numpy(W).cuda(), torch.eye(n, device="cuda"), bits, grid, 128, group, from_factor=form == "factor")
+    assert np.array_equal(res.scales.cpu().numpy(), scales, equal_nan=True)
+    assert np.array_equal(res.zeros.cpu().numpy(), zeros)
+    got = res.codes.cpu().numpy()
+    assert np.array_equal(got, codes), [(i, int((got[i] != codes[i]).sum())) for i in range(len(rows)) if (got[i] != codes[i]).any()]
+
+
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_a_quotient_beyond_the_float_range_takes_the_outermost_code(sign):
+    """The error of column 0 pushes column 1 out of the float range: code 0 or maxq by its sign."""
+    from paper_2210_17323_amd import solver as S
+    W = np.tile(np.linspace(-1.0, 0.5, 128, dtype=np.float32), (16, 1))
+    W[:, 0], W[:, 1] = 0.04, 0.1                    # e_0 = 0.04 / 2^-10
+    W[8:] *= np.float32(1e-20)                      # finite there, the quotient is not
+    U = np.eye(128, dtype=np.float32)
+    U[0, 0], U[0, 1] = 2.0 ** -10, -sign * 3e38
+    res = S.quantize(torch.from_numpy(W).cuda(), torch.from_numpy(U).cuda(), 4)
+    assert res.codes[:, 1].tolist() == [15 if sign > 0 else 0] * 16
