@@ -14,6 +14,7 @@
 // resident on one XCD form a ~4 x 8 patch of tiles that shares its row and column panels in L2.
 #include "common.h"
 #include "hessian_small.h"
+#include "rules.h"
 #include "syrk_tiles.h"
 
 namespace gptq {
@@ -779,7 +780,7 @@ extern "C" int gptq_hessian_accumulate(float* H, int64_t ldh, const void* X, int
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (xdtype == GPTQ_F32) {
         if (!aligned(X, 16) || ldx % 4) return fail(GPTQ_ERR_INVALID_ARG, "hessian_accumulate: float32 X must be 16-byte aligned with ldx %% 4 == 0");
-        if (n <= SYRK_SMALL_MAX_F32) return launch_syrk_small(H, ldh, X, xdtype, n, t, ldx, s);
+        if (hessian_f32_small_tiles(n, t)) return launch_syrk_small(H, ldh, X, xdtype, n, t, ldx, s);
         GemmF32 g{};
         g.A = static_cast<const float*>(X); g.lda = ldx;
         g.B = g.A; g.ldb = ldx;

@@ -13,6 +13,7 @@ using namespace gptq;
 extern "C" {
 int64_t outer_block(int64_t group) { return alg1_outer_block(group); }
 int64_t block_columns(int64_t o0, int64_t o1, int i) { return strip_block_columns(o0, o1, i); }
+int f32_small_tiles(int64_t n, int64_t t) { return hessian_f32_small_tiles(n, t); }
 }
 """
 
@@ -27,6 +28,7 @@ def rules(tmp_path_factory):
     i64 = ctypes.c_int64
     L.outer_block.restype, L.outer_block.argtypes = i64, [i64]
     L.block_columns.restype, L.block_columns.argtypes = i64, [i64, i64, ctypes.c_int]
+    L.f32_small_tiles.argtypes = [i64, i64]
     return L
 
 
@@ -42,3 +44,21 @@ def test_a_strip_launch_reads_the_columns_it_walks_and_no_others(rules, n, group
             first = o0 + 128 * i
             read |= set(range(first, first + min(128, rules.block_columns(o0, o1, i))))
         assert read == set(range(o0, o1)), (o0, o1)
+
+
+# float32 Hessians: (channels, tokens, microseconds with the small tiles, with the float32 product), measured on one card
+F32_TIMES = [
+    (256, 4096, 41, 245), (1000, 16, 12, 23), (1024, 64, 12, 12), (1408, 4096, 135, 250), (1500, 512, 42, 67), (1544, 64, 15, 20),
+    (1664, 64, 14, 12), (1664, 512, 42, 38), (1664, 4096, 247, 251), (1920, 4096, 248, 252), (2040, 4096, 338, 393), (2048, 64, 20, 13), (2048, 512, 59, 41), (2048, 4096, 338, 253),
+    (2056, 64, 22, 16), (2056, 512, 59, 56), (2056, 4096, 349, 367), (2144, 8, 22, 17), (2200, 64, 22, 19), (2300, 4096, 357, 395), (2500, 64, 28, 26),
+    (2500, 512, 78, 70), (2500, 8192, 907, 753), (2560, 4096, 456, 255), (2700, 4096, 476, 372), (2816, 8192, 933, 499), (2824, 512, 96, 90),
+    (2950, 4096, 573, 614), (2950, 512, 100, 90), (3000, 64, 34, 32), (3000, 8192, 1152, 1244), (3072, 64, 33, 20), (3072, 8192, 1159, 957),
+]
+
+
+@pytest.mark.parametrize("n,t,small,product", F32_TIMES)
+def test_float32_hessians_take_the_faster_kernel(rules, n, t, small, product):
+    """No call goes to the slower of the two by more than the runs differ; beyond 3072 channels it is always the product."""
+    chosen = small if rules.f32_small_tiles(n, t) else product
+    assert chosen <= 1.05 * min(small, product) + 1
+    assert not rules.f32_small_tiles(3073, t)
