@@ -12,6 +12,7 @@ CASES = [
     (torch.float32, 1013, 517, "none"), (torch.float32, 3072, 96, "none"),
     (torch.float16, 1, 5, "none"), (torch.float16, 32, 64, "none"), (torch.float16, 65, 1025, "none"), (torch.float16, 1536, 130, "none"),
     (torch.bfloat16, 999, 513, "none"), (torch.bfloat16, 1025, 8 * 64 + 1, "none"),
+    (torch.float16, 1480, 20, "none"), (torch.float32, 70, 39, "none"), (torch.bfloat16, 40, 64 + 31, "none"),      # whole and broken 16 bytes past the last chunk
     (torch.float16, 256, 32769, "asked"), (torch.bfloat16, 513, 40000, "asked"), (torch.float16, 2040, 33000, "asked"),
     (torch.float16, 300, 33000, "short"), (torch.float16, 300, 33000, "none"),
 ]
