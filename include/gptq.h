@@ -191,7 +191,7 @@ GPTQ_API int gptq_check_info(const int* info_dev, int* host_info, void* stream);
  *   ws       at least gptq_quantize_layer_workspace_bytes(r, n, block, group) bytes, 256-byte aligned.
  *   The update of column j's block and the rank-128 updates inside an outer block of 1024 columns are float32; the
  *   deferred rank-1024 updates beyond it are float32 matrix-core products or, when large, the split products of
- *   gptq_trailing_update_split below (n % 256 == 0 and n >= 2048, any r >= 64: rows are padded to whole tiles in the workspace).
+ *   gptq_trailing_update_split below (n % 256 == 0 and n >= 2048, any r > 128: rows are padded to whole tiles in the workspace).
  *   r == 0 or n == 0 is a valid no-op.  Like step 2, the call puts part of its work on the library's helper
  *   stream and joins it back before returning.
  */

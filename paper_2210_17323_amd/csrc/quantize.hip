@@ -124,15 +124,16 @@ static_assert(QOB == SPLIT_K, "the split products take exactly one outer block a
 
 // The deferred rank-1024 updates go through the split-operand kernel (bf16 matrix cores, 256 x 256 tiles, one per
 // workgroup) when columns come in whole tiles and the launch fills the chip well (split_pays).  `r` are the padded rows, so any
-// row count from 64 on qualifies.  Measured against 64-bit products on operands of Alg. 1's kind, 96 to 1372 tiles: relative error
+// row count above 128 qualifies.  Measured against 64-bit products on operands of Alg. 1's kind, 96 to 1372 tiles: relative error
 // 1.9e-7 (split) against 5.7e-7 (float32 kernel); from 144 tiles on 193 us against 245, at 128 tiles 195 against 150.  Rows'
 // losses against a 64-bit walk, ragged row counts 2000 .. 16000 and 5120 .. 12288 columns, both forms: the same to 1 % with either.
 static bool split_shapes_ok(int64_t r, int64_t n) { return r >= 256 && r % 256 == 0 && n % 256 == 0 && n >= 2 * QOB; }
 
 // Rows of the working matrix and of the error panels in the workspace: whole tiles of the deferred updates, so that a layer
 // of any row count takes the large-tile kernels (3000 rows x 5120 columns: 190-250 us an update through the guarded
-// kernel, 60-110 so).  The rows past r are never written by anything but these updates and never read by anything else.
-static int64_t padded_rows(int64_t r) { return r >= 64 ? (int64_t)round_up((size_t)r, 256) : std::max<int64_t>(r, 1); }
+// kernel, 75-210 so).  Up to 128 rows one row of 128 x 128 tiles is enough, and half the memory.  The rows past r are never
+// written by anything but these updates and never read by anything else.
+static int64_t padded_rows(int64_t r) { return r >= 64 ? (int64_t)round_up((size_t)r, r <= 128 ? 128 : 256) : std::max<int64_t>(r, 1); }
 
 struct QuantWs { size_t wk, e, pk, ub, rt, pa, pb, pr, total; int64_t ldk, rows; bool split; };
 static QuantWs quant_ws_layout(int64_t r, int64_t n, int64_t group) {

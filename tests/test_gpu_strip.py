@@ -63,7 +63,7 @@ SPLIT_CASES = [
 
 @pytest.mark.parametrize("form,bits,grid,group,dtype,r,n", SPLIT_CASES)
 def test_ragged_rows_with_split_updates_match_oracle(form, bits, grid, group, dtype, r, n):
-    """Layers of any row count from 64 on take the split products for their large deferred updates; the rows past the last one are
+    """Layers of any row count above 128 take the split products for their large deferred updates; the rows past the last one are
     never initialised (here: NaN patterns) and must reach no result."""
     import paper_2210_17323_amd as g
     from paper_2210_17323_amd import solver as S

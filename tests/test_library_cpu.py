@@ -134,3 +134,13 @@ def test_argument_validation_happens_on_the_host():
 def test_missing_library_fails_loudly(tmp_path):
     with pytest.raises(FileNotFoundError):
         g.load_library(str(tmp_path / "nope.so"))
+
+
+def test_quantize_workspace_of_few_rows():
+    """Working matrix and error panels are padded to whole tiles: one row of 128 x 128 tiles up to 128 rows, none below 64."""
+    n, panels = 8192, 2 * 1024
+    base = g.gptq_quantize_layer_workspace_bytes(1, n) - (n + panels) * 4
+    for r, rows in ((3, 3), (63, 63), (64, 128), (128, 128), (129, 256)):
+        need = g.gptq_quantize_layer_workspace_bytes(r, n) - base - (n + panels) * 4 * rows
+        planes = (rows + 1024 + n) * 6144 + 3 * 16384 if rows % 256 == 0 else 0
+        assert need == planes, (r, need, planes)
