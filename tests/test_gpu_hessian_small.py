@@ -1,6 +1,7 @@
-"""GPU parity of the Hessian of layers of few channels: the small-tile kernel (tiles of 32 and 64 channels, chunks of 64
+"""GPU parity of the Hessian of layers of few channels, and of float32 activations of any number: the small-tile kernel (tiles of 32 and 64 channels, chunks of 64
 16-bit or 32 float32 tokens dealt to 8 or 16 wavefronts) at the edges of its tiles and chunks, and the workspace path such
-layers take in long calls.  Bar: relative Frobenius error 1e-5 as everywhere, and the same bits from the same call."""
+layers take in long calls, the float32 product behind the small tiles (triangular launches of its three tile sizes, and the guarded
+kernel).  Bar: relative Frobenius error 1e-5 as everywhere, and the same bits from the same call."""
 import pytest
 import torch
 
@@ -10,6 +11,9 @@ CASES = [
     # dtype, n, t, workspace ("none", "asked", "short": one that is too small and therefore ignored)
     (torch.float32, 1, 1, "none"), (torch.float32, 31, 33, "none"), (torch.float32, 33, 31, "none"), (torch.float32, 256, 4100, "none"),
     (torch.float32, 1013, 517, "none"), (torch.float32, 3072, 96, "none"),
+    (torch.float32, 2048, 128, "none"), (torch.float32, 2300, 1100, "none"), (torch.float32, 2500, 96, "none"),      # 128 x 128 tiles, small, guarded
+    (torch.float32, 3080, 128, "none"), (torch.float32, 3200, 128, "none"), (torch.float32, 3200, 100, "none"),      # ragged rows, 128 x 128, ragged tokens
+    (torch.float32, 5888, 64, "none"), (torch.float32, 6144, 64, "none"),                                             # 256 x 128 and 256 x 256 tiles
     (torch.float16, 1, 5, "none"), (torch.float16, 32, 64, "none"), (torch.float16, 65, 1025, "none"), (torch.float16, 1536, 130, "none"),
     (torch.bfloat16, 999, 513, "none"), (torch.bfloat16, 1025, 8 * 64 + 1, "none"),
     (torch.float16, 1480, 20, "none"), (torch.float32, 70, 39, "none"), (torch.bfloat16, 40, 64 + 31, "none"),      # whole and broken 16 bytes past the last chunk

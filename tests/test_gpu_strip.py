@@ -52,6 +52,59 @@ def test_strips_match_oracle(form, bits, grid, group, dtype, r, n):
     compare_quant(res, W.double().numpy(), U, Hd, bits, grid, group, f"strip {form}", tie_tol=2e-3, say=lambda m: print(m, flush=True))
 
 
+TALL_CASES = [
+    # form, bits, grid, group, dtype, r, n: two and three outer blocks at 32, 48 and 64 rows per workgroup
+    ("factor", 3, "minmax", 0, torch.float16, 4100, 2184),
+    ("factor", 4, "minmax", 64, torch.bfloat16, 4100, 2176),
+    ("inverse", 4, "minmax", 256, torch.float16, 4100, 2304),
+    ("factor", 4, "minmax", 128, torch.float32, 8193, 1152),
+    ("inverse", 3, "minmax", 32, torch.float16, 8193, 1280),
+    ("factor", 4, "minmax", 32, torch.bfloat16, 12289, 1088),
+    ("inverse", 3, "minmax", 0, torch.float32, 12289, 1160),
+]
+
+
+@pytest.mark.parametrize("form,bits,grid,group,dtype,r,n", TALL_CASES)
+def test_tall_strips_match_oracle_on_sampled_rows(form, bits, grid, group, dtype, r, n):
+    from types import SimpleNamespace
+    from paper_2210_17323_amd import solver as S
+    print(f"tall strip form={form} bits={bits} grid={grid} group={group} {dtype} r={r} n={n}", flush=True)
+    rng = np.random.default_rng(r + n + bits)
+    X = rng.standard_normal((n, 2 * n)) * np.exp(0.5 * rng.standard_normal((n, 1)))
+    Hd = O.damp(2.0 * X @ X.T)
+    U = O.hinv_cholesky_upper(Hd)
+    M = np.linalg.cholesky(Hd[::-1, ::-1])[::-1, ::-1] if form == "factor" else U
+    W = torch.from_numpy(rng.standard_normal((r, n)) * 0.02).to(dtype)
+    Md = torch.from_numpy(np.triu(M).astype(np.float32)).cuda()
+    res = S.quantize(W.cuda(), Md, bits, grid, 128, group, want_Wq=True, from_factor=form == "factor")
+    torch.cuda.synchronize()
+    # the first workgroup whole, the last rows (their workgroup is short), and some in between
+    rows = np.unique(np.concatenate([np.arange(64), np.arange(r - 20, r), rng.integers(0, r, 24)]))
+    idx = torch.from_numpy(rows)
+    part = SimpleNamespace(**{k: getattr(res, k).cpu()[idx] for k in ("codes", "zeros", "scales", "half_E2_rows", "Wq")})
+    compare_quant(part, W.double().numpy()[rows], U, Hd, bits, grid, group, f"tall strip {form}", tie_tol=2e-3, say=lambda m: print(m, flush=True))
+
+
+@pytest.mark.parametrize("form,group", [("factor", 0), ("factor", 64), ("inverse", 0), ("inverse", 8), ("inverse", 256)])
+@pytest.mark.parametrize("r", [4100, 8193, 12289])
+def test_a_row_does_not_depend_on_the_height_of_its_strip(r, form, group):
+    """32, 48 and 64 rows per workgroup add up in the order in which 16 do: the same bits, row by row, within one outer block."""
+    from paper_2210_17323_amd import solver as S
+    n = 1024 if group else 1000
+    gen = torch.Generator(device="cuda").manual_seed(r + group)
+    X = torch.randn((n, 2 * n), generator=gen, device="cuda", dtype=torch.float64)
+    H = X @ X.T / n
+    H.diagonal().add_(0.01)
+    R = torch.linalg.cholesky(H.flip(0, 1)).flip(0, 1)
+    M = (R if form == "factor" else torch.linalg.inv(R.contiguous()).triu()).float().contiguous()
+    W = (0.02 * torch.randn((r, n), generator=gen, device="cuda")).half()
+    tall = S.quantize(W, M, 4, "minmax", 128, group, from_factor=form == "factor")
+    for r0 in (0, r // 2, r - 1000):
+        part = S.quantize(W[r0:r0 + 1000].contiguous(), M, 4, "minmax", 128, group, from_factor=form == "factor")
+        for k in ("codes", "scales", "zeros", "half_E2_rows"):
+            assert torch.equal(getattr(part, k), getattr(tall, k)[r0:r0 + 1000]), (k, r0)
+
+
 SPLIT_CASES = [
     # form, bits, grid, group, dtype, r, n: rows that fill no 256-row tile, padded to one, two and five of them
     ("factor", 3, "minmax", 0, torch.float16, 130, 3072),
