@@ -647,24 +647,8 @@ int launch_pack_factor(const float* M, int64_t ldm, const float* D, int64_t ldd,
     return GPTQ_OK;
 }
 
-// Rows per workgroup, 16 RT: a launch takes ceil(workgroups / CUs) rounds, and a strip through a whole outer block takes
-// 313, 395, 489 or 584 thousand cycles at RT = 1 .. 4 (measured on 1024 columns; the walk alone is 210 of them).  The walk is
-// as long for 16 rows as for 64 -- one wavefront per 16 rows --, so few rows are spread thin over all CUs and many are
-// taken 64 at a time: r = 4096: RT 1 (1.22 ms against 1.27, 1.44, 1.60 for a 4096-column layer), 8192: RT 2 (1.68 against
-// 1.76, 1.84, 1.99), 12288: RT 3, 49152: RT 4 (7.6 ms against 8.8, 8.5, 7.9).
-static int strip_row_tiles(int64_t r) {
-    static const int64_t cost[4] = {313, 395, 489, 584};
-    int best = 1;
-    int64_t best_cost = 0;
-    for (int rt = 1; rt <= 4; ++rt) {
-        const int64_t c = ceil_div(ceil_div(r, 16 * rt), 256) * cost[rt - 1];
-        if (rt == 1 || c < best_cost) { best = rt; best_cost = c; }
-    }
-    return best;
-}
-
 int launch_alg1_strip(bool rf, bool hybrid, const StripArgs& g, hipStream_t s) {
-    const int rt = strip_row_tiles(g.r);
+    const int rt = strip_row_tiles(hybrid ? FORM_HYBRID : (rf ? FORM_R : FORM_U), g.r);
     if (hybrid) launch_form<FORM_HYBRID>(rt, g, s);
     else if (rf) launch_form<FORM_R>(rt, g, s);
     else launch_form<FORM_U>(rt, g, s);

@@ -13,6 +13,7 @@ using namespace gptq;
 extern "C" {
 int64_t outer_block(int64_t group) { return alg1_outer_block(group); }
 int64_t block_columns(int64_t o0, int64_t o1, int i) { return strip_block_columns(o0, o1, i); }
+int row_tiles(int form, int64_t r) { return strip_row_tiles(form, r); }
 int f32_small_tiles(int64_t n, int64_t t) { return hessian_f32_small_tiles(n, t); }
 }
 """
@@ -28,6 +29,7 @@ def rules(tmp_path_factory):
     i64 = ctypes.c_int64
     L.outer_block.restype, L.outer_block.argtypes = i64, [i64]
     L.block_columns.restype, L.block_columns.argtypes = i64, [i64, i64, ctypes.c_int]
+    L.row_tiles.argtypes = [ctypes.c_int, i64]
     L.f32_small_tiles.argtypes = [i64, i64]
     return L
 
@@ -62,3 +64,14 @@ def test_float32_hessians_take_the_faster_kernel(rules, n, t, small, product):
     chosen = small if rules.f32_small_tiles(n, t) else product
     assert chosen <= 1.05 * min(small, product) + 1
     assert not rules.f32_small_tiles(3073, t)
+
+
+@pytest.mark.parametrize("form", [0, 1, 2])
+def test_strip_height_covers_the_rows_in_the_fewest_rounds_that_pay(rules, form):
+    """One strip per CU as long as that lasts; a taller strip only where the lower one would need another round."""
+    for rt in (1, 2, 3, 4):
+        assert rules.row_tiles(form, 16 * rt * 256) == rt
+    assert rules.row_tiles(form, 1) == 1 and rules.row_tiles(form, 4097) == 2 and rules.row_tiles(form, 8193) == 3
+    assert rules.row_tiles(form, 12289) == 4
+    # many rounds: four rounds of 48 rows beat three of 64 where 64 cost more than in proportion
+    assert rules.row_tiles(form, 49152) == (3 if form == 2 else 4)
