@@ -246,7 +246,7 @@ GPTQ_API int gptq_quantize_layer_from_factor(const void* W, int wdtype, int64_t 
  * block (k = 128, the rest of the current 1024-column outer block) and after every outer block (k = 1024, all
  * later columns).  float32 on the matrix cores, float32 accumulation.  All three matrices row-major, 16-byte
  * aligned, leading dimensions multiples of 4 elements (ldw >= ncols, lde >= k, ldu >= ncols).  Any size is taken;
- * r % 256 == 0, ncols % 128 == 0 and k % 64 == 0 run on the large-tile kernel.  A zero size is a no-op.
+ * r % 128 == 0, k % 64 == 0 and ncols of at least 128 run on the direct-to-LDS kernels.  A zero size is a no-op.
  */
 GPTQ_API int gptq_trailing_update(float* W, int64_t ldw, const float* E, int64_t lde, const float* U, int64_t ldu,
                          int64_t r, int64_t ncols, int64_t k, void* stream);

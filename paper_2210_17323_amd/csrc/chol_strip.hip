@@ -1,7 +1,7 @@
 // Step 2, products with the triangular 1024 x 1024 diagonal block of one outer block (Section 3, Step 3), a strip of 16 RT
 // rows per workgroup and launch.  Rows are independent in both of them:
-//   STRIP_INVERSE  the rows of U_oo = R_oo^-1:           for b first .. last:  U_b = X_b R_bb^-1,    X_c -= U_b R[b, c]   (X = identity)
-//   STRIP_PANEL    the rows above the block:             for b last .. first:  P_b = X_b R_bb^-T,    X_c -= P_b R[c, b]^T (X = H[row, o])
+//   inverse  the rows of U_oo = R_oo^-1:           for b first .. last:  U_b = X_b R_bb^-1,    X_c -= U_b R[b, c]   (X = identity)
+//   panel    the rows above the block:             for b last .. first:  P_b = X_b R_bb^-T,    X_c -= P_b R[c, b]^T (X = H[row, o])
 // X lives in registers as accumulators of v_mfma_f32_16x16x4_f32, of every block of 128 columns wavefront w owns columns 32 w
 // .. 32 w + 31; the current block goes through LDS to become the A operand, first of the product with the inverse of the
 // diagonal block, then -- replaced by its result -- of the products into the blocks still to come, whose B operands come
@@ -25,15 +25,15 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 
 // B operand order of a 128 x 128 tile: [wavefront: 32 columns][16 k][even, odd columns][lane][4 k].
 // Tiles: SB inverses of diagonal blocks, then the pairs (s, s'), s < s', of positions in the order of the walk.
-// Workgroup: one half (64 k) of one tile of one outer block.
-__global__ __launch_bounds__(256) void pack_triangle_kernel(const float* R, int64_t ld, int64_t n, const float* dinv, int64_t o_first, int panel, float* out) {
+// Workgroup: one half (64 k) of one tile.
+__global__ __launch_bounds__(256) void pack_triangle_kernel(const float* R, int64_t ld, int64_t n, const float* dinv, int64_t o, int panel, float* out) {
     __shared__ float tile[CB][65];                       // [k or column][...]: see below
     const int tid = threadIdx.x;
-    const int64_t o0 = (o_first + blockIdx.y) * (int64_t)(SB * CB);
+    const int64_t o0 = o * (int64_t)(SB * CB);
     const int nb = (int)((min((int64_t)(SB * CB), n - o0) + CB - 1) / CB);
     int t = (int)blockIdx.x >> 1;
     const int h = (int)blockIdx.x & 1;
-    float* dst = out + blockIdx.y * (int64_t)TRIANGLE_WORDS + (int64_t)t * TILE_WORDS;
+    float* dst = out + (int64_t)t * TILE_WORDS;
     const float* src;
     int64_t lds_;
     int64_t rows, cols;                                  // of the source tile that exist
@@ -67,9 +67,9 @@ __global__ __launch_bounds__(256) void pack_triangle_kernel(const float* R, int6
 
 struct StripTriArgs {
     float* X; int64_t ldx;              // panel: the rows above the outer block, in place (points at its first column)
-    float* U;                           // inverse: U_oo of the first outer block [1024 x 1024], one after the other
-    const float* packed;                // TRIANGLE_WORDS per outer block
-    int64_t n, o_first, rows;           // panel: o_first is the outer block, rows the rows of the strip range
+    float* U;                           // inverse: U_oo [1024 x 1024]
+    const float* packed;                // the outer block, TRIANGLE_WORDS
+    int64_t n, o, rows;                 // o: the outer block; panel: rows above it
 };
 
 template <bool PANEL, int RT>
@@ -79,13 +79,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, kq = lane >> 4;
     const int wcol = 32 * wave + 2 * l16;
-    const int64_t o = g.o_first + blockIdx.y, o0 = o * (int64_t)(SB * CB);
+    const int64_t o0 = g.o * (int64_t)(SB * CB);
     const int ow = (int)min((int64_t)(SB * CB), g.n - o0);
     const int nb = (ow + CB - 1) / CB;
     const int64_t row0 = (int64_t)blockIdx.x * ROWS;     // panel: row of the matrix; inverse: row of the outer block
     if (!PANEL && row0 >= ow) return;
     const int s0 = PANEL ? 0 : (int)(row0 / CB);         // position of the first block that is not zero
-    const float* packed = g.packed + blockIdx.y * (int64_t)TRIANGLE_WORDS;
     auto block_of = [&](int s) { return PANEL ? nb - 1 - s : s; };
 
     floatx4 acc[SB][RT][2];
@@ -151,8 +150,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll 1
     for (int s = s0; s < nb; ++s) {
         const int b = block_of(s), later = nb - 1 - s;
-        const float* dtile = packed + (int64_t)s * TILE_WORDS;
-        const float* ptile = packed + (int64_t)(SB + s * (2 * SB - 1 - s) / 2) * TILE_WORDS;         // pair (s, s + 1)
+        const float* dtile = g.packed + (int64_t)s * TILE_WORDS;
+        const float* ptile = g.packed + (int64_t)(SB + s * (2 * SB - 1 - s) / 2) * TILE_WORDS;         // pair (s, s + 1)
         request(dtile, 0, bf[0]);
         to_lds(acc[0], 1.f);
         lds_barrier();
@@ -173,7 +172,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             for (int e = 0; e < 4; ++e) {
                 const int64_t row = row0 + 16 * rt + 4 * kq + e;
                 if (PANEL ? row >= g.rows : row >= ow) continue;
-                float* p = PANEL ? g.X + row * g.ldx + b * CB + wcol : g.U + (o * (int64_t)(SB * CB) + row) * (SB * CB) + b * CB + wcol;
+                float* p = PANEL ? g.X + row * g.ldx + b * CB + wcol : g.U + row * (SB * CB) + b * CB + wcol;
                 const int left = ow - b * CB - wcol;
                 if (left >= 2) *reinterpret_cast<floatx2*>(p) = floatx2{out[rt][0][e], out[rt][1][e]};
                 else if (left == 1) p[0] = out[rt][0][e];
@@ -205,7 +204,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 // inverse, instead of waiting for another launch to have made them.  That is two more products of 64 x 128 x 64 per tile
 // (6 us of matrix-core time in all), where the launch between two dependent kernels costs 10 to 15.  P goes to a buffer of
 // its own because other workgroups still read H[o0:j0, b]; copy_panel_kernel puts it in its place at the end of the chain.
-struct StepArgs { float* H; int64_t ld; const float* dinv; float* panel; int64_t o0, j0; int m, nbk; };     // panel: [1024 x 1024], column j0 - o0
+struct StepArgs { float* H; int64_t ld; const float* dinv; float* panel; int64_t o0, j0; int nbk; };     // panel: [1024 x 1024], column j0 - o0
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 2))) void chol_step_kernel(StepArgs g) {
     __shared__ __attribute__((aligned(16))) float pi[64 * PW];
@@ -310,15 +309,15 @@ __global__ __launch_bounds__(256) void copy_panel_kernel(float* H, int64_t ld, i
 
 }  // namespace
 
-int launch_pack_triangle(const float* R, int64_t ld, int64_t n, const float* dinv, int64_t o_first, int64_t count, bool panel, float* packed, hipStream_t s) {
-    hipLaunchKernelGGL(pack_triangle_kernel, dim3(2 * (SB + PAIRS), (unsigned)count), dim3(256), 0, s, R, ld, n, dinv, o_first, (int)panel, packed);
+int launch_pack_triangle(const float* R, int64_t ld, int64_t n, const float* dinv, int64_t o, bool panel, float* packed, hipStream_t s) {
+    hipLaunchKernelGGL(pack_triangle_kernel, dim3(2 * (SB + PAIRS)), dim3(256), 0, s, R, ld, n, dinv, o, (int)panel, packed);
     GPTQ_LAUNCH_CHECK();
     return GPTQ_OK;
 }
 
-int launch_triangle_inverse(const float* packed, int64_t n, int64_t o_first, int64_t count, float* Uoo, hipStream_t s) {
-    StripTriArgs g{nullptr, 0, Uoo, packed, n, o_first, 0};
-    hipLaunchKernelGGL((tri_strip_kernel<false, 1>), dim3(SB * CB / 16, (unsigned)count), dim3(256), 0, s, g);
+int launch_triangle_inverse(const float* packed, int64_t n, int64_t o, float* Uoo, hipStream_t s) {
+    StripTriArgs g{nullptr, 0, Uoo, packed, n, o, 0};
+    hipLaunchKernelGGL((tri_strip_kernel<false, 1>), dim3(SB * CB / 16), dim3(256), 0, s, g);
     GPTQ_LAUNCH_CHECK();
     return GPTQ_OK;
 }
@@ -334,9 +333,9 @@ int launch_triangle_panel(float* X, int64_t ldx, int64_t rows, const float* pack
 }
 
 int launch_chol_step(float* H, int64_t ld, int64_t o0, int64_t j0, int nbk, const float* dinv_b, float* panel, hipStream_t s) {
-    const int m = (int)(j0 - o0), t = m / 64;
+    const int t = (int)(j0 - o0) / 64;
     if (t == 0) return GPTQ_OK;
-    const StepArgs g{H, ld, dinv_b, panel, o0, j0, m, nbk};
+    const StepArgs g{H, ld, dinv_b, panel, o0, j0, nbk};
     hipLaunchKernelGGL(chol_step_kernel, dim3((unsigned)(t * (t + 1) / 2)), dim3(256), 0, s, g);
     GPTQ_LAUNCH_CHECK();
     return GPTQ_OK;

@@ -192,7 +192,7 @@ static int chol_run(float* H, int64_t ld, int64_t n, float percdamp, void* ws, i
         if (o0 > 0) {
             // The rows above the outer block: R[0:o0, o] = H[0:o0, o] R_oo^-T, a strip of rows per workgroup through all of its
             // blocks in one launch (chol_strip.hip).
-            if (int rc = launch_pack_triangle(H, ld, n, dinv, o, 1, true, w.tri2, s)) return rc;
+            if (int rc = launch_pack_triangle(H, ld, n, dinv, o, true, w.tri2, s)) return rc;
             if (int rc = launch_triangle_panel(H + o0, ld, o0, w.tri2, n, o, s)) return rc;
         }
         if (want_inverse) {
@@ -205,8 +205,8 @@ static int chol_run(float* H, int64_t ld, int64_t n, float percdamp, void* ws, i
             hipLaunchKernelGGL(fill_zero_kernel, dim3(256), dim3(256), 0, s3, reinterpret_cast<float4*>(Ublk), (int64_t)OB * OB / 4);
             GPTQ_LAUNCH_CHECK();
             if (int rc = ts.wait(s3, chain)) return rc;
-            if (int rc = launch_pack_triangle(H, ld, n, dinv, o, 1, false, w.tri, s3)) return rc;
-            if (int rc = launch_triangle_inverse(w.tri, n, o, 1, w.Uoo, s3)) return rc;
+            if (int rc = launch_pack_triangle(H, ld, n, dinv, o, false, w.tri, s3)) return rc;
+            if (int rc = launch_triangle_inverse(w.tri, n, o, Ublk, s3)) return rc;
             if (o1 < n) {
                 Opt a; a.overwrite = true; a.atri = true;
                 if (int rc = gemm_on(s3, Ublk, OB, H + o0 * ld + o1, ld, w.T2, w.ld2, ow, n - o1, ow, -1.f, a)) return rc;

@@ -28,7 +28,6 @@ struct GemmArgs {
     int b_upper_tri;
     int tiles_m, tiles_n;
     int64_t per_xcd, total;
-    int64_t slots;      // tile slots of the launch: per_xcd * 8
     int tri_ratio;      // > 0: exactly the upper tiles of a square C are enumerated; value = tile rows / tile columns
 };
 
@@ -262,8 +261,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 3))) voi
 }
 
 // ---- direct-to-LDS variants: 256 x 128, 256 x 256 or 128 x 128 tile, operands copied global -> LDS, 4 stages ----
-// Used when M is a multiple of the tile height and K of 64; N may end inside a tile (B's last columns, or rows, are read again
-// in the place of those past the end, and what comes of them is not stored).  8 wavefronts, each 64 x 64 = 2 x 2 MFMA tiles
+// Used when M is a multiple of the tile height and K of 64; for B given as [K x N] N may end inside a tile (B's last columns are
+// read again in the place of those past the end, and what comes of them is not stored).  8 wavefronts, each 64 x 64 = 2 x 2 MFMA tiles
 // (128 x 64 of the wide tile); 4 wavefronts and half the LDS for the small tile, so that two workgroups share a CU.
 // A stage holds 16 values of K: the A panel as [256 rows][16 floats] and, for B given as [N x K], the B
 // panel as [128 rows][16 floats]; rows are 64 bytes = 4 chunks of 16 bytes, and global_load_lds_dwordx4
@@ -310,14 +309,14 @@ __global__ __launch_bounds__(TILE == TILE_SMALL ? 256 : 512) __attribute__((amdg
 
     // copies: A panel = one instruction per 16 rows (2 per wavefront); B panel = 8 or 16 instructions (NB per wavefront): for B
     // given as [N x K] 16 rows each, for [K x N] 1 KB of consecutive n (two k rows of 128, or one of 256).  Past the last
-    // column the last row of B, or the 16 bytes that hold its last column, are read again (rows are a multiple of 16 bytes apart).
+    // column the 16 bytes that hold it are read again (rows are a multiple of 16 bytes apart).
     const int crow = lane >> 2, cchunk = (lane & 3) ^ ((lane >> 4) & 3);
     const float* srcA = g.A + (m0 + wave * 32 + crow) * g.lda + cchunk * 4;              // + i*16 rows, + k0
     constexpr int NSRC = TILE == TILE_SMALL ? 2 : 1;         // the wide tile's second copy is one row on (its columns are whole)
     const float* srcB[NSRC];
 #pragma unroll
     for (int i = 0; i < NSRC; ++i) {
-        if (B_IS_NK) srcB[i] = g.B + min(n0 + (wave * NB + i) * 16 + crow, g.N - 1) * g.ldb + cchunk * 4;                              // + k0
+        if (B_IS_NK) srcB[i] = g.B + (n0 + (wave * NB + i) * 16 + crow) * g.ldb + cchunk * 4;                              // + k0
         else {
             const int64_t col = min(n0 + (WIDE ? lane : l32) * 4, (g.N - 1) & ~(int64_t)3);
             srcB[i] = g.B + (int64_t)(WIDE ? wave * 2 + i : (wave * NB + i) * 2 + lhi) * g.ldb + col;                                   // + k0*ldb
@@ -459,10 +458,10 @@ int launch_gemm_f32(const GemmF32& p, hipStream_t s) {
     g.overwrite = p.overwrite; g.upper_only = p.upper_only; g.crow0 = p.crow0; g.ccol0 = p.ccol0;
     g.a_upper_tri = p.a_upper_tri;
     g.b_upper_tri = p.b_upper_tri && !p.b_is_nk;
-    // Direct-to-LDS kernels: whole tile rows and K steps.  The rows decide the tile height; the columns may end inside a tile
-    // (not in a triangular launch, whose tiles are numbered by whole ones).
+    // Direct-to-LDS kernels: whole tile rows and K steps.  The rows decide the tile height; the columns of a rectangular product with
+    // B [K x N] may end inside a tile.
     const bool whole_k = (g.K % (4 * LK) == 0) && g.K > 0 && aligned(p.C, 4);
-    const bool n_ok = p.N % LN == 0 || (p.N > LN && !p.upper_only && !p.b_upper_tri);
+    const bool n_ok = p.N % LN == 0 || (p.N > LN && !p.b_is_nk && !p.upper_only && !p.b_upper_tri);
     const bool large = (p.M % LM == 0) && n_ok && whole_k;
     // 256 x 256 tiles when they still give every CU a couple of tiles (measured: 3-8 % faster on large rectangular
     // and symmetric-update launches; not on the skinny triangular products, whose tiles differ in K length)
@@ -492,8 +491,7 @@ int launch_gemm_f32(const GemmF32& p, hipStream_t s) {
         g.total = TileOrder::triangle_total(g.tiles_m, g.tiles_n, g.tri_ratio);
     }
     g.per_xcd = ceil_div(g.total, NXCD);
-    g.slots = g.per_xcd * NXCD;
-    dim3 grid((unsigned)g.slots);
+    dim3 grid((unsigned)(g.per_xcd * NXCD));
     if (dma) {
         const int tile = small ? TILE_SMALL : (wide ? TILE_WIDE : TILE_TALL);
 #define GPTQ_GEMM(T)                                                                                                        \

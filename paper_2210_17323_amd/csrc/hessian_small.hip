@@ -21,7 +21,7 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 namespace {
 
-struct SmallArgs { float* H; int64_t ldh; const void* X; int64_t ldx, n, t; int nt; };
+struct SmallArgs { float* H; int64_t ldh; const void* X; int64_t ldx, n, t; };
 
 // TYPE: GPTQ_F16, GPTQ_BF16 or GPTQ_F32
 template <int TYPE, int T, int WAVES>
@@ -162,14 +162,11 @@ __global__ __launch_bounds__(64 * WAVES) void syrk_small_kernel(SmallArgs g) {
 }
 
 template <int TYPE>
-int launch(const SmallArgs& a0, hipStream_t s) {
-    SmallArgs a = a0;
+int launch(const SmallArgs& a, hipStream_t s) {
     const int64_t n64 = ceil_div(a.n, 64), n32 = ceil_div(a.n, 32);
     if (n64 * (n64 + 1) / 2 >= 128) {
-        a.nt = (int)n64;
         hipLaunchKernelGGL((syrk_small_kernel<TYPE, 64, 8>), dim3((unsigned)(n64 * (n64 + 1) / 2)), dim3(512), 0, s, a);
     } else {
-        a.nt = (int)n32;
         hipLaunchKernelGGL((syrk_small_kernel<TYPE, 32, 16>), dim3((unsigned)(n32 * (n32 + 1) / 2)), dim3(1024), 0, s, a);
     }
     GPTQ_LAUNCH_CHECK();
@@ -179,7 +176,7 @@ int launch(const SmallArgs& a0, hipStream_t s) {
 }  // namespace
 
 int launch_syrk_small(float* H, int64_t ldh, const void* X, int xdtype, int64_t n, int64_t t, int64_t ldx, hipStream_t s) {
-    const SmallArgs a{H, ldh, X, ldx, n, t, 0};
+    const SmallArgs a{H, ldh, X, ldx, n, t};
     if (xdtype == GPTQ_F32) return launch<GPTQ_F32>(a, s);
     if (xdtype == GPTQ_BF16) return launch<GPTQ_BF16>(a, s);
     return launch<GPTQ_F16>(a, s);

@@ -1,11 +1,8 @@
-// Device code shared by the translation units of step 3 (Algorithm 1): the conversion helpers, the grid of
-// Section 4 from a range of weights, and the machinery with which a lane walks the 128 columns of a block -- the
-// stream of a 128 x 128 triangular block through LDS and the DPP row broadcast, the rank-1 update of a column.
+// Shared by the translation units of step 3 (Algorithm 1): the conversion helpers, the grid of Section 4 from a range of weights,
+// and the interface of the strip kernel that walks the columns of one outer block.
 #pragma once
 #include "common.h"
 #include "rules.h"
-
-#include <utility>
 
 namespace gptq {
 

@@ -24,6 +24,8 @@
 // 3.92 -> 1.61 ms.
 #include "quantize_common.h"
 
+#include <utility>
+
 namespace gptq {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));

@@ -72,7 +72,7 @@ def test_factor_form_equals_algorithm_1(bits, grid, group, n):
 
 
 def block_form_quantize(W, R, bits, grid, group, block=128):
-    """The arrangement quant_block_hybrid_kernel uses for groups inside a block: at a block start the working weights
+    """The arrangement the factor form of alg1_strip_kernel uses for groups inside a block: at a block start the working weights
     are w + s R_bb^-1 (the conditions (delta R)_k = 0 over the whole block), the block is then walked as Alg. 1 walks
     it, on U's diagonal block R_bb^-1, and hands d = w - q to the accumulators of the later columns."""
     W = np.asarray(W, dtype=np.float64)
