@@ -12,7 +12,8 @@
 //           loses the panel's products;
 //   inverse X_pc = L_pp^-1 X_pc, then X_ic -= L_ip X_pc for the rows below, X = L^-1 in accumulators too.
 // Three barriers a panel.  What bounds it is the chain of 128 pivots, ~150 cycles each, then latency of 8 x 3 barriers and of the
-// load.  Measured: 28 us a block; 37 us when the blocks were 32 x 32 with their columns handed round through LDS.
+// load.  Measured: 28 us a block with the chip to itself, 36 us on the mean beside the trailing updates of a 12288 x 12288
+// matrix; 37 us alone when the blocks were 32 x 32 with their columns handed round through LDS.
 #include "chol_diag.h"
 
 #include <utility>

@@ -14,8 +14,9 @@
 //     P = R[o0:j0, b] = H[o0:j0, b] R_bb^-T ;  H[o0:j0, o0:j0] -= P P^T    (one launch, inside the outer block only)
 //   after the outer block: R[0:o0, o] = H[0:o0, o] R_oo^-T              (strips of rows, one launch, chol_strip.hip)
 //                          H[0:o0, 0:o0] -= R[0:o0, o] R[0:o0, o]^T     (rank 1024, carries the flops)
-// The chain of an outer block is 8 x (27 us diagonal block + 15 us step).  With the panel and the update as products of
-// their own over all rows above it was 8 x (37 + 17 to 50 + 20 to 60 us): 11.5 ms at n = 12288 where this route takes 8.9.
+// The chain of an outer block is 8 x (28 us diagonal block + 15 us step) while nothing else runs, 8 x (36 + 26 us) on the mean of a
+// 12288 x 12288 factorisation, whose rank-1024 updates run beside it.  With the panel and the update as products of their own
+// over all rows above it was 8 x (37 + 17 to 50 + 20 to 60 us): 11.6 ms at n = 12288 where this route takes 9.25.
 //
 //   one outer block behind, on a stream of its own (only when the inverse is wanted): U_oo = R_oo^-1, kept dense for the
 //     inverse (chol_strip.hip).

@@ -734,9 +734,10 @@ __global__ __launch_bounds__(256) void symmetrize_kernel(float* H, int64_t ld, i
 using namespace gptq;
 
 constexpr int64_t SYRK_DMA_MIN_N = 2048;
-// Smaller layers take a workspace (and with it the 256 x 256 tiles over a split token range) only in long calls: what the
-// repack and the partial tiles cost is won back there -- 131072 tokens of 1000 channels: 250 us against 890 without one --,
-// and shorter calls go without.
+// Smaller layers take a workspace (and with it the 256 x 256 tiles over a split token range) in calls of more than 32768 tokens.  The
+// line is not where the two are equally fast: callers have been told that such layers need no workspace, and up to the length at
+// which a call is sliced elsewhere that stays so.  Measured with and without one, us: 256 channels 8192 tokens 37 / 36, 32768 48 / 118,
+// 131072 80 / 448; 1000 channels 4096 48 / 39, 8192 57 / 66, 32768 94 / 232, 131072 273 / 900; 2000 channels 4096 59 / 92, 32768 213 / 551.
 constexpr int64_t SYRK_SMALL_WS_TOKENS = 32768;
 constexpr int64_t SYRK_SMALL_WS_MIN_N = 256;
 static bool syrk_small_with_ws(int64_t n, int64_t t) {

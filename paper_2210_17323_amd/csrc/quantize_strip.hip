@@ -15,13 +15,13 @@
 //     registers of all four DPP rows: lane l of DPP row c receives M[j][4 (16 t + l) + c], and the multiply-add of
 //     register 16 t + l picks it up with the DPP row broadcast.
 //
-// What bounds it: a column is ~16 instructions that depend on one another in a chain plus 16 multiply-adds on average, all
-// of one wavefront (~205 cycles); a block's update is RT * 64 matrix instructions per later block and wavefront.  An
-// outer block takes 313 / 489 / 584 thousand cycles with 16 / 48 / 64 rows per workgroup, 210 of them in the walk.  With
-// one lane per row, a launch per block and an update launch between blocks the walk was 86 instructions per column for a
-// quarter of the wavefronts, and an outer block of 4096 rows took ~600 us (now ~145); Alg. 1 on a 4096 x 4096 layer 2.88 ->
-// 1.18 ms, 12288 x 12288 17.0 -> 13.0 ms, 14336 x 14336 in groups of 128 23.3 -> 20.4 ms, 3000 x 5120 in groups of 1024
-// 3.92 -> 1.61 ms.
+// What bounds it: a column is ~17 instructions that depend on one another in a chain plus 16 multiply-adds on average, all
+// of one wavefront (~210 cycles); a block's update is RT * 64 matrix instructions per later block and wavefront.  An
+// outer block takes 144 / 181 / 232 / 308 us with 16 / 32 / 48 / 64 rows per workgroup (driven by R; strip_row_tiles has all forms),
+// 100 of them in the walk.  With one lane per row, a launch per block and an update launch between blocks the walk was 86
+// instructions per column for a quarter of the wavefronts, and an outer block of 4096 rows took ~600 us; Alg. 1 on a 4096 x 4096
+// layer 2.88 -> 1.08 ms, 12288 x 12288 16.8 -> 13.3 ms, 14336 x 14336 in groups of 128 24.1 -> 21.3 ms, 3000 x 5120 in groups of 1024
+// 3.92 -> 1.48 ms.
 #include "quantize_common.h"
 
 #include <utility>
