@@ -9,6 +9,7 @@
 // row pitch 132 floats) so that the 32 lanes of a half-wavefront read 32 consecutive floats
 // (conflict free); the next K step is prefetched into registers while the current one is multiplied.
 #include "common.h"
+#include "rules.h"
 
 namespace gptq {
 
@@ -277,11 +278,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 3))) voi
 // k+2 is in flight and step k+3 is being issued; one bare s_barrier per step.
 constexpr int LM = 256, LN = 128, LK = 16;
 constexpr int WIDE_MIN_TILES = 512;
-constexpr int SMALL_MAX_LARGE_TILES = 256;
 
 // TILE_WIDE: a wavefront owns 128 x 64 (4 x 2 MFMA tiles): a third fewer copy instructions and a quarter fewer LDS reads per
 // flop, and half as many tile prologues and C read-modify-writes per flop.  TILE_SMALL: four times as many workgroups for
-// products that do not fill the chip (a 3072 x 1024 x 1024 product is 96 tiles of 256 x 128, 131 us each at the peak rate).
+// products that do not fill the chip (a 3072 x 1024 x 1024 product is 96 tiles of 256 x 128, 131 us each at the peak rate),
+// or whose last columns would be a second round of large tiles (product_small_tiles in rules.h).
 enum { TILE_TALL = 0, TILE_WIDE = 1, TILE_SMALL = 2 };
 
 template <bool B_IS_NK, int TILE>
@@ -475,9 +476,7 @@ int launch_gemm_f32(const GemmF32& p, hipStream_t s) {
         const double en = 0.77 * (double)tn_ / (double)(ceil_div(tn_, 256) * 256);
         wide = ew > en;
     }
-    // 128 x 128 tiles where the larger ones leave CUs without any, and for row counts that are only whole tiles of 128
-    const bool small = whole_k && n_ok && (p.M % 128 == 0) &&
-                       (!large || (p.M / LM) * ceil_div(p.N, LN) < SMALL_MAX_LARGE_TILES);
+    const bool small = whole_k && n_ok && (p.M % 128 == 0) && product_small_tiles(p.M, p.N);
     if (small) wide = false;
     const bool dma = large || small;
     const int64_t th = small ? 128 : (large ? LM : TM), tw = wide ? 256 : (dma ? LN : TN);      // tile height and width

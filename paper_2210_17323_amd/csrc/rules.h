@@ -23,6 +23,17 @@ constexpr bool hessian_f32_small_tiles(int64_t n, int64_t t) {
     return !whole && 118 * rounds < (hessian_rounds(n, 128) == 1 ? 385 : 630);
 }
 
+// ---- float32 products with rows in whole tiles of 128 and K in whole steps: 128 x 128 tiles, or 256 rows (256 x 128 and larger) ----
+// Small tiles where the larger ones leave CUs without any, for rows that are only whole tiles of 128, and where columns that end
+// inside a tile make a second round of which at most half is filled: the small ones take half of such a round.  Measured at
+// K = 1024, us, 256 x 128 / 128 x 128 / the guarded kernel: 4096 x 2050 (272 large tiles) 254 / 194 / 244, 8192 x 1026 (288) 254 / 193 / 245,
+// 2048 x 6018 (384) 256 / 198 / 242, 4096 x 3202 (416) 258 / 257 / 328, 4096 x 4098 (528) 381 / 320 / 390.  Beyond two rounds a product alone still
+// gains, but Alg. 1 on 12288 rows, whose strips run beside it, loses (10250 columns 12.5 ms against 13.0): the large tiles stay.
+constexpr bool product_small_tiles(int64_t m, int64_t n) {
+    const int64_t large = (m / 256) * ((n + 127) / 128);
+    return m % 256 != 0 || large < 256 || (n % 128 != 0 && large <= 384);
+}
+
 // ---- Alg. 1: columns are walked in blocks of QB; one strip launch takes an outer block of up to QOB of them ----
 constexpr int QB = 128;
 constexpr int QOB = 1024;

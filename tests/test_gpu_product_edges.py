@@ -9,7 +9,8 @@ pytestmark = pytest.mark.gpu
 CASES = [
     # rows, columns, k
     (128, 201, 128), (128, 129, 64), (384, 1023, 1024), (640, 130, 64), (256, 4097, 128),     # 128 x 128
-    (4096, 2050, 64), (2304, 4001, 192),                                                      # 256 x 128
+    (4096, 2050, 64), (2304, 4001, 192),                                                      # ... more than the chip holds at once
+    (4096, 2176, 64), (4096, 3201, 64),                                                       # 256 x 128, whole and ragged
     (256 * 16, 256 * 32, 64),                                                                 # 256 x 256
     (128, 127, 64), (129, 201, 128), (128, 201, 100),                                         # guarded: one tile's columns, rows, k
 ]

@@ -14,6 +14,7 @@ extern "C" {
 int64_t outer_block(int64_t group) { return alg1_outer_block(group); }
 int64_t block_columns(int64_t o0, int64_t o1, int i) { return strip_block_columns(o0, o1, i); }
 int row_tiles(int form, int64_t r) { return strip_row_tiles(form, r); }
+int product_small(int64_t m, int64_t n) { return product_small_tiles(m, n); }
 int f32_small_tiles(int64_t n, int64_t t) { return hessian_f32_small_tiles(n, t); }
 }
 """
@@ -31,6 +32,7 @@ def rules(tmp_path_factory):
     L.block_columns.restype, L.block_columns.argtypes = i64, [i64, i64, ctypes.c_int]
     L.row_tiles.argtypes = [ctypes.c_int, i64]
     L.f32_small_tiles.argtypes = [i64, i64]
+    L.product_small.argtypes = [i64, i64]
     return L
 
 
@@ -64,6 +66,24 @@ def test_float32_hessians_take_the_faster_kernel(rules, n, t, small, product):
     chosen = small if rules.f32_small_tiles(n, t) else product
     assert chosen <= 1.05 * min(small, product) + 1
     assert not rules.f32_small_tiles(3073, t)
+
+
+# float32 products, K = 1024: (rows, columns, microseconds with 256 x 128 tiles, with 128 x 128 tiles, with the guarded kernel)
+PRODUCT_TIMES = [
+    (2048, 4098, 263, 208, 254), (4096, 2050, 254, 194, 244), (8192, 1026, 254, 193, 245), (2304, 4994, 255, 197, 242), (2048, 6018, 256, 198, 242),
+    (4096, 2946, 257, 197, 243), (2048, 6530, 257, 257, 325), (12288, 1026, 259, 257, 329), (2048, 8066, 261, 259, 324), (4096, 4098, 381, 320, 390),
+    (2304, 9090, 383, 383, 456), (8192, 4098, 635, 572, 680), (12288, 12162, 2361, 2304, 2636),
+]
+
+
+@pytest.mark.parametrize("m,n,tall,small,guarded", PRODUCT_TIMES)
+def test_products_of_ragged_columns_are_no_slower_than_through_the_guarded_kernel(rules, m, n, tall, small, guarded):
+    assert (small if rules.product_small(m, n) else tall) <= guarded
+
+
+def test_products_take_large_tiles_once_they_fill_the_chip(rules):
+    for m, n, small in ((4096, 2048, 0), (4096, 1920, 1), (3840, 2048, 1), (4224, 4096, 1), (256, 32768, 0), (256, 32640, 1), (128, 65536, 1), (4096, 3201, 0)):
+        assert bool(rules.product_small(m, n)) == bool(small), (m, n)
 
 
 @pytest.mark.parametrize("form", [0, 1, 2])
