@@ -476,7 +476,7 @@ int launch_gemm_f32(const GemmF32& p, hipStream_t s) {
         const double en = 0.77 * (double)tn_ / (double)(ceil_div(tn_, 256) * 256);
         wide = ew > en;
     }
-    const bool small = whole_k && n_ok && (p.M % 128 == 0) && product_small_tiles(p.M, p.N);
+    const bool small = whole_k && n_ok && (p.M % 128 == 0) && product_small_tiles(p.M, p.N) && !(p.upper_only && triangle_guarded(p.M, p.K));
     if (small) wide = false;
     const bool dma = large || small;
     const int64_t th = small ? 128 : (large ? LM : TM), tw = wide ? 256 : (dma ? LN : TN);      // tile height and width

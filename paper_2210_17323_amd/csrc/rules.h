@@ -34,6 +34,12 @@ constexpr bool product_small_tiles(int64_t m, int64_t n) {
     return m % 256 != 0 || large < 256 || (n % 128 != 0 && large <= 384);
 }
 
+// Triangular products (upper tiles of A B^T: float32 Hessians) with rows in whole tiles of 128 but not of 256, in short calls: what counts
+// is how many workgroups start and end on a CU at a time, three of the guarded kernel's against two.  Measured, us, 128 x 128 direct-to-LDS
+// tiles / guarded: 64 tokens of 1664 channels 10.4 / 10.7, 3968 19.8 / 20.1, 4224 26.5 / 25.0, 6272 43.5 / 41.3, 14464 227 / 206; 128 tokens of 4224 37.4 / 37.1, 5504 49.1 / 50.2,
+// 6272 59.6 / 58.2, 14464 310 / 302; 192 tokens of 4224 48.2 / 49.0, 14464 405 / 404; 256 of 14464 492 / 508.
+constexpr bool triangle_guarded(int64_t m, int64_t k) { return m % 256 != 0 && m > 4096 && k < (m > 6144 ? 192 : 128); }
+
 // ---- Alg. 1: columns are walked in blocks of QB; one strip launch takes an outer block of up to QOB of them ----
 constexpr int QB = 128;
 constexpr int QOB = 1024;

@@ -13,6 +13,7 @@ CASES = [
     (torch.float32, 1013, 517, "none"), (torch.float32, 3072, 96, "none"),
     (torch.float32, 2048, 128, "none"), (torch.float32, 2300, 1100, "none"), (torch.float32, 2500, 96, "none"),      # 128 x 128 tiles, small, guarded
     (torch.float32, 3080, 128, "none"), (torch.float32, 3200, 128, "none"), (torch.float32, 3200, 100, "none"),      # ragged rows, 128 x 128, ragged tokens
+    (torch.float32, 4224, 64, "none"), (torch.float32, 6272, 128, "none"), (torch.float32, 6272, 192, "none"),      # guarded in short calls
     (torch.float32, 5888, 64, "none"), (torch.float32, 6144, 64, "none"),                                             # 256 x 128 and 256 x 256 tiles
     (torch.float16, 1, 5, "none"), (torch.float16, 32, 64, "none"), (torch.float16, 65, 1025, "none"), (torch.float16, 1536, 130, "none"),
     (torch.bfloat16, 999, 513, "none"), (torch.bfloat16, 1025, 8 * 64 + 1, "none"),

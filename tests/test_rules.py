@@ -15,6 +15,7 @@ int64_t outer_block(int64_t group) { return alg1_outer_block(group); }
 int64_t block_columns(int64_t o0, int64_t o1, int i) { return strip_block_columns(o0, o1, i); }
 int row_tiles(int form, int64_t r) { return strip_row_tiles(form, r); }
 int product_small(int64_t m, int64_t n) { return product_small_tiles(m, n); }
+int triangle_guarded_(int64_t m, int64_t k) { return triangle_guarded(m, k); }
 int f32_small_tiles(int64_t n, int64_t t) { return hessian_f32_small_tiles(n, t); }
 }
 """
@@ -32,7 +33,7 @@ def rules(tmp_path_factory):
     L.block_columns.restype, L.block_columns.argtypes = i64, [i64, i64, ctypes.c_int]
     L.row_tiles.argtypes = [ctypes.c_int, i64]
     L.f32_small_tiles.argtypes = [i64, i64]
-    L.product_small.argtypes = [i64, i64]
+    L.product_small.argtypes = L.triangle_guarded_.argtypes = [i64, i64]
     return L
 
 
@@ -79,6 +80,23 @@ PRODUCT_TIMES = [
 @pytest.mark.parametrize("m,n,tall,small,guarded", PRODUCT_TIMES)
 def test_products_of_ragged_columns_are_no_slower_than_through_the_guarded_kernel(rules, m, n, tall, small, guarded):
     assert (small if rules.product_small(m, n) else tall) <= guarded
+
+
+# triangular float32 products: (channels, tokens, microseconds with 128 x 128 direct-to-LDS tiles, with the guarded kernel)
+TRIANGLE_TIMES = [
+    (1664, 64, 10.4, 10.7), (2688, 128, 15.8, 17.6), (2944, 64, 16.8, 16.5), (3200, 64, 18.4, 18.2), (3200, 128, 26.0, 26.6), (3968, 64, 19.8, 20.1),
+    (4224, 64, 26.5, 25.0), (4224, 128, 37.4, 37.1), (4224, 192, 48.2, 49.0), (4480, 64, 26.7, 25.4),
+    (5248, 64, 34.3, 33.3), (5248, 128, 48.7, 48.2), (5504, 64, 34.7, 35.2), (5504, 128, 49.1, 50.2), (6272, 64, 43.5, 41.3), (6272, 128, 59.6, 58.2), (6272, 192, 78.0, 78.7),
+    (8320, 64, 70.4, 65.9), (8320, 128, 102.2, 99.5), (8320, 192, 134.1, 135.3), (10368, 64, 106.6, 97.9), (14464, 64, 227, 206), (14464, 128, 310, 302),
+    (14464, 192, 405, 404), (14464, 256, 492, 508), (14464, 512, 876, 935),
+]
+
+
+@pytest.mark.parametrize("n,t,small,guarded", TRIANGLE_TIMES)
+def test_short_triangular_products_take_the_faster_kernel(rules, n, t, small, guarded):
+    """... within 2 %; whole tiles of 256 rows never take the guarded one."""
+    assert (guarded if rules.triangle_guarded_(n, t) else small) <= 1.02 * min(small, guarded)
+    assert not rules.triangle_guarded_(n // 256 * 256, t)
 
 
 def test_products_take_large_tiles_once_they_fill_the_chip(rules):
