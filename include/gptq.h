@@ -191,7 +191,7 @@ GPTQ_API int gptq_check_info(const int* info_dev, int* host_info, void* stream);
  *   ws       at least gptq_quantize_layer_workspace_bytes(r, n, block, group) bytes, 256-byte aligned.
  *   The update of column j's block and the rank-128 updates inside an outer block of 1024 columns are float32; the
  *   deferred rank-1024 updates beyond it are float32 matrix-core products or, when large, the split products of
- *   gptq_trailing_update_split below (n > 1024, any r > 128: rows are padded to whole tiles in the workspace).
+ *   gptq_trailing_update_split below (n % 256 == 0 and n >= 2048, any r > 128: rows are padded to whole tiles in the workspace).
  *   r == 0 or n == 0 is a valid no-op.  Like step 2, the call puts part of its work on the library's helper
  *   stream and joins it back before returning.
  */
@@ -257,7 +257,7 @@ GPTQ_API int gptq_trailing_update(float* W, int64_t ldw, const float* E, int64_t
  * statement of the outer loop).  Every row of E and P and every column of U is scaled by a power of two that brings its
  * largest element to [2^14, 2^15), every scaled element is the sum of two float16 pieces but for at most 2^-23 of it (2^-40 of the
  * row's largest element, if that is more), and the four piece products of a * b are accumulated in float32, smallest first: at most
- * 2^-22 |a b| a product, 1.4e-7 to 2.1e-7 of the result's norm with the accumulation (normal data; the float32 kernel 5.7e-7).
+ * 2^-22 |a b| a product, 2.1e-7 of the result's norm with the accumulation (normal data; the float32 kernel 5.7e-7).
  *
  * gptq_trailing_update_split:   W[r x ncols] -= E[r x k] * U[k x ncols]       (arguments as gptq_trailing_update)
  * gptq_symmetric_update_split:  H[n x n] -= P[n x k] * P^T on the 256 x 256 tiles that touch the upper triangle
@@ -268,8 +268,7 @@ GPTQ_API int gptq_trailing_update(float* W, int64_t ldw, const float* E, int64_t
  *   Operand elements must be finite and below 2^127 in magnitude.
  */
 /*
- * Which launches take the split products is decided per launch from its count of 256 x 256 tiles: at least 65 beside other work,
- * 126 where the rest of the call waits for them (a quarter of the 128 x 128 tiles they have).
+ * Which launches take the split products is decided per launch from its count of 256 x 256 tiles: at least 144.
  * gptq_set_split_min_tiles(t) with t > 0 replaces that minimum for every later call of the process (t <= 0 restores
  * it) and returns the previous setting: a tuning and test knob -- the results of a call depend on it only through
  * rounding.  Not meant to be changed while another thread is inside a library call.

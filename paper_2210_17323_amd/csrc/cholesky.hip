@@ -92,8 +92,8 @@ using namespace gptq;
 namespace {
 constexpr int OB = 1024;     // outer block: rank-1024 updates keep the big GEMMs compute-bound and their tiles long
 static_assert(OB == SPLIT_K, "the split products take exactly one outer block as K");
-// A rank-1024 update goes through the split-operand kernel (float16 matrix cores) when its tiles fill the
-// chip well (split_pays): the strip of the next outer block has 8 tile columns, the square rest t (t + 1) / 2 tiles.
+// A rank-1024 update goes through the split-operand kernel (float16 matrix cores, 256 x 256 tiles) when its tiles fill the
+// chip well (split_pays): the strip of the next outer block has 4 tile columns, the square rest t (t + 1) / 2 tiles.
 
 struct CholWs { float* dinv; float* T; float* T2; int64_t ld2; float* Uoo; float* tri; float* tri2; unsigned char* planes; unsigned char* planes2; int* flags; size_t total; };
 CholWs chol_ws_layout(void* ws, int64_t n, bool with_split = true) {
@@ -238,13 +238,11 @@ static int chol_run(float* H, int64_t ld, int64_t n, float percdamp, void* ws, i
         // parts, as row operand and as column operand; the pieces of two panels take turns, since the square of the outer block before
         // may still be read.
         if (int rc = ts.wait(s4, rows_done)) return rc;
-        // (The two run beside each other: what counts is whether they fill the chip together.  Measured with a minimum of 260 / 504 tiles,
-        // us: factor 4096 1118 / 1162, 5000 1491 / 1565, 7000 2220 / 2323, 8192 2676 / 2786; with the inverse's row blocks on the third
-        // stream 5000 2262 / 2199, 6144 2940 / 2826, 7000 3800 / 3757.)
-        const bool split = w.planes && split_pays((p0 / 128) * (OB / 128) + (p0 / 128) * (p0 / 128 + 1) / 2, want_inverse ? SPLIT_WAITED_FOR : SPLIT_BESIDE);
+        // (the two run beside each other: what counts is whether they fill the chip together)
+        const bool split = w.planes && ow == OB && split_pays((p0 / 256) * (OB / 256) + (p0 / 256) * (p0 / 256 + 1) / 2);
         unsigned char* planes = (o & 1) ? w.planes2 : w.planes;
         if (split)
-            if (int rc = launch_split_rows(H + o0, ld, o0, ow, planes, s4)) return rc;
+            if (int rc = launch_split_rows(H + o0, ld, o0, planes, s4)) return rc;
         hipEvent_t panel = nullptr;
         if (int rc = ts.mark(s4, &panel)) return rc;
         if (int rc = ts.wait(s4, before)) return rc;     // it wrote the same columns
@@ -254,7 +252,7 @@ static int chol_run(float* H, int64_t ld, int64_t n, float percdamp, void* ws, i
         sg.ldc = ld; sg.alpha = -1.f;
         if (split) {
             sg.a_panel0 = 0; sg.b_panel0 = (int)(p0 / 256); sg.C = H + p0;
-            sg.M = p0; sg.N = OB;
+            sg.tiles_m = (int)(p0 / 256); sg.tiles_n = (int)(OB / 256);
             if (int rc = launch_gemm_split(sg, s4)) return rc;
         } else {
             Opt co; co.nk = true;
@@ -264,7 +262,7 @@ static int chol_run(float* H, int64_t ld, int64_t n, float percdamp, void* ws, i
         if (int rc = ts.wait(s2, panel)) return rc;
         if (split) {
             sg.a_panel0 = sg.b_panel0 = 0; sg.C = H;
-            sg.M = sg.N = p0;
+            sg.tiles_m = sg.tiles_n = (int)(p0 / 256);
             sg.upper_square = true;
             if (int rc = launch_gemm_split(sg, s2)) return rc;
         } else {
@@ -296,16 +294,16 @@ static int chol_run(float* H, int64_t ld, int64_t n, float percdamp, void* ws, i
         if (k1 < n && k0 > 0) {
             // U[0:k0, k1:n] += U[0:k0, k] (-U_kk R[k, k1:n])   (U[0:k0, k] not yet multiplied by U_kk; the second factor is
             // what the factorisation left in the row block)
-            if (w.planes && split_pays((k0 / 128) * ceil_div(n - k1, 128), SPLIT_WAITED_FOR)) {
+            if (w.planes && kw == OB && (n - k1) % 256 == 0 && split_pays((k0 / 256) * ((n - k1) / 256))) {
                 // through the split products; the column block has been read once its pieces are made
-                if (int rc = launch_split_rows(H + k0, ld, k0, kw, w.planes, s)) return rc;
+                if (int rc = launch_split_rows(H + k0, ld, k0, w.planes, s)) return rc;
                 if (int rc = ts.mark(s, &read_done)) return rc;
                 marked = true;
-                if (int rc = launch_split_cols(H + k0 * ld + k1, ld, n - k1, kw, w.planes2, s)) return rc;
+                if (int rc = launch_split_cols(H + k0 * ld + k1, ld, n - k1, w.planes2, s)) return rc;
                 SplitGemm sg{};
                 sg.A_planes = w.planes; sg.A_exps = split_exponents(w.planes, k0);
                 sg.B_planes = w.planes2; sg.B_exps = split_exponents(w.planes2, n - k1);
-                sg.C = H + k1; sg.ldc = ld; sg.alpha = 1.f; sg.M = k0; sg.N = n - k1;
+                sg.C = H + k1; sg.ldc = ld; sg.alpha = 1.f; sg.tiles_m = (int)(k0 / 256); sg.tiles_n = (int)((n - k1) / 256);
                 if (int rc = launch_gemm_split(sg, s)) return rc;
             } else {
                 Opt u;

@@ -127,14 +127,15 @@ struct GemmF32 {
 int launch_gemm_f32(const GemmF32& g, hipStream_t s);
 
 // ---- float32 products of rank 1024 on the 16-bit matrix cores (gemm_split.hip) -----------------
-// C[M x N] += alpha * A * B^T over K = up to SPLIT_K, with both operands given as "planes": the two
+// C[256 tiles_m x 256 tiles_n] += alpha * A * B^T over K = SPLIT_K, with both operands given as "planes": the two
 // float16 pieces of every float32 element, scaled by a power of two per row, in the blocked layout the kernel copies
 // straight into LDS, and the rows' exponents behind them.
-//   launch_split_rows: A [rows x k] float32, K contiguous, k <= SPLIT_K    -> planes of ceil(rows / 256) panels
-//   launch_split_cols: B [k x cols] float32, columns contiguous            -> planes of ceil(cols / 256) panels (of B^T)
-// Both write split_planes_bytes(rows) bytes; rows and k past the operand's end are zeros.  A launch reads panels a_panel0 .. and
+//   launch_split_rows: A [rows x SPLIT_K] float32, K contiguous        -> planes of ceil(rows / 256) panels
+//   launch_split_cols: B [SPLIT_K x cols] float32, columns contiguous  -> planes of ceil(cols / 256) panels (of B^T)
+// Both write split_planes_bytes(rows) bytes; rows past the operand's end are zeros.  A launch reads panels a_panel0 .. and
 // b_panel0 .. of the two plane buffers.
 //   upper_square: C is square and only the tiles of its upper triangle are computed (diagonal tiles whole).
+//   skip_lower:   rectangular C at (crow0, ccol0) of a parent matrix: tiles entirely below the parent's diagonal are left out.
 constexpr int SPLIT_K = 1024;
 struct SplitGemm {
     const unsigned char* A_planes; int a_panel0;
@@ -143,21 +144,17 @@ struct SplitGemm {
     const int* B_exps;
     float* C; int64_t ldc;
     float alpha;
-    int64_t M, N;
+    int tiles_m, tiles_n;
     bool upper_square;
-    bool whole_tiles;                   // tiles of 256 x 256 (M and N must be whole ones)
+    bool skip_lower; int64_t crow0, ccol0;
 };
 size_t split_planes_bytes(int64_t rows);
-// Whether a launch of that many 128 x 128 tiles should take the split kernel.  `least` by what the launch is to its caller: beside other work
-// the split products gain as soon as the float32 kernel's 128 x 128 tiles begin a second round; where something waits for them they also have
-// their operands' split before them (5120 x 1024, 320 tiles: 117 us against 133, 2048 x 2048: 92 against 78).
-constexpr int64_t SPLIT_BESIDE = 260, SPLIT_WAITED_FOR = 504;
-bool split_pays(int64_t tiles128, int64_t least);
+bool split_pays(int64_t tiles);         // whether a launch of that many 256 x 256 tiles should take the split kernel
 inline int* split_exponents(unsigned char* planes, int64_t rows) {      // behind the planes: two of 256 x SPLIT_K float16 a panel
     return reinterpret_cast<int*>(planes + ceil_div(rows < 1 ? 1 : rows, 256) * (2 * 256 * SPLIT_K * 2));
 }
-int launch_split_rows(const float* A, int64_t lda, int64_t rows, int64_t k, unsigned char* planes, hipStream_t s);
-int launch_split_cols(const float* B, int64_t ldb, int64_t cols, int64_t k, unsigned char* planes, hipStream_t s);
+int launch_split_rows(const float* A, int64_t lda, int64_t rows, unsigned char* planes, hipStream_t s);
+int launch_split_cols(const float* B, int64_t ldb, int64_t cols, unsigned char* planes, hipStream_t s);
 int launch_gemm_split(const SplitGemm& g, hipStream_t s);
 
 }  // namespace gptq

@@ -122,12 +122,12 @@ static bool factor_form_group_supported(int64_t group) { return group == 0 || gr
 // Trailing updates beyond an outer block are deferred and applied as one rank-1024 GEMM.
 static_assert(QOB == SPLIT_K, "the split products take exactly one outer block as K");
 
-// The deferred rank-1024 updates go through the split-operand kernel (float16 matrix cores) when the launch fills the chip well
-// (split_pays).  `r` are the padded rows, so any row count above 128 qualifies, and any number of columns.  Error against
-// 64-bit products on operands of Alg. 1's kind: 1.4e-7 (split, 128 x 128 tiles) or 2.2e-7 (256 x 256) against 5.7e-7 (float32 kernel).  Minimum of the
-// rest / of the next columns, whole calls, us with 260 / 504 tiles: rest 3000 x 5120 1086 / 1139, 1500 x 8192 1623 / 1783; next 6144 x 6144 2115 / 2060.  Rows'
-// losses against a 64-bit walk: the same to 1 % with either kernel.
-static bool split_shapes_ok(int64_t r, int64_t n) { return r >= 256 && r % 256 == 0 && n > QOB; }
+// The deferred rank-1024 updates go through the split-operand kernel (float16 matrix cores, 256 x 256 tiles, one per
+// workgroup) when columns come in whole tiles and the launch fills the chip well (split_pays).  `r` are the padded rows, so any
+// row count above 128 qualifies.  Measured against 64-bit products on operands of Alg. 1's kind, 96 to 1372 tiles: relative error
+// 2.2e-7 (split) against 5.7e-7 (float32 kernel); from 144 tiles on 160 us against 245, at 128 tiles 160 against 150.  Rows'
+// losses against a 64-bit walk, ragged row counts 2000 .. 16000 and 5120 .. 12288 columns, both forms: the same to 1 % with either.
+static bool split_shapes_ok(int64_t r, int64_t n) { return r >= 256 && r % 256 == 0 && n % 256 == 0 && n >= 2 * QOB; }
 
 // Rows of the working matrix and of the error panels in the workspace: whole tiles of the deferred updates, so that a layer
 // of any row count takes the large-tile kernels (3000 rows x 5120 columns: 190-250 us an update through the guarded
@@ -136,7 +136,7 @@ static bool split_shapes_ok(int64_t r, int64_t n) { return r >= 256 && r % 256 =
 static int64_t padded_rows(int64_t r) { return r >= 64 ? (int64_t)round_up((size_t)r, r <= 128 ? 128 : 256) : std::max<int64_t>(r, 1); }
 
 struct QuantWs { size_t wk, e, pk, ub, rt, pa, pb, pr, total; int64_t ldk, rows; bool split; };
-static QuantWs quant_ws_layout(int64_t r, int64_t n, int64_t group, bool with_split = true) {
+static QuantWs quant_ws_layout(int64_t r, int64_t n, int64_t group) {
     QuantWs l;
     l.ldk = (int64_t)round_up((size_t)std::max<int64_t>(n, 1), 4);
     l.rows = padded_rows(r);
@@ -150,7 +150,7 @@ static QuantWs quant_ws_layout(int64_t r, int64_t n, int64_t group, bool with_sp
     l.rt = off;                                                                                       // ... and R with its column blocks scaled by them
     if (inner_groups) off += round_up((size_t)std::max<int64_t>(n, 1) * l.ldk * sizeof(float), 256);
     // split products (gemm_split.hip): the pieces of an error panel, of the next outer block's rows of U and of all rows beyond
-    l.split = with_split && split_shapes_ok(l.rows, n);
+    l.split = split_shapes_ok(l.rows, n);
     l.pa = l.pb = l.pr = off;
     if (l.split) {
         l.pa = off; off += round_up(split_planes_bytes(l.rows), 256);
@@ -212,9 +212,7 @@ static int alg1_run(bool rf, const void* W, int wdtype, int64_t ldw, int64_t r, 
     if (!W || !U || !codes || !scales || !zeros) return fail(GPTQ_ERR_INVALID_ARG, "quantize_layer: null pointer");
     if (ldw < n || ldu < n || ldc < n || (Wq && ldq < n)) return fail(GPTQ_ERR_INVALID_ARG, "quantize_layer: leading dimension smaller than n");
     if (!aligned(U, 16) || ldu % 4) return fail(GPTQ_ERR_INVALID_ARG, "quantize_layer: U must be 16-byte aligned with ldu %% 4 == 0");
-    QuantWs lay = quant_ws_layout(r, n, group);
-    // a workspace without room for the split products is enough for few columns and where they do not come in whole tiles of 256
-    if (ws_bytes < lay.total && (n % 256 != 0 || n < 2 * QOB)) lay = quant_ws_layout(r, n, group, false);
+    const QuantWs lay = quant_ws_layout(r, n, group);
     if (!ws || !aligned(ws, 256) || ws_bytes < lay.total) return fail(GPTQ_ERR_WORKSPACE, "quantize_layer: workspace missing, misaligned or too small");
     if (r > 0x7fffffffLL) return fail(GPTQ_ERR_UNSUPPORTED, "quantize_layer: too many rows");
 
@@ -319,22 +317,22 @@ static int alg1_run(bool rf, const void* W, int wdtype, int64_t ldw, int64_t r, 
             rest_done = nullptr;
             const float alpha = 1.f;                 // the U form's panel holds -e
             const bool full = lay.split && ob == QOB && o1 - o0 == QOB;
-            const bool split_strip = full && split_pays((rows / 128) * ceil_div(o2 - o1, 128), SPLIT_WAITED_FOR);
-            const bool split_rest = full && o2 < n && split_pays((rows / 128) * ceil_div(n - o2, 128), SPLIT_BESIDE);
+            const bool split_strip = full && o2 - o1 == QOB && split_pays((rows / 256) * (QOB / 256));
+            const bool split_rest = full && o2 < n && split_pays((rows / 256) * ((n - o2) / 256));
             SplitGemm sg{};
             sg.A_planes = Pa; sg.A_exps = split_exponents(Pa, rows); sg.a_panel0 = 0;
-            sg.ldc = lay.ldk; sg.alpha = alpha; sg.M = rows;
+            sg.ldc = lay.ldk; sg.alpha = alpha; sg.tiles_m = (int)(rows / 256);
             GemmF32 g{};
             g.A = E; g.lda = QOB; g.B = Bm + o0 * ldb + o1; g.ldb = ldb; g.C = Wk + o1; g.ldc = lay.ldk;
             g.M = rows; g.N = o2 - o1; g.K = o1 - o0; g.alpha = alpha; g.b_is_nk = false; g.overwrite = false;
             if (split_strip) {
                 // the pieces of the error panel are made here, for both parts (the helper stream's last reader of the
                 // buffer is what the wait above was for); those of U's rows for the next outer block's columns as well
-                if (int rc = launch_split_rows(E, QOB, rows, QOB, Pa, s)) return rc;
-                if (int rc = launch_split_cols(Bm + o0 * ldb + o1, ldb, o2 - o1, o1 - o0, Pb, s)) return rc;
+                if (int rc = launch_split_rows(E, QOB, rows, Pa, s)) return rc;
+                if (int rc = launch_split_cols(Bm + o0 * ldb + o1, ldb, QOB, Pb, s)) return rc;
                 if (int rc = ts.mark(s, &quantized)) return rc;
-                sg.B_planes = Pb; sg.B_exps = split_exponents(Pb, o2 - o1); sg.b_panel0 = 0;
-                sg.C = Wk + o1; sg.N = o2 - o1;
+                sg.B_planes = Pb; sg.B_exps = split_exponents(Pb, QOB); sg.b_panel0 = 0;
+                sg.C = Wk + o1; sg.tiles_n = QOB / 256;
                 if (int rc = launch_gemm_split(sg, s)) return rc;
             } else {
                 if (int rc = launch_gemm_f32(g, s)) return rc;
@@ -343,13 +341,13 @@ static int alg1_run(bool rf, const void* W, int wdtype, int64_t ldw, int64_t r, 
                 if (split_rest) {
                     // U's rows for all columns beyond depend on nothing of this outer block: they are split before the helper
                     // stream waits for it (the buffer's last reader, the previous rest update, precedes this on the stream)
-                    if (int rc = launch_split_cols(Bm + o0 * ldb + o2, ldb, n - o2, o1 - o0, Pr, s2)) return rc;
+                    if (int rc = launch_split_cols(Bm + o0 * ldb + o2, ldb, n - o2, Pr, s2)) return rc;
                 }
                 if (int rc = ts.wait(s2, quantized)) return rc;
                 if (split_rest) {
-                    if (!split_strip) { if (int rc = launch_split_rows(E, QOB, rows, QOB, Pa, s2)) return rc; }
+                    if (!split_strip) { if (int rc = launch_split_rows(E, QOB, rows, Pa, s2)) return rc; }
                     sg.B_planes = Pr; sg.B_exps = split_exponents(Pr, n - o2); sg.b_panel0 = 0;
-                    sg.C = Wk + o2; sg.N = n - o2;
+                    sg.C = Wk + o2; sg.tiles_n = (int)((n - o2) / 256);
                     if (int rc = launch_gemm_split(sg, s2)) return rc;
                 } else {
                     g.B = Bm + o0 * ldb + o2; g.C = Wk + o2; g.N = n - o2;

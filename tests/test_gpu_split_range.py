@@ -68,7 +68,7 @@ def split_everywhere():
 @pytest.mark.parametrize("n", [2052, 2500, 3072, 3604])
 @pytest.mark.parametrize("inverse", [False, True])
 def test_factors_whose_last_outer_block_is_ragged(split_everywhere, n, inverse):
-    # products over fewer than 1024 columns (the last outer block's) and into columns that end inside a tile (the inverse's)
+    # beside whole outer blocks, products over fewer than 1024 columns (the last one's) and into columns that end inside a tile (the inverse's)
     g = split_everywhere
     gen = torch.Generator(device="cuda").manual_seed(n)
     X = torch.randn((n, 2 * n), device="cuda", generator=gen)
@@ -92,7 +92,7 @@ def test_factors_whose_last_outer_block_is_ragged(split_everywhere, n, inverse):
 @pytest.mark.parametrize("r, n", [(300, 1028), (300, 2050), (520, 3100), (1000, 4096)])
 @pytest.mark.parametrize("factor", [False, True])
 def test_layers_of_ragged_columns(r, n, factor):
-    # deferred updates of columns that end inside a tile: the same layer with the float32 products and with the split ones
+    # the same layer with the float32 products and, where columns come in whole tiles, with the split ones
     import paper_2210_17323_amd as g
     gen = torch.Generator(device="cuda").manual_seed(r + n)
     W = torch.randn((r, n), device="cuda", generator=gen).half()
@@ -105,22 +105,21 @@ def test_layers_of_ragged_columns(r, n, factor):
     (g.gptq_damp_cholesky if factor else g.gptq_damp_cholesky_inverse)(H, 0.01, ws, info)
     res = []
     need = g.gptq_quantize_layer_workspace_bytes(r, n, 128, 0)
-    pieces = ((r + 255) // 256 + 4 + (n + 255) // 256) * 3 * 32 * 16384 + 3 * 16384      # of the error panel, of the next and of all columns
-    # the last: a workspace without room for the pieces does for columns that are no whole tiles, with the float32 products
-    for tiles, nbytes in ((1 << 30, need), (1, need)) + (((1, need - pieces),) if n % 256 else ()):
+    for tiles in (1 << 30, 1):
         prev = g.gptq_set_split_min_tiles(tiles)
         try:
             codes = torch.zeros((r, n), dtype=torch.uint8, device="cuda")
             scales, zeros = torch.zeros((r, 1), device="cuda"), torch.zeros((r, 1), dtype=torch.int32, device="cuda")
             e2 = torch.zeros(r, dtype=torch.float64, device="cuda")
-            qws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda")
-            print(f"layer {r} x {n} factor={factor} min tiles {tiles} workspace {nbytes}", flush=True)
+            qws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
+            print(f"layer {r} x {n} factor={factor} min tiles {tiles}", flush=True)
             g.gptq_quantize_layer(W, H, 4, g.GPTQ_GRID_MINMAX, 128, 0, codes, scales, zeros, qws, half_E2_rows=e2, from_factor=factor)
             torch.cuda.synchronize()
         finally:
             g.gptq_set_split_min_tiles(prev)
         res.append((codes, e2))
-    assert len(res) == 2 or (torch.equal(res[2][0], res[0][0]) and torch.equal(res[2][1], res[0][1]))
+    if n % 256:                                             # columns that are no whole tiles: float32 products whatever the minimum
+        assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
     # a rounding tie decided the other way changes later codes of its row: few rows, and no row's loss by much
     differ = (res[0][0] != res[1][0]).any(1)
     rel = ((res[0][1] - res[1][1]) / res[0][1]).abs()

@@ -144,3 +144,15 @@ def test_quantize_workspace_of_few_rows():
         need = g.gptq_quantize_layer_workspace_bytes(r, n) - base - (n + panels) * 4 * rows
         planes = (rows + 1024 + n) * 6144 + 3 * 16384 if rows % 256 == 0 else 0
         assert need == planes, (r, need, planes)
+
+
+def test_quantize_workspace_of_ragged_columns():
+    """Columns that are no whole tiles of 256, or fewer than two outer blocks of them, never take the split products: no room for their
+    pieces.  Working matrix, two error panels, the packed factor (the same for all) and 256 bytes, in whole 256 bytes each."""
+    up = lambda b: (b + 255) // 256 * 256
+    need = lambda r, n: g.gptq_quantize_layer_workspace_bytes(r, n)
+    packed = need(1, 4) - up(4 * 4) - 2 * up(1024 * 4)
+    for r, rows, n in ((300, 512, 1028), (300, 512, 2050), (3000, 3072, 5000), (4096, 4096, 1500), (4096, 4096, 1792), (12288, 12288, 10250)):
+        ld = (n + 3) // 4 * 4
+        assert need(r, n) == up(rows * ld * 4) + 2 * up(rows * 4096) + packed, (r, n)
+    assert need(300, 2048) > need(300, 2052)
