@@ -129,9 +129,9 @@ GPTQ_API int gptq_hessian_symmetrize(float* H, int64_t ldh, int64_t n, void* str
  *             gptq_check_info.  percdamp < 0 is invalid; percdamp == 0 is allowed.
  *   Computed as a Cholesky factorisation taken from the last column backwards, H + lambda I = R R^T with R
  *   upper triangular, followed by the triangular inverse U = R^-1 (the same matrix, by uniqueness of
- *   the Cholesky factor), all in float32; the rank-1024 updates that carry most of the flops multiply two-piece
- *   float16 splits of their float32 operands on the float16 matrix cores when they are large (see
- *   gptq_symmetric_update_split below), which is also what the second half of
+ *   the Cholesky factor), all in float32; the rank-1024 updates that carry most of the flops multiply three-piece
+ *   bfloat16 splits of their float32 operands on the bf16 matrix cores when they are large (see
+ *   gptq_symmetric_update_split below: the error of a float32 multiply-add), which is also what the second half of
  *   the workspace is for.
  *   Part of the work is enqueued on helper streams owned by the library (created once per host thread and
  *   device, default priority) and joined back with events: when the call returns, everything it enqueued
@@ -252,12 +252,11 @@ GPTQ_API int gptq_trailing_update(float* W, int64_t ldw, const float* E, int64_t
                          int64_t r, int64_t ncols, int64_t k, void* stream);
 
 /*
- * The two deferred rank-1024 updates through split float32 products on the float16 matrix cores -- the form
+ * The two deferred rank-1024 updates through split float32 products on the bf16 matrix cores -- the form
  * gptq_damp_cholesky* and gptq_quantize_layer* use for their large updates (Section 3, Steps 2 and 3; Alg. 1, last
- * statement of the outer loop).  Every row of E and P and every column of U is scaled by a power of two that brings its
- * largest element to [2^14, 2^15), every scaled element is the sum of two float16 pieces but for at most 2^-23 of it (2^-40 of the
- * row's largest element, if that is more), and the four piece products of a * b are accumulated in float32, smallest first: at most
- * 2^-22 |a b| a product, 2.1e-7 of the result's norm with the accumulation (normal data; the float32 kernel 5.7e-7).
+ * statement of the outer loop).  Every float32 operand element is the exact sum of three bfloat16 pieces
+ * (8 + 8 + 8 significant bits); of the nine piece products of a * b the six with i + j <= 4 are accumulated in
+ * float32, smallest first; the three left out are below 2^-23 |a b|, the size of a float32 rounding.
  *
  * gptq_trailing_update_split:   W[r x ncols] -= E[r x k] * U[k x ncols]       (arguments as gptq_trailing_update)
  * gptq_symmetric_update_split:  H[n x n] -= P[n x k] * P^T on the 256 x 256 tiles that touch the upper triangle

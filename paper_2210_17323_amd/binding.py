@@ -279,7 +279,7 @@ def gptq_trailing_update_split_workspace_bytes(r: int, ncols: int) -> int:
 
 
 def gptq_trailing_update_split(W: torch.Tensor, E: torch.Tensor, U: torch.Tensor, ws: torch.Tensor) -> None:
-    """W[r x ncols] -= E[r x 1024] @ U[1024 x ncols] through split float32 products on the float16 matrix cores."""
+    """W[r x ncols] -= E[r x 1024] @ U[1024 x ncols] through split float32 products on the bf16 matrix cores."""
     for t, nm in ((W, "W"), (E, "E"), (U, "U")):
         _dev2d(t, nm, (torch.float32,))
     r, ncols = W.shape

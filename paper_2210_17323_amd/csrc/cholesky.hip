@@ -92,7 +92,7 @@ using namespace gptq;
 namespace {
 constexpr int OB = 1024;     // outer block: rank-1024 updates keep the big GEMMs compute-bound and their tiles long
 static_assert(OB == SPLIT_K, "the split products take exactly one outer block as K");
-// A rank-1024 update goes through the split-operand kernel (float16 matrix cores, 256 x 256 tiles) when its tiles fill the
+// A rank-1024 update goes through the split-operand kernel (bf16 matrix cores, 256 x 256 tiles) when its tiles fill the
 // chip well (split_pays): the strip of the next outer block has 4 tile columns, the square rest t (t + 1) / 2 tiles.
 
 struct CholWs { float* dinv; float* T; float* T2; int64_t ld2; float* Uoo; float* tri; float* tri2; unsigned char* planes; unsigned char* planes2; int* flags; size_t total; };
@@ -111,7 +111,7 @@ CholWs chol_ws_layout(void* ws, int64_t n, bool with_split = true) {
     l.Uoo = static_cast<float*>(at(nouter * OB * OB * sizeof(float)));       // U_oo of every outer block, dense
     l.tri = static_cast<float*>(at(TRIANGLE_WORDS * sizeof(float)));         // an outer block of R packed for its inverse
     l.tri2 = static_cast<float*>(at(TRIANGLE_WORDS * sizeof(float)));        // ... and for the rows above it (every other one)
-    if (with_split && (int64_t)n1 >= 2 * OB) {                               // split products: pieces of a column panel
+    if (with_split && (int64_t)n1 >= 2 * OB) {                               // split products: bf16 pieces of a column panel
         l.planes = static_cast<unsigned char*>(at(split_planes_bytes((int64_t)n1)));
         l.planes2 = static_cast<unsigned char*>(at(split_planes_bytes((int64_t)n1)));      // ... and of a row block (the inverse)
     }
@@ -234,7 +234,7 @@ static int chol_run(float* H, int64_t ld, int64_t n, float percdamp, void* ws, i
         if (int rc = launch_next_block_update(H + p0 * ld + p0, ld, H + p0 * ld + o0, ld, ow, s)) return rc;
         if (p0 == 0) continue;
         // H[0:p0, 0:o0] -= R[0:p0, o] R[0:o0, o]^T (rank 1024, upper tiles), the columns [p0, o0) on one stream and the square left of
-        // them on the other.  Large updates multiply the pieces of the panel R[0:o0, o] (gemm_split.hip): one split of it serves both
+        // them on the other.  Large updates multiply the bf16 pieces of the panel R[0:o0, o] (gemm_split.hip): one split of it serves both
         // parts, as row operand and as column operand; the pieces of two panels take turns, since the square of the outer block before
         // may still be read.
         if (int rc = ts.wait(s4, rows_done)) return rc;
@@ -248,7 +248,7 @@ static int chol_run(float* H, int64_t ld, int64_t n, float percdamp, void* ws, i
         if (int rc = ts.wait(s4, before)) return rc;     // it wrote the same columns
         SplitGemm sg{};
         sg.A_planes = sg.B_planes = planes;
-        sg.A_exps = sg.B_exps = planes ? split_exponents(planes, o0) : nullptr;
+        sg.A_zero = sg.B_zero = planes ? split_zero_block(planes, o0) : nullptr;
         sg.ldc = ld; sg.alpha = -1.f;
         if (split) {
             sg.a_panel0 = 0; sg.b_panel0 = (int)(p0 / 256); sg.C = H + p0;
@@ -301,8 +301,8 @@ static int chol_run(float* H, int64_t ld, int64_t n, float percdamp, void* ws, i
                 marked = true;
                 if (int rc = launch_split_cols(H + k0 * ld + k1, ld, n - k1, w.planes2, s)) return rc;
                 SplitGemm sg{};
-                sg.A_planes = w.planes; sg.A_exps = split_exponents(w.planes, k0);
-                sg.B_planes = w.planes2; sg.B_exps = split_exponents(w.planes2, n - k1);
+                sg.A_planes = w.planes; sg.A_zero = split_zero_block(w.planes, k0);
+                sg.B_planes = w.planes2; sg.B_zero = split_zero_block(w.planes2, n - k1);
                 sg.C = H + k1; sg.ldc = ld; sg.alpha = 1.f; sg.tiles_m = (int)(k0 / 256); sg.tiles_n = (int)((n - k1) / 256);
                 if (int rc = launch_gemm_split(sg, s)) return rc;
             } else {

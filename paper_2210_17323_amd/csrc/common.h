@@ -126,22 +126,22 @@ struct GemmF32 {
 };
 int launch_gemm_f32(const GemmF32& g, hipStream_t s);
 
-// ---- float32 products of rank 1024 on the 16-bit matrix cores (gemm_split.hip) -----------------
-// C[256 tiles_m x 256 tiles_n] += alpha * A * B^T over K = SPLIT_K, with both operands given as "planes": the two
-// float16 pieces of every float32 element, scaled by a power of two per row, in the blocked layout the kernel copies
-// straight into LDS, and the rows' exponents behind them.
+// ---- float32 products of rank 1024 on the bf16 matrix cores (gemm_split.hip) -----------------
+// C[256 tiles_m x 256 tiles_n] += alpha * A * B^T over K = SPLIT_K, with both operands given as "planes": the three
+// bfloat16 pieces of every float32 element in the blocked layout the kernel copies straight into LDS.
 //   launch_split_rows: A [rows x SPLIT_K] float32, K contiguous        -> planes of ceil(rows / 256) panels
 //   launch_split_cols: B [SPLIT_K x cols] float32, columns contiguous  -> planes of ceil(cols / 256) panels (of B^T)
-// Both write split_planes_bytes(rows) bytes; rows past the operand's end are zeros.  A launch reads panels a_panel0 .. and
-// b_panel0 .. of the two plane buffers.
+// Both write split_planes_bytes(rows) bytes, the last 16 KB of which are zeros (split_zero_block); rows past the
+// operand's end are zeros.  A launch reads panels a_panel0 .. and b_panel0 .. of the two plane buffers.
 //   upper_square: C is square and only the tiles of its upper triangle are computed (diagonal tiles whole).
 //   skip_lower:   rectangular C at (crow0, ccol0) of a parent matrix: tiles entirely below the parent's diagonal are left out.
+// The six piece products kept leave a relative error of at most 2^-23 per product of two elements.
 constexpr int SPLIT_K = 1024;
 struct SplitGemm {
     const unsigned char* A_planes; int a_panel0;
     const unsigned char* B_planes; int b_panel0;
-    const int* A_exps;                  // each operand's exponents: split_exponents(planes, rows given to its split)
-    const int* B_exps;
+    const unsigned char* A_zero;        // each operand's block of zeros: split_zero_block(planes, rows given to its split)
+    const unsigned char* B_zero;
     float* C; int64_t ldc;
     float alpha;
     int tiles_m, tiles_n;
@@ -150,9 +150,7 @@ struct SplitGemm {
 };
 size_t split_planes_bytes(int64_t rows);
 bool split_pays(int64_t tiles);         // whether a launch of that many 256 x 256 tiles should take the split kernel
-inline int* split_exponents(unsigned char* planes, int64_t rows) {      // behind the planes: two of 256 x SPLIT_K float16 a panel
-    return reinterpret_cast<int*>(planes + ceil_div(rows < 1 ? 1 : rows, 256) * (2 * 256 * SPLIT_K * 2));
-}
+inline const unsigned char* split_zero_block(const unsigned char* planes, int64_t rows) { return planes + split_planes_bytes(rows) - 16384; }
 int launch_split_rows(const float* A, int64_t lda, int64_t rows, unsigned char* planes, hipStream_t s);
 int launch_split_cols(const float* B, int64_t ldb, int64_t cols, unsigned char* planes, hipStream_t s);
 int launch_gemm_split(const SplitGemm& g, hipStream_t s);

@@ -122,10 +122,10 @@ static bool factor_form_group_supported(int64_t group) { return group == 0 || gr
 // Trailing updates beyond an outer block are deferred and applied as one rank-1024 GEMM.
 static_assert(QOB == SPLIT_K, "the split products take exactly one outer block as K");
 
-// The deferred rank-1024 updates go through the split-operand kernel (float16 matrix cores, 256 x 256 tiles, one per
+// The deferred rank-1024 updates go through the split-operand kernel (bf16 matrix cores, 256 x 256 tiles, one per
 // workgroup) when columns come in whole tiles and the launch fills the chip well (split_pays).  `r` are the padded rows, so any
 // row count above 128 qualifies.  Measured against 64-bit products on operands of Alg. 1's kind, 96 to 1372 tiles: relative error
-// 2.2e-7 (split) against 5.7e-7 (float32 kernel); from 144 tiles on 160 us against 245, at 128 tiles 160 against 150.  Rows'
+// 1.9e-7 (split) against 5.7e-7 (float32 kernel); from 144 tiles on 193 us against 245, at 128 tiles 195 against 150.  Rows'
 // losses against a 64-bit walk, ragged row counts 2000 .. 16000 and 5120 .. 12288 columns, both forms: the same to 1 % with either.
 static bool split_shapes_ok(int64_t r, int64_t n) { return r >= 256 && r % 256 == 0 && n % 256 == 0 && n >= 2 * QOB; }
 
@@ -149,7 +149,7 @@ static QuantWs quant_ws_layout(int64_t r, int64_t n, int64_t group) {
     if (inner_groups) off += round_up((size_t)ceil_div(std::max<int64_t>(n, 1), QB) * QB * QB * sizeof(float), 256);
     l.rt = off;                                                                                       // ... and R with its column blocks scaled by them
     if (inner_groups) off += round_up((size_t)std::max<int64_t>(n, 1) * l.ldk * sizeof(float), 256);
-    // split products (gemm_split.hip): the pieces of an error panel, of the next outer block's rows of U and of all rows beyond
+    // split products (gemm_split.hip): the bf16 pieces of an error panel, of the next outer block's rows of U and of all rows beyond
     l.split = split_shapes_ok(l.rows, n);
     l.pa = l.pb = l.pr = off;
     if (l.split) {
@@ -320,7 +320,7 @@ static int alg1_run(bool rf, const void* W, int wdtype, int64_t ldw, int64_t r, 
             const bool split_strip = full && o2 - o1 == QOB && split_pays((rows / 256) * (QOB / 256));
             const bool split_rest = full && o2 < n && split_pays((rows / 256) * ((n - o2) / 256));
             SplitGemm sg{};
-            sg.A_planes = Pa; sg.A_exps = split_exponents(Pa, rows); sg.a_panel0 = 0;
+            sg.A_planes = Pa; sg.A_zero = split_zero_block(Pa, rows); sg.a_panel0 = 0;
             sg.ldc = lay.ldk; sg.alpha = alpha; sg.tiles_m = (int)(rows / 256);
             GemmF32 g{};
             g.A = E; g.lda = QOB; g.B = Bm + o0 * ldb + o1; g.ldb = ldb; g.C = Wk + o1; g.ldc = lay.ldk;
@@ -331,7 +331,7 @@ static int alg1_run(bool rf, const void* W, int wdtype, int64_t ldw, int64_t r, 
                 if (int rc = launch_split_rows(E, QOB, rows, Pa, s)) return rc;
                 if (int rc = launch_split_cols(Bm + o0 * ldb + o1, ldb, QOB, Pb, s)) return rc;
                 if (int rc = ts.mark(s, &quantized)) return rc;
-                sg.B_planes = Pb; sg.B_exps = split_exponents(Pb, QOB); sg.b_panel0 = 0;
+                sg.B_planes = Pb; sg.B_zero = split_zero_block(Pb, QOB); sg.b_panel0 = 0;
                 sg.C = Wk + o1; sg.tiles_n = QOB / 256;
                 if (int rc = launch_gemm_split(sg, s)) return rc;
             } else {
@@ -346,7 +346,7 @@ static int alg1_run(bool rf, const void* W, int wdtype, int64_t ldw, int64_t r, 
                 if (int rc = ts.wait(s2, quantized)) return rc;
                 if (split_rest) {
                     if (!split_strip) { if (int rc = launch_split_rows(E, QOB, rows, Pa, s2)) return rc; }
-                    sg.B_planes = Pr; sg.B_exps = split_exponents(Pr, n - o2); sg.b_panel0 = 0;
+                    sg.B_planes = Pr; sg.B_zero = split_zero_block(Pr, n - o2); sg.b_panel0 = 0;
                     sg.C = Wk + o2; sg.tiles_n = (int)((n - o2) / 256);
                     if (int rc = launch_gemm_split(sg, s2)) return rc;
                 } else {
