@@ -859,7 +859,8 @@ extern "C" int gptq_hessian_accumulate_token_major(float* H, int64_t ldh, const 
         const int64_t nt = ceil_div(n, tile), tiles = nt * (nt + 1) / 2;
         int64_t parts = tile == 256 ? syrk_plan(n, t).splits : std::max<int64_t>(1, 512 / tiles);
         parts = std::min(parts, ceil_div(t, 160));           // a part is a trip of the kernel's loop at least
-        const int64_t room = (int64_t)(ws_bytes / ((size_t)tiles * tile * tile * sizeof(float)));
+        // ... and has its partial tile in the size that is asked for: the parts are the same, and the bits, in whatever larger buffer is passed
+        const int64_t room = (int64_t)(syrk_token_major_ws_bytes(n, t) / ((size_t)tiles * tile * tile * sizeof(float)));
         return launch_syrk_tokens(H, ldh, X, xdtype == GPTQ_BF16, n, t, ldx, TokenPlan{tile, (int)std::max<int64_t>(1, std::min(parts, room))}, ws, s);
     }
     return xdtype == GPTQ_BF16 ? launch_syrk_dma<true>(g, ws, s, true) : launch_syrk_dma<false>(g, ws, s, true);

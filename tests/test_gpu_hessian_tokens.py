@@ -40,3 +40,20 @@ def test_hessian_of_tokens(dtype, n, t, extra):
     print(f"  rel_fro={err:.3e}", flush=True)
     assert err <= 1e-5
     assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("n, t", [(1000, 2048), (1000, 4096), (512, 4096), (1928, 8192)])
+def test_hessian_of_tokens_in_a_larger_workspace(n, t):
+    """The parts of the token range, and with them the bits, depend on the call's sizes alone: a program keeps one buffer for its longest
+    call."""
+    import paper_2210_17323_amd as g
+    print(f"hessian tokens n={n} t={t}, two workspaces", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(n + t)
+    X = torch.randn((t, n), generator=gen, device="cuda").half()
+    need = g.gptq_hessian_accumulate_token_major_workspace_bytes(n, t, X.dtype)
+    out = []
+    for nbytes in (need, need + (1 << 20), need + (256 << 20)):
+        H = torch.zeros((n, n), device="cuda")
+        g.gptq_hessian_accumulate_token_major(H, X, torch.full((nbytes,), 255, dtype=torch.uint8, device="cuda"))
+        out.append(torch.triu(H))
+    assert torch.equal(out[0], out[1]) and torch.equal(out[0], out[2])
