@@ -41,7 +41,7 @@ enum {
     GPTQ_OK = 0,
     GPTQ_ERR_INVALID_ARG = 1,      /* null pointer, bad size, bad alignment, bad enum                   */
     GPTQ_ERR_NOT_POSDEF = 2,       /* reported by gptq_check_info when a pivot was not positive          */
-    GPTQ_ERR_HIP = 3,              /* a HIP runtime call failed                                          */
+    GPTQ_ERR_HIP = 3,              /* a HIP runtime call failed, or work on the device did not finish    */
     GPTQ_ERR_UNSUPPORTED = 4,      /* valid request this build has no kernel for                         */
     GPTQ_ERR_WORKSPACE = 5         /* workspace pointer null or smaller than *_workspace_bytes            */
 };
@@ -125,8 +125,10 @@ GPTQ_API int gptq_hessian_symmetrize(float* H, int64_t ldh, int64_t n, void* str
  *             upper triangle, zeros strictly below the diagonal.
  *   ws        workspace of at least gptq_damp_cholesky_inverse_workspace_bytes(n) bytes, 256-byte aligned.
  *   info_dev  device int.  Set to 0, or to the 1-based index of a column whose pivot was not
- *             positive (then U is meaningless).  Read it after synchronising, e.g. through
- *             gptq_check_info.  percdamp < 0 is invalid; percdamp == 0 is allowed.
+ *             positive (then U is meaningless), or to a negative number where the device did not get to finish the
+ *             factorisation: its workgroups wait for one another, each for 10 s at most (then U is meaningless and nothing is
+ *             said about H).  Read it after synchronising, e.g. through gptq_check_info.  percdamp < 0 is invalid; percdamp == 0
+ *             is allowed.
  *   Computed as a Cholesky factorisation taken from the last column backwards, H + lambda I = R R^T with R
  *   upper triangular, followed by the triangular inverse U = R^-1 (the same matrix, by uniqueness of
  *   the Cholesky factor), all in float32; the rank-1024 updates that carry most of the flops multiply three-piece
@@ -161,8 +163,8 @@ GPTQ_API int64_t gptq_noalloc_max_n(void);
 GPTQ_API int gptq_damp_cholesky_inverse_noalloc(float* H_U, int64_t ld, int64_t n, float percdamp,
                                        int* info_dev, void* stream);
 
-/* Synchronises `stream`, reads *info_dev and returns GPTQ_OK or GPTQ_ERR_NOT_POSDEF
- * (the failing 1-based column index is stored in *host_info if host_info is not NULL). */
+/* Synchronises `stream`, reads *info_dev and returns GPTQ_OK, GPTQ_ERR_NOT_POSDEF (a 1-based column index) or
+ * GPTQ_ERR_HIP (a negative value); what was read is stored in *host_info if host_info is not NULL. */
 GPTQ_API int gptq_check_info(const int* info_dev, int* host_info, void* stream);
 
 /*

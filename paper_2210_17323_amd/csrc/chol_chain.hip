@@ -124,9 +124,11 @@ struct ChainArgs { float* H; int64_t ld; int64_t o0; int ow; float* dinv; float*
 __device__ __forceinline__ int pair_flag(int i, int k) { return k * (k - 1) / 2 + i; }
 __device__ __forceinline__ int diag_flag(int k) { return PAIR_FLAGS + k; }
 
-// A wait ends when the counter is there.  It ends after WAIT_TICKS of the 100 MHz clock too, with an error in *info, so that a
-// workgroup whose partner never starts leaves all the same; nothing more is waited for then.
+// A wait ends when the counter is there.  It ends after WAIT_TICKS of the 100 MHz clock too, with CHAIN_TIMED_OUT in *info, so that a
+// workgroup whose partner never starts leaves all the same; nothing more is waited for then.  The clock runs on while the process is
+// scheduled off, so what passes between two reads of the counter counts as POLL_TICKS at most, and the last thing before giving up is a read.
 constexpr uint64_t WAIT_TICKS = 1000000000ull;           // 10 s
+constexpr uint64_t POLL_TICKS = 100000ull;               // 1 ms
 struct Counters {
     const ChainArgs& g;
     int base;
@@ -138,13 +140,18 @@ struct Counters {
         int v = read(f);
         if (v >= want) return v;
         if (lost) return NP;
-        const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+        uint64_t waited = 0, last = __builtin_amdgcn_s_memrealtime();
         do {
             __builtin_amdgcn_s_sleep(1);
-            if (__builtin_amdgcn_s_memrealtime() - t0 > WAIT_TICKS) { lost = true; atomicCAS(g.info, 0, (int)g.o0 + 1); return NP; }
+            const uint64_t now = __builtin_amdgcn_s_memrealtime();
+            waited += min(now - last, POLL_TICKS);
+            last = now;
             v = read(f);
-        } while (v < want);
-        return v;
+            if (v >= want) return v;
+        } while (waited <= WAIT_TICKS);
+        lost = true;
+        atomicCAS(g.info, 0, CHAIN_TIMED_OUT);
+        return NP;
     }
     __device__ __forceinline__ void raise(int f, int count) const { __hip_atomic_store(g.flags + f, base + count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 };

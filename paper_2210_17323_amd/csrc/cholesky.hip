@@ -405,6 +405,7 @@ extern "C" int gptq_check_info(const int* info_dev, int* host_info, void* stream
     GPTQ_HIP_CHECK(hipMemcpyAsync(&v, info_dev, sizeof(int), hipMemcpyDeviceToHost, s));
     GPTQ_HIP_CHECK(hipStreamSynchronize(s));
     if (host_info) *host_info = v;
+    if (v < 0) return fail(GPTQ_ERR_HIP, "the factorisation did not finish on the device: workgroups that wait for one another gave up; nothing is said about the matrix");
     if (v != 0) return fail(GPTQ_ERR_NOT_POSDEF, "pivot of column %d (1-based) was not positive", v);
     return GPTQ_OK;
 }

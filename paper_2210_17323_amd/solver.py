@@ -35,7 +35,7 @@ def accumulate(H: torch.Tensor, X: torch.Tensor, chunk: int | None = None) -> No
 
 
 def cholesky_inverse(H: torch.Tensor, percdamp: float = 0.01, check: bool = True) -> torch.Tensor:
-    """In place H -> U; returns H (now U).  Raises GptqError if a pivot is not positive."""
+    """In place H -> U; returns H (now U).  Raises GptqError if a pivot is not positive or the device did not finish."""
     n = H.shape[0]
     ws = torch.empty(B.gptq_damp_cholesky_inverse_workspace_bytes(n), dtype=torch.uint8, device=H.device)
     info = torch.zeros(1, dtype=torch.int32, device=H.device)

@@ -113,3 +113,16 @@ def test_first_non_positive_pivot(n, column):
     with pytest.raises(g.GptqError) as ei:
         S.cholesky_factor(H, 0.0)
     assert ei.value.code == 2 and f"column {column + 1} " in str(ei.value)
+
+
+@pytest.mark.parametrize("value, code, word", [(0, 0, ""), (1, 2, "column 1 "), (1025, 2, "1025"), (-1, 3, "did not finish")])
+def test_what_the_status_of_a_factorisation_says(value, code, word):
+    """A pivot that is not positive is a statement about the matrix; a factorisation that the device did not get to finish is none."""
+    import paper_2210_17323_amd as g
+    info = torch.full((1,), value, dtype=torch.int32, device="cuda")
+    if code == 0:
+        assert g.gptq_check_info(info) == 0
+        return
+    with pytest.raises(g.GptqError) as ei:
+        g.gptq_check_info(info)
+    assert ei.value.code == code and word in str(ei.value) and (code == 2) == ("pivot" in str(ei.value))
