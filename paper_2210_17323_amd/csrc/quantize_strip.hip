@@ -349,6 +349,10 @@ __global__ __launch_bounds__(256) void pack_factor_kernel(const float* M, int64_
     }
 }
 
+// No memory access moves across, for the compiler: between a count in LDS and the data that it stands for.  (The hardware takes a
+// wavefront's LDS accesses in order, so it costs no instruction.)
+__device__ __forceinline__ void compiler_fence() { asm volatile("" ::: "memory"); }
+
 // A barrier that orders LDS accesses only: __syncthreads() would also wait for every global access in flight.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
@@ -428,6 +432,7 @@ __global__ __launch_bounds__(64 * STRIP_WAVES) void alg1_strip_kernel(StripArgs 
             request_quad<0, FORM>(s);
             [&]<int... T>(std::integer_sequence<int, T...>) {
                 ((walk_quads<FORM, 4 * T>(s, g.in_group, g.grid, nbk, go, std::make_integer_sequence<int, 4>{}),
+                  compiler_fence(),
                   *(volatile __attribute__((address_space(3))) int*)(&walked[wave]) = NT * b + T + 1), ...);        // behind the tile's errors: LDS takes a wavefront's stores in order
             }(std::make_integer_sequence<int, NT>{});
             lds_barrier();
@@ -640,7 +645,9 @@ __global__ __launch_bounds__(64 * STRIP_WAVES) void alg1_strip_kernel(StripArgs 
             int v = NT;
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt) v = min(v, *(volatile __attribute__((address_space(3))) int*)(&walked[rt]) - NT * b);
-            return __builtin_amdgcn_readfirstlane(v);
+            v = __builtin_amdgcn_readfirstlane(v);
+            compiler_fence();                           // the errors are read behind the count
+            return v;
         };
         lds_barrier();                                  // the walk of block b starts
         if (later > 0) {
