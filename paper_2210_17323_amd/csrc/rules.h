@@ -75,11 +75,11 @@ constexpr int64_t strip_block_columns(int64_t o0, int64_t o1, int i) { return o1
 // takes the microseconds below (mean of a first and a second outer block of 1024 columns, every CU with one strip; form 0 driven by
 // U, 1 by R, 2 by R with groups inside a block; the walk alone is 80).  The walk is as long for 16 rows as for 48 -- one wavefront per
 // 16 rows --, so few rows are spread thin over all CUs and many are taken 32 or 48 at a time.  Four row tiles do not fit in a CU's
-// registers and LDS: they are two strips of two, one behind the other, 250 / 259 / 261 a round in long launches.  The table takes
-// 3 % less for the first two forms: launches of 36865 rows and more, where three rounds of 64 rows and four of 48 are within 5 % of each other
-// (49152 rows: 749 against 713, 776 against 746, 782 against 767), go on taking 64.
+// registers and LDS: they are two strips of two, one behind the other, 250 / 259 / 261 a round in long launches.  Calls on 2048 columns
+// (two such launches and an update), us, four rounds of 48 rows / three of 64: 41216 rows 2326 / 2373, 2345 / 2433, 2524 / 2530; 45056 2365 / 2432,
+// 2382 / 2471, 2564 / 2569; 49152 2432 / 2483, 2442 / 2538, 2618 / 2618.
 constexpr int strip_row_tiles(int form, int64_t r) {
-    constexpr int us[3][4] = {{94, 132, 182, 242}, {95, 136, 191, 254}, {98, 136, 194, 259}};
+    constexpr int us[3][4] = {{94, 132, 182, 250}, {95, 136, 191, 259}, {98, 136, 194, 261}};
     int best = 1;
     int64_t best_us = 0;
     for (int rt = 1; rt <= 4; ++rt) {
