@@ -544,6 +544,8 @@ __global__ __launch_bounds__(256) void syrk_reduce_kernel(SyrkArgs g) {
 // count minimises a simple cost: rounds of 256 workgroups x (steps per part x 0.76 us + a fixed cost per work
 // item: ~8 us to start and to add a tile to H, ~30 us when a partial tile is written, read back and reduced).
 struct SyrkPlan { int splits; int64_t nsteps; size_t repack_bytes, partial_bytes; };
+constexpr int64_t REPACK_MAX_STEPS = 65535;                // steps of 32 tokens, a dimension of the repack's grid
+
 static SyrkPlan syrk_plan(int64_t n, int64_t t) {
     const int64_t nt = ceil_div(n, 256), tiles = nt * (nt + 1) / 2, steps = ceil_div(t, DK);
     int best = 1;
@@ -593,7 +595,7 @@ static int launch_syrk_dma(SyrkArgs g, void* ws, hipStream_t s, bool token_major
     const int64_t blocks = std::min<int64_t>(g.per_xcd, 32) * NXCD;   // persistent: one workgroup per CU walks its slots
     if (ws) {
         const int64_t rgroups = (int64_t)g.nt * 16, tgroups = ceil_div(g.nsteps, 16);
-        if (tgroups > 65535 || g.nsteps > 65535) return fail(GPTQ_ERR_UNSUPPORTED, "hessian: chunk too long for the repack grid (split the call)");
+        if (tgroups > 65535 || g.nsteps > REPACK_MAX_STEPS) return fail(GPTQ_ERR_UNSUPPORTED, "hessian: chunk too long for the repack grid (split the call)");
         if (token_major)
             hipLaunchKernelGGL(repack_token_major_kernel, dim3((unsigned)g.nt, (unsigned)g.nsteps), dim3(256), 0, s, g.X, g.ldx, g.n, g.t,
                                g.nsteps, static_cast<unsigned char*>(ws));
@@ -742,7 +744,7 @@ constexpr int64_t SYRK_DMA_MIN_N = 2048;
 constexpr int64_t SYRK_SMALL_WS_TOKENS = 32768;
 constexpr int64_t SYRK_SMALL_WS_MIN_N = 256;
 static bool syrk_small_with_ws(int64_t n, int64_t t) {
-    return n < SYRK_DMA_MIN_N && n >= SYRK_SMALL_WS_MIN_N && t > SYRK_SMALL_WS_TOKENS && syrk_plan(n, t).nsteps <= 65535;
+    return n < SYRK_DMA_MIN_N && n >= SYRK_SMALL_WS_MIN_N && t > SYRK_SMALL_WS_TOKENS && syrk_plan(n, t).nsteps <= REPACK_MAX_STEPS;
 }
 
 static size_t syrk_ws_bytes(int64_t n, int64_t t, int xdtype) {
@@ -855,7 +857,8 @@ extern "C" int gptq_hessian_accumulate_token_major(float* H, int64_t ldh, const 
     hipStream_t s = static_cast<hipStream_t>(stream);
     // Channels in whole 16 bytes are read in place where that pays and the channel-major call works without a workspace: one
     // with a workspace repacks to the same bytes as this call does, and gives the same bits.
-    if (const int tile = n % 8 == 0 && syrk_ws_bytes(n, t, xdtype) == 0 ? tokens_tile(n, t) : 0) {
+    // (Calls too long for the repack grid are refused whatever the channels, launch_syrk_dma says so.)
+    if (const int tile = n % 8 == 0 && syrk_plan(n, t).nsteps <= REPACK_MAX_STEPS && syrk_ws_bytes(n, t, xdtype) == 0 ? tokens_tile(n, t) : 0) {
         const int64_t nt = ceil_div(n, tile), tiles = nt * (nt + 1) / 2;
         int64_t parts = tile == 256 ? syrk_plan(n, t).splits : std::max<int64_t>(1, 512 / tiles);
         parts = std::min(parts, ceil_div(t, 160));           // a part is a trip of the kernel's loop at least

@@ -156,3 +156,12 @@ def test_quantize_workspace_of_ragged_columns():
         ld = (n + 3) // 4 * 4
         assert need(r, n) == up(rows * ld * 4) + 2 * up(rows * 4096) + packed, (r, n)
     assert need(300, 2048) > need(300, 2052)
+
+
+def test_token_major_calls_too_long_to_repack_are_refused_whatever_the_channels():
+    """65535 steps of 32 tokens are the longest call, also where the call would be read in place; nothing is enqueued."""
+    fake = 1 << 20
+    for n in (8, 64, 130, 248, 1000):
+        t = 65536 * 32
+        rc = g.lib().gptq_hessian_accumulate_token_major(fake, n, fake, 0, n, t, (n + 7) // 8 * 8, fake, 1 << 50, None)
+        assert rc == UNSUPPORTED and "split the call" in _err(), n
