@@ -8,9 +8,10 @@
 // step's first operands read across it.  Tokens past the last one are read from a block of zeros.
 // A tile of 128 x 128 (4 wavefronts of 64 x 64) is bound by LDS, one of 256 x 256 (128 x 128 each) by the matrix cores; few tiles get their
 // token range split into parts, whose partial tiles are added in the order of their ranges (the same bits from every call).
-// Against a repack and the repacked kernel, a call of float16 tokens, us: 256 channels x 16384 tokens 42 -> 24, 1000 x 16384 66 -> 38, 1536 x 32768 137 ->
-// 108, 2048 x 8192 76 -> 59, 3072 x 16384 210 -> 179, 4096 x 2048 108 -> 77, 4096 x 32768 671 -> 640, 8192 x 2048 311 -> 201.  Where the repack is little beside the products the
-// repacked kernel's 16-byte reads win (4096 x 262144: 4839 against 4906, 12288 x 16384: 2431 against 2500); syrk_tokens_plan has the line.
+// Against a repack and the repacked kernel, a call of float16 tokens, us: 256 channels x 16384 tokens 38 -> 23, 1000 x 16400 64 -> 37, 1536 x 32768 138 ->
+// 105, 2000 x 32000 196 -> 159, 2048 x 1880 75 -> 27, 4096 x 2048 107 -> 77, 4096 x 6500 220 -> 184, 5632 x 8192 298 -> 292, 6144 x 2048 191 -> 121.
+// Where the repack is little beside the products the repacked kernel's 16-byte reads win (6144 channels x 16384: 750 against 708 and 901);
+// tokens_tile in rules.h has the line, and which calls may come here.
 #include "hessian_tokens.h"
 #include "syrk_tiles.h"
 

@@ -24,22 +24,22 @@ constexpr bool hessian_f32_small_tiles(int64_t n, int64_t t) {
 }
 
 // ---- Hessian of [tokens, channels] activations: the tile of the kernel that reads them in place, 0: repacked ----
+// For calls that the channel-major call makes without a workspace: one with a workspace repacks, to the same bytes as the token-major
+// call does, and the two give the same bits.  That leaves fewer than 256 channels, up to 32768 tokens of fewer than 2048, and beyond, to 6144
+// channels, ranges too short to be worth splitting (1889 tokens of 2048 to 3072 channels, 7073 of 4096, 15000 of 4608).
 // Measured, us, in place with tiles of 128 (512 / tiles parts, at least one) / of 256 (the repacked kernel's parts) / repacked, float16:
-//   2048 tokens: 1000 channels 19 / 29 / 42, 2048 29 / 38 / 53, 4096 77 / 86 / 108, 8192 201 / 298 / 311, 12288 443 / 538 / 611
-//   4096:        2304 46 / 51 / 64, 3072 69 / 71 / 81, 4096 124 / 134 / 164, 6144 203 / 282 / 288, 12288 767 / 814 / 860
-//   8192:        1536 39 / 49 / 69, 2304 74 / 72 / 88, 3072 124 / 106 / 125, 4096 223 / 212 / 235, 6144 368 / 485 / 451, 8192 648 / 778 / 760, 12288 1421 / 1359 / 1386
-//   16384:       1664 68 / 79 / 96, 2048 99 / 95 / 114, 4096 419 / 347 / 390, 6144 708 / 901 / 750, 8192 1254 / 1424 / 1215
-//   32768:       1800 155 / 159 / 192, 2048 183 / 163 / 195, 3072 447 / 332 / 376, 4096 832 / 640 / 671
-//   262144:      256 53 / 69 / 118, 1000 439 / 433 / 506, 1536 828 / 820 / 890, 2048 1526 / 1414 / 1390, 4096 - / 4906 / 4839
+//   2048 tokens: 1000 channels 19 / 29 / 42, 4096 77 / 86 / 108
+//   4096:        4096 124 / 134 / 164, 6144 203 / 282 / 288
+//   8192:        1536 39 / 49 / 69, 6144 368 / 485 / 451 (whole calls in place / repacked: 4608 226 / 272, 5120 271 / 285, 5632 292 / 298)
+//   16384:       1664 68 / 79 / 96, 6144 708 / 901 / 750
+//   32768:       1800 155 / 159 / 192
+//   262144:      256 53 / 69 / 118
 // Few channels always gain, tiles of 128 as long as they fill the chip in parts; in short calls the repack is most of the work
-// whatever the channels; in between the larger tiles up to 4096 channels.  Calls whose channel-major form has a workspace -- beyond 32768
-// tokens, 6144 channels, or wherever the token range is worth splitting from 2048 channels on -- are repacked whatever this says (hessian.hip).
+// whatever the channels; in between the larger tiles up to 4096 channels (8192 tokens of 2304 74 / 72 / 88, 3072 124 / 106 / 125).
 constexpr int tokens_tile(int64_t n, int64_t t) {
-    if (n <= 1536) return 128;
-    if (t > 32768) return 0;
     if (n <= 1920) return 128;
     if (n <= 4096) return t <= 6144 ? 128 : 256;
-    return t <= (n <= 8192 ? 8192 : 4096) ? 128 : 0;
+    return t <= 8192 ? 128 : 0;
 }
 
 // ---- float32 products with rows in whole tiles of 128 and K in whole steps: 128 x 128 tiles, or 256 rows (256 x 128 and larger) ----

@@ -1,5 +1,6 @@
 """GPU parity of the Hessian of [tokens, channels] activations read in place: tiles of 128 and 256 channels, steps of 32 and trips of
-160 tokens, parts of the token range, chains of five trips, and the calls beside them that are repacked.  Bar: relative Frobenius
+160 tokens, parts of the token range, chains of five trips, and the calls beside them that are repacked (tests/test_rules.py holds the
+cases to the route they name).  Bar: relative Frobenius
 error 1e-5 as everywhere against float64, and the same bits from the same call."""
 import pytest
 import torch
@@ -7,17 +8,19 @@ import torch
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # dtype, n, t, extra elements of a row's pitch
-    (torch.float16, 8, 1, 0), (torch.bfloat16, 120, 31, 8), (torch.float16, 128, 32, 0), (torch.bfloat16, 136, 33, 16),
-    (torch.float16, 256, 159, 0), (torch.bfloat16, 264, 160, 0), (torch.float16, 392, 161, 8), (torch.bfloat16, 1000, 805, 0),
-    (torch.float16, 640, 16400, 0), (torch.float16, 1536, 33000, 0), (torch.bfloat16, 1544, 3000, 0), (torch.float16, 1920, 6200, 0),
-    (torch.bfloat16, 1928, 6144, 0), (torch.float16, 1928, 6145, 0), (torch.float16, 2560, 6500, 8), (torch.bfloat16, 4096, 6241, 0),      # 128 | 256 wide tiles
-    (torch.float16, 4104, 1030, 0), (torch.bfloat16, 8200, 170, 0), (torch.float16, 4104, 8200, 0),                                          # one part | repacked
-    (torch.float16, 1001, 300, 7), (torch.bfloat16, 130, 4000, 6),                                                                           # broken 16 bytes: repacked
+    # dtype, n, t, extra elements of a row's pitch, the tile of the kernel that reads the call in place (0: repacked)
+    (torch.float16, 8, 1, 0, 128), (torch.bfloat16, 120, 31, 8, 128), (torch.float16, 128, 32, 0, 128), (torch.bfloat16, 136, 33, 16, 128),
+    (torch.float16, 256, 159, 0, 128), (torch.bfloat16, 264, 160, 0, 128), (torch.float16, 392, 161, 8, 128), (torch.bfloat16, 1000, 805, 0, 128),
+    (torch.float16, 640, 16400, 0, 128), (torch.float16, 248, 33000, 0, 128), (torch.float16, 1536, 32768, 0, 128), (torch.bfloat16, 1544, 3000, 0, 128),
+    (torch.float16, 1920, 6200, 0, 128), (torch.bfloat16, 1928, 6144, 0, 128), (torch.float16, 1928, 6145, 0, 256), (torch.bfloat16, 2040, 32760, 8, 256),
+    (torch.bfloat16, 4096, 6241, 0, 256), (torch.float16, 2560, 1800, 8, 128), (torch.float16, 4104, 1030, 0, 128), (torch.bfloat16, 5632, 8192, 0, 128),      # one part
+    (torch.float16, 1536, 33000, 0, 0), (torch.float16, 2560, 6500, 8, 0), (torch.bfloat16, 8200, 170, 0, 0), (torch.float16, 4104, 8200, 0, 0),           # the channel-major call repacks
+    (torch.float16, 5632, 8200, 0, 0),                                                                                                                    # the repack is little
+    (torch.float16, 1001, 300, 7, 0), (torch.bfloat16, 130, 4000, 6, 0),                                                                                  # broken 16 bytes
 ]
 
 
-@pytest.mark.parametrize("dtype,n,t,extra", CASES)
+@pytest.mark.parametrize("dtype,n,t,extra", [c[:4] for c in CASES])
 def test_hessian_of_tokens(dtype, n, t, extra):
     import paper_2210_17323_amd as g
     print(f"hessian tokens {dtype} n={n} t={t} pitch +{extra}", flush=True)

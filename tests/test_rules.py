@@ -17,6 +17,7 @@ int row_tiles(int form, int64_t r) { return strip_row_tiles(form, r); }
 int product_small(int64_t m, int64_t n) { return product_small_tiles(m, n); }
 int triangle_guarded_(int64_t m, int64_t k) { return triangle_guarded(m, k); }
 int f32_small_tiles(int64_t n, int64_t t) { return hessian_f32_small_tiles(n, t); }
+int tokens_tile_(int64_t n, int64_t t) { return tokens_tile(n, t); }
 }
 """
 
@@ -33,7 +34,7 @@ def rules(tmp_path_factory):
     L.block_columns.restype, L.block_columns.argtypes = i64, [i64, i64, ctypes.c_int]
     L.row_tiles.argtypes = [ctypes.c_int, i64]
     L.f32_small_tiles.argtypes = [i64, i64]
-    L.product_small.argtypes = L.triangle_guarded_.argtypes = [i64, i64]
+    L.product_small.argtypes = L.triangle_guarded_.argtypes = L.tokens_tile_.argtypes = [i64, i64]
     return L
 
 
@@ -114,3 +115,14 @@ def test_strip_height_covers_the_rows_in_the_fewest_rounds_that_pay(rules, form)
     # many rounds: four rounds of 48 rows beat three of 64, which are strips of 32 one behind the other (a call on 2048 columns, driven by
     # U / R / R with groups: 2432 against 2483 us, 2442 against 2538, 2618 against 2618)
     assert rules.row_tiles(form, 49152) == 3 and rules.row_tiles(form, 41216) == 3
+
+
+def test_token_major_cases_take_the_route_they_name(rules):
+    """A call is read in place where its channels come in whole 16 bytes, the channel-major call has no workspace and the rule names a tile."""
+    import paper_2210_17323_amd as g
+    from test_gpu_hessian_tokens import CASES
+    for dtype, n, t, _, tile in CASES:
+        in_place = n % 8 == 0 and g.gptq_hessian_accumulate_workspace_bytes(n, t, dtype) == 0
+        assert (rules.tokens_tile_(n, t) if in_place else 0) == tile, (n, t)
+    # every line of the rule is reached
+    assert {c[4] for c in CASES} == {0, 128, 256}
