@@ -152,12 +152,12 @@ static int chol_run(float* H, int64_t ld, int64_t n, float percdamp, void* ws, i
     GPTQ_LAUNCH_CHECK();
 
     // C (+)= alpha A op(B) on stream st
-    struct Opt { bool nk = false, overwrite = false, upper = false, atri = false, btri = false; int64_t crow0 = 0, ccol0 = 0; };
+    struct Opt { bool nk = false, overwrite = false, upper = false, atri = false, btri = false; };
     auto gemm_on = [&](hipStream_t st, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int64_t ldc,
                        int64_t M, int64_t N, int64_t K, float alpha, const Opt& o) -> int {
         GemmF32 g{};
         g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.C = C; g.ldc = ldc; g.M = M; g.N = N; g.K = K; g.alpha = alpha;
-        g.b_is_nk = o.nk; g.overwrite = o.overwrite; g.upper_only = o.upper; g.crow0 = o.crow0; g.ccol0 = o.ccol0;
+        g.b_is_nk = o.nk; g.overwrite = o.overwrite; g.upper_only = o.upper;
         g.a_upper_tri = o.atri; g.b_upper_tri = o.btri;
         return launch_gemm_f32(g, st);
     };

@@ -134,7 +134,6 @@ int launch_gemm_f32(const GemmF32& g, hipStream_t s);
 // Both write split_planes_bytes(rows) bytes, the last 16 KB of which are zeros (split_zero_block); rows past the
 // operand's end are zeros.  A launch reads panels a_panel0 .. and b_panel0 .. of the two plane buffers.
 //   upper_square: C is square and only the tiles of its upper triangle are computed (diagonal tiles whole).
-//   skip_lower:   rectangular C at (crow0, ccol0) of a parent matrix: tiles entirely below the parent's diagonal are left out.
 // The six piece products kept leave a relative error of at most 2^-23 per product of two elements.
 constexpr int SPLIT_K = 1024;
 struct SplitGemm {
@@ -146,7 +145,6 @@ struct SplitGemm {
     float alpha;
     int tiles_m, tiles_n;
     bool upper_square;
-    bool skip_lower; int64_t crow0, ccol0;
 };
 size_t split_planes_bytes(int64_t rows);
 bool split_pays(int64_t tiles);         // whether a launch of that many 256 x 256 tiles should take the split kernel
