@@ -206,6 +206,10 @@ __global__ __launch_bounds__(512) void chol_chain_kernel(ChainArgs g) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, kq = lane >> 4;
     const int nb = (g.ow + DB - 1) / DB;
+    // Panels whose products are subtracted at once, not summed with those of the later ones: up to the first one of the outer block that is not past
+    // its end.  Where the channels have much in common (inputs behind a ReLU) its first column carries that, and a sum that
+    // began with it would be rounded at its size ever after, not at the size of what it leaves.  The column comes in the last of the panel's products.
+    auto first_panel = [&](int q) { return q == nb - 1 ? (DB - min(DB, g.ow - DB * q)) / PB : -1; };
     // workgroup -> tiles: column by column from the last, the diagonal tile first, then upwards
     int k = nb - 1, m = (int)blockIdx.x;
     while (m > k) { m -= k + 1; --k; }
@@ -266,7 +270,9 @@ __global__ __launch_bounds__(512) void chol_chain_kernel(ChainArgs g) {
             for (int j = 0; j < NP; ++j) C[j] -= acc[j];
         }
         barrier_lds();
-        // P = C R_kk^-T, column block by column block: P_p^T = L_pp^-1 (C_p^T - sum), then L_jp P_p^T onto the sums of the later ones
+        // P = C R_kk^-T, column block by column block: P_p^T = L_pp^-1 (C_p^T - sum), then L_jp P_p^T onto the sums of the later ones.
+        // (What the first panels leave goes to C at once, first_panel.)
+        const int first = first_panel(k);
         PanelStream L{counters, diag_flag(k), g.panel + (int64_t)(DB * k + (tid >> 2)) * OBW + DB * k + (tid & 3) * 4, PB, pa, &slot};
         floatx4 S[NP];
 #pragma unroll
@@ -287,7 +293,11 @@ __global__ __launch_bounds__(512) void chol_chain_kernel(ChainArgs g) {
             for (int j = p + 1; j < NP; ++j) {
                 const floatx4 a = *reinterpret_cast<const floatx4*>(&lp[(PB * j + l16) * PP + 4 * kq]);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) S[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], cur[e], S[j], 0, 0, 0);
+                for (int e = 3; e >= 0; --e) S[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], cur[e], S[j], 0, 0, 0);
+            }
+            if (p <= first) {
+#pragma unroll
+                for (int j = p + 1; j < NP; ++j) { C[j] -= S[j]; S[j] = floatx4{0.f, 0.f, 0.f, 0.f}; }
             }
         };
         [&]<int... P>(std::integer_sequence<int, P...>) { (solve(std::integral_constant<int, P>{}), ...); }(std::make_integer_sequence<int, NP>{});
@@ -478,9 +488,10 @@ __global__ __launch_bounds__(512) void chol_chain_kernel(ChainArgs g) {
         const floatx4 a = *reinterpret_cast<const floatx4*>(&pp[(DB - 1 - (PB * ci[s] + l16)) * PP + 4 * kq]);
         const floatx4 b = *reinterpret_cast<const floatx4*>(&pp[(DB - 1 - (PB * cc[s] + l16)) * PP + 4 * kq]);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sum[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], sum[s], 0, 0, 0);
+        for (int e = 3; e >= 0; --e) sum[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], sum[s], 0, 0, 0);
     };
     if (k + 1 < nb) {
+        const int first = first_panel(k + 1);
         PanelStream S{counters, pair_flag(k, k + 1), g.panel + (int64_t)(DB * k + (tid >> 2)) * OBW + DB * (k + 1) + DB - PB + (tid & 3) * 4, -PB, pa, &slot};
         auto take = [&](auto P) {
             constexpr int p = decltype(P)::value;
@@ -489,6 +500,10 @@ __global__ __launch_bounds__(512) void chol_chain_kernel(ChainArgs g) {
 #pragma unroll
                 for (int s = 0; s < CT; ++s)
                     if (p + 2 < NP || (WORKERS * s < tiles_before(1) && cc[s] == 0)) add_tile(s, pp);
+                if (p <= first) {
+#pragma unroll
+                    for (int s = 0; s < CT; ++s) { ch[s] -= sum[s]; sum[s] = floatx4{0.f, 0.f, 0.f, 0.f}; }
+                }
             }
         };
         [&]<int... P>(std::integer_sequence<int, P...>) { (take(std::integral_constant<int, P>{}), ...); }(std::make_integer_sequence<int, NP>{});

@@ -126,3 +126,25 @@ def test_what_the_status_of_a_factorisation_says(value, code, word):
     with pytest.raises(g.GptqError) as ei:
         g.gptq_check_info(info)
     assert ei.value.code == code and word in str(ei.value) and (code == 2) == ("pivot" in str(ei.value))
+
+
+@pytest.mark.parametrize("n", [256, 384, 1000, 1024, 2100])
+@pytest.mark.parametrize("inverse", [False, True])
+def test_factor_of_channels_with_much_in_common(n, inverse):
+    """Positive inputs (a layer behind a ReLU): the first column of the factorisation carries what the channels share, and every element loses most of itself to it.
+    Rounded at the size of what is left, the factor is 0.9e-6 to 1.5e-6 from 64 bits and its inverse 2.2e-6 to 3.8e-6; with sums that begin with that
+    column 2.4e-6 to 3.3e-6 and 6.0e-6 to 8.7e-6 (256 to 1024 channels)."""
+    from paper_2210_17323_amd import solver as S
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    X = torch.randn((n, 2 * n), generator=gen, device="cuda").abs()
+    H = X @ X.T
+    H = torch.triu(H) + torch.triu(H, 1).T
+    Hd = H.double().cpu()
+    Hd.diagonal().add_(0.01 * float(Hd.diagonal().mean()))
+    want = torch.linalg.cholesky(Hd.flip(0, 1)).flip(0, 1)
+    if inverse:
+        want = torch.linalg.inv(want)
+    got = (S.cholesky_inverse if inverse else S.cholesky_factor)(H, 0.01).double().cpu()
+    err = float((got - want).norm() / want.norm())
+    print(f"positive inputs n={n} inverse={inverse}: rel_fro {err:.3e}", flush=True)
+    assert err <= (5.5e-6 if inverse else 2.1e-6)
