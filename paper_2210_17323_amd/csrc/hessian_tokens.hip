@@ -225,14 +225,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WT == 4 ? 1
         }
 }
 
-// H tile += 2 (part 0 + part 1 + ..), in the order of the token ranges, eight at a time and then the eights.  A thread takes four columns.
+// H tile += 2 (part 0 + part 1 + ..), in the order of the token ranges, eight at a time, then eight of these, then the sixty-fours: few channels have up
+// to 512 parts, and 64 sums of eight one behind the other round each at the size of all before it.  A thread takes four columns.
 template <int TILE>
 __global__ __launch_bounds__(256) void tokens_reduce_kernel(TokenArgs g) {
     int bi, bj;
     syrk_tile_of(g.nt, (int64_t)blockIdx.x, bi, bj);
     const int e = ((int)blockIdx.y * 256 + (int)threadIdx.x) * 4, rt = e / TILE, ct = e % TILE;
     const float4* p = reinterpret_cast<const float4*>(g.P + (int64_t)blockIdx.x * g.parts * (TILE * TILE) + e);
-    float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 sum = make_float4(0.f, 0.f, 0.f, 0.f), eights = sum;
     for (int q0 = 0; q0 < g.parts; q0 += 8) {
         float4 v[8], eight = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
@@ -241,7 +242,11 @@ __global__ __launch_bounds__(256) void tokens_reduce_kernel(TokenArgs g) {
 #pragma unroll
         for (int q = 0; q < 8; ++q)
             if (q0 + q < g.parts) { eight.x += v[q].x; eight.y += v[q].y; eight.z += v[q].z; eight.w += v[q].w; }
-        sum.x += eight.x; sum.y += eight.y; sum.z += eight.z; sum.w += eight.w;
+        eights.x += eight.x; eights.y += eight.y; eights.z += eight.z; eights.w += eight.w;
+        if ((q0 & 56) == 56 || q0 + 8 >= g.parts) {
+            sum.x += eights.x; sum.y += eights.y; sum.z += eights.z; sum.w += eights.w;
+            eights = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
     }
     const int64_t row = (int64_t)bi * TILE + rt, col = (int64_t)bj * TILE + ct;
     if (row >= g.n) return;
