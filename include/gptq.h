@@ -20,7 +20,7 @@
  *     Arguments are validated on the host before any launch: GPTQ_ERR_INVALID_ARG, GPTQ_ERR_UNSUPPORTED and
  *     GPTQ_ERR_WORKSPACE mean that nothing has been enqueued.  GPTQ_ERR_HIP (a launch or runtime call failed
  *     part way through) may leave earlier kernels of the call enqueued: the outputs are then undefined, but
- *     all of that work is ordered on `stream` (the library's helper stream is joined back on every return
+ *     all of that work is ordered on `stream` (the library's helper streams are joined back on every return
  *     path), so synchronising `stream` is enough before the buffers are reused or freed.  No C++ exception
  *     crosses this boundary.
  *   - Not re-entrant on the same workspace: two calls sharing a workspace must be on the same stream.
@@ -53,7 +53,7 @@ GPTQ_API int gptq_version(void);
 GPTQ_API const char* gptq_last_error(void);
 
 /*
- * The only state the library keeps between calls: two helper streams (default priority, non-blocking) and 32 events per
+ * The only state the library keeps between calls: three helper streams (default priority, non-blocking) and 32 events per
  * host thread and device, created by the first call of gptq_damp_cholesky* / gptq_quantize_layer* on that thread and
  * device and used by the later ones (two caller streams of one thread therefore share them: their calls are correct
  * but do not overlap each other's helper work).  gptq_release_thread_resources waits for the calling thread's helper
