@@ -17,7 +17,7 @@
 // which on this chip take the vector units' cycles: 40 each), 9.9 us a block; with more rows a CU's vector units, which walkers
 // and updaters share.  An outer block takes 95 / 136 / 191 us with 16 / 32 / 48 rows per workgroup (driven by R; strip_row_tiles has all
 // forms).  With updates and walk one behind the other and a multiply-add per lane and column in the walk it took 144 / 181 / 232: Alg. 1 on a
-// 4096 x 4096 layer 1.07 -> 0.86 ms, 3000 x 5120 in groups of 1024 1.48 -> 1.21 ms, 14336 x 14336 in groups of 128 20.9 -> 20.2 ms.
+// 4096 x 4096 layer 1.07 -> 0.84 ms, 3000 x 5120 in groups of 1024 1.48 -> 1.17 ms, 14336 x 14336 in groups of 128 20.9 -> 20.2 ms.
 #include "quantize_common.h"
 
 #include <utility>
