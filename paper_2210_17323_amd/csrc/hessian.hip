@@ -23,6 +23,7 @@ namespace gptq {
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int HK = 64;          // token step (halves)
 constexpr int NXCD = 8;
@@ -61,6 +62,22 @@ __device__ __forceinline__ floatx16 mfma16(uint4 a, uint4 b, floatx16 c) {
     } else {
         return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, a), __builtin_bit_cast(halfx8, b), c, 0, 0, 0);
     }
+}
+
+// c += a b, the accumulator in place.  As a statement of its own and not the builtin: with 256 accumulator registers in groups of
+// four the compiler gives the builtin's result another place than its addend and copies and spills between them.  What it
+// cannot see is that this is a matrix-core instruction: the callers see to it that no vector instruction writes an operand
+// right before, and wait before the first read of an accumulator (mfma_settle).
+template <bool IS_BF16>
+__device__ __forceinline__ void mfma16x16_acc(floatx4& c, uint4 a, uint4 b) {
+    if constexpr (IS_BF16)
+        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(__builtin_bit_cast(bf16x8, a)), "v"(__builtin_bit_cast(bf16x8, b)));
+    else
+        asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(c) : "v"(__builtin_bit_cast(halfx8, a)), "v"(__builtin_bit_cast(halfx8, b)));
+}
+// The last results of a loop of these, four at a time, before something else reads them: 16 wait states and more.
+__device__ __forceinline__ void mfma_settle(floatx4& a, floatx4& b, floatx4& c, floatx4& d) {
+    asm volatile("s_nop 15\n\ts_nop 3" : "+a"(a), "+a"(b), "+a"(c), "+a"(d));
 }
 
 __device__ __forceinline__ uint4 load8h_guard(const uint16_t* p, int64_t valid) {
@@ -319,9 +336,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         return;
     }
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
-    const int l32 = lane & 31, lhi = lane >> 5;
+    const int l16 = lane & 15, lq = lane >> 4;
 
     // this lane's part of the 4 + 4 copies of a step: row (wave*4 + i)*16 + lane/4 of each panel, chunk
     // (lane%4) ^ ((lane/16)%4).  Rows past n are clamped: they only feed outputs that are never stored.
@@ -337,81 +354,60 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         syrk_tile_of(g.nt, L, bi, bj);
         r0 = (int64_t)bi * BT; c0 = (int64_t)bj * BT;
         if (BLOCKED) {
-            blkA = g.Xb + ((int64_t)bi * g.nsteps + q * g.spp) * 16384 + wave * 4096 + lane * 16;
-            blkB = g.Xb + ((int64_t)bj * g.nsteps + q * g.spp) * 16384 + wave * 4096 + lane * 16;
+            blkA = g.Xb + ((int64_t)bi * g.nsteps + q * g.spp) * 16384 + wave * 4096;
+            blkB = g.Xb + ((int64_t)bj * g.nsteps + q * g.spp) * 16384 + wave * 4096;
             part = g.P ? g.P + item * (int64_t)(BT * BT) : nullptr;
         }
     };
-    auto issue_copies = [&](unsigned char* stage, int64_t k0) {
-        unsigned char* base = stage + wave * 4 * 1024;
+    auto issue_copy = [&](unsigned char* stage, int64_t k0, int q) {       // copy q of 8: even ones of A's panel, odd ones of B's
+        const int i = q >> 1;
+        const unsigned char* src;
         if (BLOCKED) {
-            const int64_t off = (k0 / DK) * 16384;     // this step's block inside the panel
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(blkA + off + i * 1024),
-                                                 (__attribute__((address_space(3))) void*)(base + i * 1024), 16, 0, 0);
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(blkB + off + i * 1024),
-                                                 (__attribute__((address_space(3))) void*)(base + PANEL + i * 1024), 16, 0, 0);
-            }
-            return;
+            src = ((q & 1) ? blkB : blkA) + (k0 / DK) * 16384 + i * 1024 + lane * 16;  // this step's block inside the panel
+        } else {
+            const int row = (wave * 4 + i) * 16 + lrow;
+            src = reinterpret_cast<const unsigned char*>(xcol + min(((q & 1) ? c0 : r0) + row, g.n - 1) * g.ldx + k0);
         }
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                         (__attribute__((address_space(3))) void*)(stage + (q & 1) * PANEL + (wave * 4 + i) * 1024), 16, 0, 0);
+    };
+    auto issue_copies = [&](unsigned char* stage, int64_t k0) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) issue_copy(stage, k0, q);
+    };
+
+    floatx4 acc[8][8];
+
+    // This lane's operand rows are wm*128 + s*16 + lane%16 (A) and wn*128 + u*16 + lane%16 (B), its chunk of a row's four
+    // lane/16: the swizzle term (row / 4) % 4 is (lane / 4) % 4 for all of them, and s / u only add a constant 1024 bytes.
+    const int rowA = (wm * 128 + l16) * 64 + ((lq ^ ((l16 >> 2) & 3)) << 4), rowB = PANEL + (wn * 128 + l16) * 64 + ((lq ^ ((l16 >> 2) & 3)) << 4);
+    // One 32-token step out of `cur`, a quarter of the tile (64 x 64) at a time: rows and columns each in a first and a second half.
+    // The fragments of both first halves are in fa / fb already; a quarter fetches what a later one wants into the registers that
+    // are free by then -- the second rows, the second columns, then both first halves of the NEXT step (`nxt`, whose copies have
+    // landed) --, eight MFMAs before they are read, so that no MFMA waits for an LDS round trip, not even right after the barrier.
+    // The step's 8 copies are spread over its MFMAs as well: with one wavefront per SIMD nothing else can
+    // issue while a copy instruction is being accepted (tens of cycles each), so copies issued back to back idle the matrix core.
+    uint4 fa[8], fb[8];
+    auto fetchA = [&](const unsigned char* st, int s) { fa[s] = *reinterpret_cast<const uint4*>(st + rowA + s * 1024); };
+    auto fetchB = [&](const unsigned char* st, int u) { fb[u] = *reinterpret_cast<const uint4*>(st + rowB + u * 1024); };
+    auto quarter = [&](int hs, int hu, auto&& fetch, auto&& copy) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int row = (wave * 4 + i) * 16 + lrow;
-            const uint16_t* sa = xcol + min(r0 + row, g.n - 1) * g.ldx + k0;
-            const uint16_t* sb = xcol + min(c0 + row, g.n - 1) * g.ldx + k0;
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)sa,
-                                             (__attribute__((address_space(3))) void*)(base + i * 1024), 16, 0, 0);
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)sb,
-                                             (__attribute__((address_space(3))) void*)(base + PANEL + i * 1024), 16, 0, 0);
+            const int s = 4 * hs + i;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {                // back and forth: one operand changes at a time
+                const int u = 4 * hu + ((i & 1) ? 3 - j : j);
+                mfma16x16_acc<IS_BF16>(acc[s][u], fa[s], fb[u]);
+                if (i < 2 && (j & 1)) fetch(2 * i + (j >> 1));
+            }
+            if (i >= 2) copy(i - 2);
         }
     };
-
-    floatx16 acc[4][4];
-
-    // This lane's operand rows are wm*128 + s*32 + lane%32 (A) and wn*128 + u*32 + lane%32 (B): the swizzle
-    // term (row / 4) % 4 is (lane / 4) % 4 for all of them, and s / u only add a constant 2048 bytes.
-    const int rowA = (wm * 128 + l32) * 64, rowB = PANEL + (wn * 128 + l32) * 64;
-    const int co0 = (lhi ^ ((l32 >> 2) & 3)) << 4;      // chunk offset of sub-step 0; sub-step 1 flips bit 5
-    // One 32-token step out of `cur`.  The operand fragments of its first 16 tokens are already in fa[0]/fb[0]
-    // (fetched at the end of the previous step); those of the second 16 tokens are fetched from LDS while the
-    // first 16 MFMAs run, and the first fragments of the NEXT step (`nxt`, whose copies have landed) while
-    // the second 16 run -- so no MFMA ever waits for an LDS round trip, not even right after the barrier.
-    // The step's 8 copies are spread over its MFMAs as well: with one wavefront per SIMD nothing else can
-    // issue while a copy instruction is being accepted (tens of cycles each), so copies issued back to back
-    // idle the matrix core, while one copy every four MFMAs hides behind the MFMA in flight.
-    uint4 fa[2][4], fb[2][4];
-    auto fetch = [&](const unsigned char* st, int kk) {
-        const int co = co0 ^ (kk << 5);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            fa[kk][s] = *reinterpret_cast<const uint4*>(st + rowA + co + s * 2048);
-            fb[kk][s] = *reinterpret_cast<const uint4*>(st + rowB + co + s * 2048);
-        }
-    };
-    auto multiply = [&](const unsigned char* cur, const unsigned char* nxt) {
-        fetch(cur, 1);
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int u = 0; u < 4; ++u) acc[s][u] = mfma16<IS_BF16>(fa[0][s], fb[0][u], acc[s][u]);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);   // 2 MFMA
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // 1 LDS read
-            if (i & 1) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);   // 1 of this step's 8 copies
-        }
-        fetch(nxt, 0);
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int u = 0; u < 4; ++u) acc[s][u] = mfma16<IS_BF16>(fa[1][s], fb[1][u], acc[s][u]);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            if (i & 1) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
-        }
+    auto multiply = [&](const unsigned char* cur, const unsigned char* nxt, auto&& copy) {
+        quarter(0, 0, [&](int i) { fetchA(cur, 4 + i); }, [&](int i) { copy(i); });
+        quarter(1, 0, [&](int i) { fetchB(cur, 4 + i); }, [&](int i) { copy(2 + i); });
+        quarter(0, 1, [&](int i) { fetchB(nxt, i); }, [&](int i) { copy(4 + i); });
+        quarter(1, 1, [&](int i) { fetchA(nxt, i); }, [&](int i) { copy(6 + i); });
     };
     // A bare s_barrier: __syncthreads() would also drain every outstanding copy (it fences all memory),
     // which is exactly what the multi-stage pipeline must not do.  Visibility of a stage is established by
@@ -423,8 +419,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     auto next_stage = [&](unsigned char* refill, int64_t k_refill, const unsigned char* cur, const unsigned char* nxt) {
         __builtin_amdgcn_s_waitcnt(0x4F70);             // vmcnt(16)
         asm volatile("s_barrier" ::: "memory");         // the next step's stage is complete; everybody left `refill`
-        issue_copies(refill, min(k_refill, (g.spp - 1) * DK));
-        multiply(cur, nxt);
+        const int64_t k0 = min(k_refill, (g.spp - 1) * DK);
+        multiply(cur, nxt, [&](int i) { issue_copy(refill, k0, i); });
     };
     const int64_t ksteps = g.spp;                       // a multiple of 5 (the caller pads or splits off the tail)
     set_tile(tile_at(slot));
@@ -434,15 +430,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     issue_copies(stage3, 3 * DK);
     for (;;) {
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
+        for (int s = 0; s < 8; ++s)
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
+            for (int u = 0; u < 8; ++u)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) acc[s][u][i] = 0.f;
+                for (int i = 0; i < 4; ++i) acc[s][u][i] = 0.f;
         __builtin_amdgcn_s_waitcnt(0x4F78);             // vmcnt(24): step 0 has landed (and, from the second tile
                                                         // on, the previous tile's updates of H have left)
         asm volatile("s_barrier" ::: "memory");
-        fetch(stage0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) { fetchA(stage0, i); fetchB(stage0, i); }
         for (int64_t ks = 0; ks < ksteps; ks += 5) {
             next_stage(stage4, (ks + 4) * DK, stage0, stage1);
             next_stage(stage0, (ks + 5) * DK, stage1, stage2);
@@ -451,6 +448,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             next_stage(stage3, (ks + 8) * DK, stage4, stage0);
         }
         __builtin_amdgcn_s_waitcnt(0x0F70);             // this wavefront's surplus copies have landed: its parts of the stages are free
+#pragma unroll
+        for (int s = 4; s < 8; ++s) mfma_settle(acc[s][4], acc[s][5], acc[s][6], acc[s][7]);
 
         // The next tile's first four steps start now.  Another wavefront may still be in its last multiply:
         // that one reads stage 4, which is not refilled here, and prefetches fragments from stage 0 that nobody uses.
@@ -472,33 +471,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         if (BLOCKED && epart) {
             // split token range: the partial tile as it is, whole (rows and columns past n hold zeros)
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
+            for (int s = 0; s < 8; ++s)
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    float* pb = epart + (wm * 128 + s * 32 + 4 * lhi) * BT + wn * 128 + u * 32 + l32;
+                for (int u = 0; u < 8; ++u) {
+                    float* pb = epart + (wm * 128 + s * 16 + 4 * lq) * BT + wn * 128 + u * 16 + l16;
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) pb[(8 * (i >> 2) + (i & 3)) * BT] = acc[s][u][i];
+                    for (int i = 0; i < 4; ++i) pb[i * BT] = acc[s][u][i];
                 }
             if (!more) break;
             continue;
         }
         const bool inside = (er0 + BT <= g.n) && (ec0 + BT <= g.n);
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
+        for (int s = 0; s < 8; ++s)
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int64_t col = ec0 + wn * 128 + u * 32 + l32;
-                const int64_t rbase = er0 + wm * 128 + s * 32 + 4 * lhi;
+            for (int u = 0; u < 8; ++u) {
+                const int64_t col = ec0 + wn * 128 + u * 16 + l16;
+                const int64_t rbase = er0 + wm * 128 + s * 16 + 4 * lq;
                 if (inside) {
                     float* hb = g.H + rbase * g.ldh + col;
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) unsafeAtomicAdd(hb + (int64_t)(8 * (i >> 2) + (i & 3)) * g.ldh, 2.0f * acc[s][u][i]);
+                    for (int i = 0; i < 4; ++i) unsafeAtomicAdd(hb + i * g.ldh, 2.0f * acc[s][u][i]);
                 } else {
                     if (col >= g.n) continue;
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int64_t row = rbase + 8 * (i >> 2) + (i & 3);
-                        if (row < g.n) unsafeAtomicAdd(g.H + row * g.ldh + col, 2.0f * acc[s][u][i]);
+                    for (int i = 0; i < 4; ++i) {
+                        if (rbase + i < g.n) unsafeAtomicAdd(g.H + (rbase + i) * g.ldh + col, 2.0f * acc[s][u][i]);
                     }
                 }
             }
