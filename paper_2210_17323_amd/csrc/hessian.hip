@@ -17,13 +17,11 @@
 #include "hessian_tokens.h"
 #include "rules.h"
 #include "syrk_tiles.h"
+#include "tile256.h"
 
 namespace gptq {
 
-typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int HK = 64;          // token step (halves)
 constexpr int NXCD = 8;
@@ -62,22 +60,6 @@ __device__ __forceinline__ floatx16 mfma16(uint4 a, uint4 b, floatx16 c) {
     } else {
         return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, a), __builtin_bit_cast(halfx8, b), c, 0, 0, 0);
     }
-}
-
-// c += a b, the accumulator in place.  As a statement of its own and not the builtin: with 256 accumulator registers in groups of
-// four the compiler gives the builtin's result another place than its addend and copies and spills between them.  What it
-// cannot see is that this is a matrix-core instruction: the callers see to it that no vector instruction writes an operand
-// right before, and wait before the first read of an accumulator (mfma_settle).
-template <bool IS_BF16>
-__device__ __forceinline__ void mfma16x16_acc(floatx4& c, uint4 a, uint4 b) {
-    if constexpr (IS_BF16)
-        asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(__builtin_bit_cast(bf16x8, a)), "v"(__builtin_bit_cast(bf16x8, b)));
-    else
-        asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(c) : "v"(__builtin_bit_cast(halfx8, a)), "v"(__builtin_bit_cast(halfx8, b)));
-}
-// The last results of a loop of these, four at a time, before something else reads them: 16 wait states and more.
-__device__ __forceinline__ void mfma_settle(floatx4& a, floatx4& b, floatx4& c, floatx4& d) {
-    asm volatile("s_nop 15\n\ts_nop 3" : "+a"(a), "+a"(b), "+a"(c), "+a"(d));
 }
 
 __device__ __forceinline__ uint4 load8h_guard(const uint16_t* p, int64_t valid) {
@@ -376,39 +358,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         for (int q = 0; q < 8; ++q) issue_copy(stage, k0, q);
     };
 
-    floatx4 acc[8][8];
-
-    // This lane's operand rows are wm*128 + s*16 + lane%16 (A) and wn*128 + u*16 + lane%16 (B), its chunk of a row's four
-    // lane/16: the swizzle term (row / 4) % 4 is (lane / 4) % 4 for all of them, and s / u only add a constant 1024 bytes.
-    const int rowA = (wm * 128 + l16) * 64 + ((lq ^ ((l16 >> 2) & 3)) << 4), rowB = PANEL + (wn * 128 + l16) * 64 + ((lq ^ ((l16 >> 2) & 3)) << 4);
-    // One 32-token step out of `cur`, a quarter of the tile (64 x 64) at a time: rows and columns each in a first and a second half.
-    // The fragments of both first halves are in fa / fb already; a quarter fetches what a later one wants into the registers that
-    // are free by then -- the second rows, the second columns, then both first halves of the NEXT step (`nxt`, whose copies have
-    // landed) --, eight MFMAs before they are read, so that no MFMA waits for an LDS round trip, not even right after the barrier.
-    // The step's 8 copies are spread over its MFMAs as well: with one wavefront per SIMD nothing else can
-    // issue while a copy instruction is being accepted (tens of cycles each), so copies issued back to back idle the matrix core.
-    uint4 fa[8], fb[8];
-    auto fetchA = [&](const unsigned char* st, int s) { fa[s] = *reinterpret_cast<const uint4*>(st + rowA + s * 1024); };
-    auto fetchB = [&](const unsigned char* st, int u) { fb[u] = *reinterpret_cast<const uint4*>(st + rowB + u * 1024); };
-    auto quarter = [&](int hs, int hu, auto&& fetch, auto&& copy) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int s = 4 * hs + i;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {                // back and forth: one operand changes at a time
-                const int u = 4 * hu + ((i & 1) ? 3 - j : j);
-                mfma16x16_acc<IS_BF16>(acc[s][u], fa[s], fb[u]);
-                if (i < 2 && (j & 1)) fetch(2 * i + (j >> 1));
-            }
-            if (i >= 2) copy(i - 2);
-        }
-    };
-    auto multiply = [&](const unsigned char* cur, const unsigned char* nxt, auto&& copy) {
-        quarter(0, 0, [&](int i) { fetchA(cur, 4 + i); }, [&](int i) { copy(i); });
-        quarter(1, 0, [&](int i) { fetchB(cur, 4 + i); }, [&](int i) { copy(2 + i); });
-        quarter(0, 1, [&](int i) { fetchB(nxt, i); }, [&](int i) { copy(4 + i); });
-        quarter(1, 1, [&](int i) { fetchA(nxt, i); }, [&](int i) { copy(6 + i); });
-    };
+    Tile256Lane<IS_BF16> mm(lane, wm, wn);
     // A bare s_barrier: __syncthreads() would also drain every outstanding copy (it fences all memory),
     // which is exactly what the multi-stage pipeline must not do.  Visibility of a stage is established by
     // each wavefront waiting for its own copies of that step before it arrives at the barrier.  A step's
@@ -420,7 +370,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         __builtin_amdgcn_s_waitcnt(0x4F70);             // vmcnt(16)
         asm volatile("s_barrier" ::: "memory");         // the next step's stage is complete; everybody left `refill`
         const int64_t k0 = min(k_refill, (g.spp - 1) * DK);
-        multiply(cur, nxt, [&](int i) { issue_copy(refill, k0, i); });
+        mm.multiply(cur, nxt, [&](int i) { issue_copy(refill, k0, i); });
     };
     const int64_t ksteps = g.spp;                       // a multiple of 5 (the caller pads or splits off the tail)
     set_tile(tile_at(slot));
@@ -429,17 +379,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     issue_copies(stage2, 2 * DK);
     issue_copies(stage3, 3 * DK);
     for (;;) {
-#pragma unroll
-        for (int s = 0; s < 8; ++s)
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc[s][u][i] = 0.f;
+        mm.clear();
         __builtin_amdgcn_s_waitcnt(0x4F78);             // vmcnt(24): step 0 has landed (and, from the second tile
                                                         // on, the previous tile's updates of H have left)
         asm volatile("s_barrier" ::: "memory");
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { fetchA(stage0, i); fetchB(stage0, i); }
+        mm.fetch_first(stage0);
         for (int64_t ks = 0; ks < ksteps; ks += 5) {
             next_stage(stage4, (ks + 4) * DK, stage0, stage1);
             next_stage(stage0, (ks + 5) * DK, stage1, stage2);
@@ -448,8 +392,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             next_stage(stage3, (ks + 8) * DK, stage4, stage0);
         }
         __builtin_amdgcn_s_waitcnt(0x0F70);             // this wavefront's surplus copies have landed: its parts of the stages are free
-#pragma unroll
-        for (int s = 4; s < 8; ++s) mfma_settle(acc[s][4], acc[s][5], acc[s][6], acc[s][7]);
+        mm.settle();
 
         // The next tile's first four steps start now.  Another wavefront may still be in its last multiply:
         // that one reads stage 4, which is not refilled here, and prefetches fragments from stage 0 that nobody uses.
@@ -476,7 +419,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                 for (int u = 0; u < 8; ++u) {
                     float* pb = epart + (wm * 128 + s * 16 + 4 * lq) * BT + wn * 128 + u * 16 + l16;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) pb[i * BT] = acc[s][u][i];
+                    for (int i = 0; i < 4; ++i) pb[i * BT] = mm.acc[s][u][i];
                 }
             if (!more) break;
             continue;
@@ -491,12 +434,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
                 if (inside) {
                     float* hb = g.H + rbase * g.ldh + col;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) unsafeAtomicAdd(hb + i * g.ldh, 2.0f * acc[s][u][i]);
+                    for (int i = 0; i < 4; ++i) unsafeAtomicAdd(hb + i * g.ldh, 2.0f * mm.acc[s][u][i]);
                 } else {
                     if (col >= g.n) continue;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        if (rbase + i < g.n) unsafeAtomicAdd(g.H + (rbase + i) * g.ldh + col, 2.0f * acc[s][u][i]);
+                        if (rbase + i < g.n) unsafeAtomicAdd(g.H + (rbase + i) * g.ldh + col, 2.0f * mm.acc[s][u][i]);
                     }
                 }
             }
