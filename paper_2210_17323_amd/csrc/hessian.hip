@@ -320,7 +320,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
-    const int l16 = lane & 15, lq = lane >> 4;
 
     // this lane's part of the 4 + 4 copies of a step: row (wave*4 + i)*16 + lane/4 of each panel, chunk
     // (lane%4) ^ ((lane/16)%4).  Rows past n are clamped: they only feed outputs that are never stored.
@@ -416,10 +415,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
             for (int s = 0; s < 8; ++s)
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    float* pb = epart + (wm * 128 + s * 16 + 4 * lq) * BT + wn * 128 + u * 16 + l16;
+                for (int hu = 0; hu < 2; ++hu) {
+                    float* pb = epart + (wm * 128 + s * 16) * BT + wn * 128 + hu * 64 + lane;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) pb[i * BT] = mm.acc[s][u][i];
+                    for (int i = 0; i < 4; ++i) {
+                        float row[4];
+                        mm.rows64(s, hu, i, row);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) pb[(i + 4 * q) * BT] = row[q];
+                    }
                 }
             if (!more) break;
             continue;
@@ -428,19 +432,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
         for (int s = 0; s < 8; ++s)
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int64_t col = ec0 + wn * 128 + u * 16 + l16;
-                const int64_t rbase = er0 + wm * 128 + s * 16 + 4 * lq;
-                if (inside) {
-                    float* hb = g.H + rbase * g.ldh + col;
+            for (int hu = 0; hu < 2; ++hu) {
+                const int64_t col = ec0 + wn * 128 + hu * 64 + lane, r = er0 + wm * 128 + s * 16;
+                float* hb = g.H + r * g.ldh + col;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) unsafeAtomicAdd(hb + i * g.ldh, 2.0f * mm.acc[s][u][i]);
-                } else {
-                    if (col >= g.n) continue;
+                for (int i = 0; i < 4; ++i) {
+                    float row[4];
+                    mm.rows64(s, hu, i, row);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        if (rbase + i < g.n) unsafeAtomicAdd(g.H + (rbase + i) * g.ldh + col, 2.0f * mm.acc[s][u][i]);
-                    }
+                    for (int q = 0; q < 4; ++q)
+                        if (inside || (col < g.n && r + i + 4 * q < g.n)) unsafeAtomicAdd(hb + (i + 4 * q) * g.ldh, 2.0f * row[q]);
                 }
             }
         if (!more) break;
