@@ -74,8 +74,8 @@ struct Tile256Lane {
                 const int u = 4 * hu + ((i & 1) ? 3 - j : j);
                 mfma16x16_acc<IS_BF16>(acc[s][u], fa[s], fb[u]);
                 if (i < 2 && (j & 1)) fetch(2 * i + (j >> 1));
+                if ((i & 1) && j == 2) copy(i >> 1);
             }
-            if (i >= 2) copy(i - 2);
         }
     }
     // One step out of `cur`.  The fragments of the first half of the rows and of the columns are there already; a quarter fetches what a
