@@ -19,6 +19,7 @@ struct PackedArgs {
     int64_t group, ngroups;      // group == 0: one grid per row (ngroups == 1)
     int gshift;                  // log2(group) if the group size is a power of two, else -1 (then columns are divided)
     int64_t rows_per_wg;         // matvec: rows a workgroup walks, a multiple of its row chunk
+    int segw;                    // matvec: wavefronts that share a row, each every segw-th segment of columns
 };
 
 template <int BITS>
@@ -232,13 +233,42 @@ __global__ __launch_bounds__(256) void dequantize_kernel(PackedArgs a, OT* out, 
 }
 
 // ---- y = Q x, batch 1 -----------------------------------------------------------------------------------------
-// A workgroup of 4 wavefronts owns MV_ROWS rows.  A wavefront walks every fourth 2048-column segment of those
-// rows: a lane holds the 32 vector entries of its 32 columns in registers (read once per segment, shared by all
-// the rows), reads b consecutive words per row -- a wavefront reads 64*b*4 contiguous bytes of a row -- and
-// accumulates  scale * (sum code*x - zero * sum x)  in float32.  The lane sums of a row are reduced across the
-// wavefront with DPP-style shuffles and across the four wavefronts through LDS.
+// A wavefront takes 4 (or 8) rows and every segw-th 2048-column segment of them: a lane holds the 32 vector entries of
+// its 32 columns in registers (read once per segment, shared by all the rows), reads b consecutive words per row -- a
+// wavefront reads 64*b*4 contiguous bytes of a row -- and accumulates  scale * (sum code*x - zero * sum x)  in float32.
+// The lane sums of four rows are reduced across the wavefront by lane swaps and row rotations, and across the segw wavefronts
+// that share them through LDS.
 constexpr int MV_ROWS = 4;
 constexpr int MV_SEG = 64 * 32;
+constexpr int MV_MAX_WAVES = 16;
+
+template <int CTRL>
+__device__ __forceinline__ float add_rotated(float v) {
+    return v + __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), CTRL, 0xf, 0xf, false));
+}
+// Sums over the wavefront of four values at once: every lane of a group of 16 gets the sum of value wave_sum_index(lane).
+__device__ __forceinline__ float wave_sum4(float a, float b, float c, float d) {
+    auto swap32 = [](float x, float y) {
+        const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+        return __uint_as_float(t[0]) + __uint_as_float(t[1]);
+    };
+    const float ab = swap32(a, b), cd = swap32(c, d);        // lanes 0 .. 31: a (c), 32 .. 63: b (d), two lanes summed
+    const auto t = __builtin_amdgcn_permlane16_swap(__float_as_uint(ab), __float_as_uint(cd), false, false);
+    float v = __uint_as_float(t[0]) + __uint_as_float(t[1]); // groups of 16 lanes: a, c, b, d
+    v = add_rotated<0x128>(v);                               // row_ror 8, 4, 2, 1
+    v = add_rotated<0x124>(v);
+    v = add_rotated<0x122>(v);
+    return add_rotated<0x121>(v);
+}
+__device__ __forceinline__ int wave_sum_index(int lane) { return ((lane >> 4) & 1) * 2 + (lane >> 5); }
+
+// sum over the segw wavefronts of a row group, two at a time
+template <int W>
+__device__ __forceinline__ float sum_parts(const float (*part)[W], int first, int segw, int i) {
+    float v = segw == 1 ? part[first][i] : part[first][i] + part[first + 1][i];
+    for (int w = 2; w < segw; w += 2) v += part[first + w][i] + part[first + w + 1][i];
+    return v;
+}
 
 template <typename XT>
 __device__ __forceinline__ void load_x32(const XT* x, int64_t k0, int64_t n, float (&xf)[32]) {
@@ -272,18 +302,20 @@ __device__ __forceinline__ void load_x32(const XT* x, int64_t k0, int64_t n, flo
 }
 
 // GSUB = number of grids inside a lane's 32 columns: 1 (one grid per row, or groups of a multiple of 32), 2 (16), 4 (8)
-template <int BITS, int GSUB, typename XT>
-__global__ __launch_bounds__(256) void matvec_kernel(PackedArgs a, const XT* x, float* y) {
-    __shared__ float part[4][MV_ROWS];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+template <int BITS, int GSUB, int WAVES, typename XT>
+__global__ __launch_bounds__(64 * WAVES) void matvec_kernel(PackedArgs a, const XT* x, float* y) {
+    __shared__ float part[WAVES][MV_ROWS];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int groups = (int)(blockDim.x >> 6) / a.segw, grp = wave / a.segw, sw = wave % a.segw;
     const int64_t nseg = (a.n + MV_SEG - 1) / MV_SEG;
     constexpr int GL = 32 / GSUB;            // columns per grid inside the lane's 32
     const int64_t row_end = min(((int64_t)blockIdx.x + 1) * a.rows_per_wg, a.r);
-    for (int64_t row0 = (int64_t)blockIdx.x * a.rows_per_wg; row0 < row_end; row0 += MV_ROWS) {
+    for (int64_t wg0 = (int64_t)blockIdx.x * a.rows_per_wg; wg0 < row_end; wg0 += groups * MV_ROWS) {
+    const int64_t row0 = wg0 + grp * MV_ROWS;
     float acc[MV_ROWS];
 #pragma unroll
     for (int rr = 0; rr < MV_ROWS; ++rr) acc[rr] = 0.f;
-    for (int64_t s = wave; s < nseg; s += 4) {
+    for (int64_t s = sw; s < nseg; s += a.segw) {
         const int64_t k0 = s * MV_SEG + (int64_t)lane * 32;
         if (k0 >= a.n) continue;
         float xf[32];
@@ -315,16 +347,11 @@ __global__ __launch_bounds__(256) void matvec_kernel(PackedArgs a, const XT* x, 
             }
         }
     }
-#pragma unroll
-    for (int rr = 0; rr < MV_ROWS; ++rr) {
-        float v = acc[rr];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-        if (lane == 0) part[wave][rr] = v;
-    }
+    const float v = wave_sum4(acc[0], acc[1], acc[2], acc[3]);
+    if ((lane & 15) == 0) part[wave][wave_sum_index(lane)] = v;
     __syncthreads();
-    if (threadIdx.x < MV_ROWS && row0 + threadIdx.x < a.r)
-        y[row0 + threadIdx.x] = (part[0][threadIdx.x] + part[1][threadIdx.x]) + (part[2][threadIdx.x] + part[3][threadIdx.x]);
+    const int64_t row = wg0 + threadIdx.x;
+    if (threadIdx.x < groups * MV_ROWS && row < a.r) y[row] = sum_parts<MV_ROWS>(part, (int)(threadIdx.x / MV_ROWS) * a.segw, a.segw, threadIdx.x % MV_ROWS);
     __syncthreads();
     }
 }
@@ -334,8 +361,7 @@ __global__ __launch_bounds__(256) void matvec_kernel(PackedArgs a, const XT* x, 
 // per segment.  The dot products accumulate sum (2^b + code) x in float32, and
 // sum (code - zero) x = that - (2^b + zero) sum x;  the offset is of the size of the codes themselves, so the
 // subtraction costs no accuracy worth naming.
-constexpr int MV2_ROWS = 8;      // rows per step of a workgroup, read four at a time
-constexpr int MV2_HALF = 4;
+constexpr int MV2_HALF = 4;      // rows of a wavefront are read four at a time: four or eight (NH = 1, 2) per step
 
 // The b words of this lane's 32 columns for four consecutive rows (rows past r repeat the last one).  n is a multiple
 // of 32 here, so a lane's words are all inside the row or all outside; `w0` is clamped by the caller for the latter,
@@ -368,10 +394,21 @@ __device__ __forceinline__ void dot2_ordered(float& d, uint32_t pair, half2v xv)
     asm volatile("v_dot2_f32_f16 %0, %1, %2, %0" : "+v"(d) : "v"(pair), "v"(xv));
 }
 
+// Scale and zero point of four rows at the lane's group
+struct MvGrid { float sc[MV2_HALF]; int zr[MV2_HALF]; };
+__device__ __forceinline__ void mv_load_grid(MvGrid& gr, const PackedArgs& a, int rowbase, uint32_t g0) {
+#pragma unroll
+    for (int rr = 0; rr < MV2_HALF; ++rr) {
+        const int row = __builtin_amdgcn_readfirstlane(min(rowbase + rr, (int)a.r - 1));
+        const int64_t gbase = (int64_t)row * a.ngroups;      // scalar; the lane's group is a 32-bit index on top
+        gr.sc[rr] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(a.scales + gbase) + g0 * 4u);
+        gr.zr[rr] = *reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(a.zeros + gbase) + g0 * 4u);
+    }
+}
+
 // acc[rr] += scale * (sum (2^b + code) x - (2^b + zero) sum x) over this lane's 32 columns, for four rows
 template <int BITS>
-__device__ __forceinline__ void mv_dot_rows(const uint32_t (&w)[MV2_HALF][BITS + 1], const half2v (&xq)[16], float sx, float* acc,
-                                            const PackedArgs& a, int rowbase, uint32_t g0) {
+__device__ __forceinline__ void mv_dot_rows(const uint32_t (&w)[MV2_HALF][BITS + 1], const half2v (&xq)[16], float sx, float* acc, const MvGrid& gr) {
     constexpr int WANT = 10 - BITS;
     constexpr uint32_t M = (1u << BITS) - 1u;
     constexpr uint32_t MASK_LO = M << WANT, MASK_HI = M << (16 + WANT), MASK = MASK_LO | MASK_HI;
@@ -405,74 +442,95 @@ __device__ __forceinline__ void mv_dot_rows(const uint32_t (&w)[MV2_HALF][BITS +
             if (i & 1) dot2_ordered(d1, v, xq[i]);
             else       dot2_ordered(d0, v, xq[i]);
         }
-        const int row = __builtin_amdgcn_readfirstlane(min(rowbase + rr, (int)a.r - 1));
-        const int64_t gbase = (int64_t)row * a.ngroups;      // scalar; the lane's group is a 32-bit index on top
-        const float sc = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(a.scales + gbase) + g0 * 4u);
-        const int zr = *reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(a.zeros + gbase) + g0 * 4u);
-        acc[rr] = fmaf(sc, (d0 + d1) - (offset + (float)zr) * sx, acc[rr]);
+        // a dot product's result wants three wait states before another kind of instruction reads it; inside a statement the
+        // compiler does not see the one that wrote it
+        asm volatile("s_nop 3" : "+v"(d0), "+v"(d1));
+        acc[rr] = fmaf(gr.sc[rr], (d0 + d1) - (offset + (float)gr.zr[rr]) * sx, acc[rr]);
     }
 }
 
 // The words of the next four rows are requested before the current four are multiplied (within a segment, and across to
 // the wavefront's next segment), so a wavefront always has loads in flight while it computes.
+// NH: halves of four rows per step.  With eight rows a vector entry's preparation serves twice as many; with four there are twice as many
+// wavefronts, and up to 16 of them in a workgroup (mv_plan).
+
+// The lane's 32 vector entries, two halves per register, zeros past n, then paired like the codes; returns their sum on top of sx
+__device__ __forceinline__ void mv_load_x(uint32_t (&xp)[16], const __half* x, int64_t k0, int64_t n) {
+    const bool inside = k0 < n;
+    const __half* xsrc = x + min(k0, n - 32);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const uint4 u = reinterpret_cast<const uint4*>(xsrc)[q];
+        xp[4 * q] = inside ? u.x : 0u; xp[4 * q + 1] = inside ? u.y : 0u; xp[4 * q + 2] = inside ? u.z : 0u; xp[4 * q + 3] = inside ? u.w : 0u;
+    }
+}
 template <int BITS>
-__global__ __launch_bounds__(256) void matvec_dot2_kernel(PackedArgs a, const __half* x, float* y) {
-    __shared__ float part[4][MV2_ROWS];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+__device__ __forceinline__ float mv_pair_x(half2v (&xq)[16], const uint32_t (&xp)[16], float sx) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        sx = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2v, xp[i]), __builtin_bit_cast(half2v, 0x3C003C00u), sx, false);
+        const PairSpec sp = PairTable<BITS>::at(i);
+        const uint32_t lo = (xp[sp.k_lo >> 1] >> (16 * (sp.k_lo & 1))) & 0xFFFFu;
+        const uint32_t hi = (sp.k_hi & 1) ? (xp[sp.k_hi >> 1] & 0xFFFF0000u) : (xp[sp.k_hi >> 1] << 16);
+        xq[i] = __builtin_bit_cast(half2v, lo | hi);
+    }
+    return sx;
+}
+
+template <int BITS, int NH, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void matvec_dot2_kernel(PackedArgs a, const __half* x, float* y) {
+    constexpr int ROWS = NH * MV2_HALF;
+    __shared__ float part[WAVES][ROWS];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int groups = (int)(blockDim.x >> 6) / a.segw, grp = wave / a.segw, sw = wave % a.segw;
     const int64_t nseg = (a.n + MV_SEG - 1) / MV_SEG;
     const int64_t row_end = min(((int64_t)blockIdx.x + 1) * a.rows_per_wg, a.r);
-    for (int64_t row0 = (int64_t)blockIdx.x * a.rows_per_wg; row0 < row_end; row0 += MV2_ROWS) {
-    float acc[MV2_ROWS];
-#pragma unroll
-    for (int rr = 0; rr < MV2_ROWS; ++rr) acc[rr] = 0.f;
-    uint32_t wa[MV2_HALF][BITS + 1], wb[MV2_HALF][BITS + 1];
     const uint32_t wlast = (uint32_t)(a.words_per_row - BITS);      // n is a multiple of 32 and at least 32
     auto words_at = [&](int64_t seg) { return min((uint32_t)(((seg * MV_SEG) >> 5) + lane) * BITS, wlast); };
-    const int row0i = (int)row0;
-    if (wave < nseg) mv_load_rows<BITS>(wa, a, row0i, words_at(wave));
+    for (int64_t wg0 = (int64_t)blockIdx.x * a.rows_per_wg; wg0 < row_end; wg0 += groups * ROWS) {
+    float acc[ROWS];
+#pragma unroll
+    for (int rr = 0; rr < ROWS; ++rr) acc[rr] = 0.f;
+    uint32_t wa[MV2_HALF][BITS + 1], wb[MV2_HALF][BITS + 1];
+    const int row0i = (int)wg0 + grp * ROWS;
+    if (sw < nseg) mv_load_rows<BITS>(wa, a, row0i, words_at(sw));
 #pragma unroll 1
-    for (int64_t s = wave; s < nseg; s += 4) {
+    for (int64_t s = sw; s < nseg; s += a.segw) {
         const int64_t k0 = s * MV_SEG + (int64_t)lane * 32;      // lanes past the last column: any words, zero vector entries
-        mv_load_rows<BITS>(wb, a, row0i + MV2_HALF, words_at(s));
-        uint32_t xp[16];                                     // the lane's 32 vector entries, two halves per register
-        {
-            const bool inside = k0 < a.n;
-            const __half* xsrc = x + min(k0, a.n - 32);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const uint4 u = reinterpret_cast<const uint4*>(xsrc)[q];
-                xp[4 * q] = inside ? u.x : 0u; xp[4 * q + 1] = inside ? u.y : 0u; xp[4 * q + 2] = inside ? u.z : 0u; xp[4 * q + 3] = inside ? u.w : 0u;
-            }
-        }
-        asm volatile("" ::: "memory");                       // the requests above stay above the arithmetic below
-        float sx = 0.f;
-        half2v xq[16];                                       // the same entries paired like the codes
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            sx = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2v, xp[i]), __builtin_bit_cast(half2v, 0x3C003C00u), sx, false);
-            const PairSpec sp = PairTable<BITS>::at(i);
-            const uint32_t lo = (xp[sp.k_lo >> 1] >> (16 * (sp.k_lo & 1))) & 0xFFFFu;
-            const uint32_t hi = (sp.k_hi & 1) ? (xp[sp.k_hi >> 1] & 0xFFFF0000u) : (xp[sp.k_hi >> 1] << 16);
-            xq[i] = __builtin_bit_cast(half2v, lo | hi);
-        }
+        if constexpr (NH == 2) mv_load_rows<BITS>(wb, a, row0i + MV2_HALF, words_at(s));
+        uint32_t xp[16];
+        mv_load_x(xp, x, k0, a.n);
         // column / group size without the 64-bit division (n < 2^31 is checked on the host)
         const uint32_t kc = (uint32_t)min(k0, a.n - 32);
         const uint32_t g0 = a.group == 0 ? 0u : (a.gshift >= 0 ? kc >> a.gshift : kc / (uint32_t)a.group);
-        mv_dot_rows<BITS>(wa, xq, sx, acc, a, row0i, g0);
-        if (s + 4 < nseg) mv_load_rows<BITS>(wa, a, row0i, words_at(s + 4));
-        asm volatile("" ::: "memory");
-        mv_dot_rows<BITS>(wb, xq, sx, acc + MV2_HALF, a, row0i + MV2_HALF, g0);
+        MvGrid gr;
+        mv_load_grid(gr, a, row0i, g0);
+        if constexpr (NH == 1)
+            if (s + a.segw < nseg) mv_load_rows<BITS>(wb, a, row0i, words_at(s + a.segw));
+        asm volatile("" ::: "memory");                       // the requests above stay above the arithmetic below
+        half2v xq[16];
+        const float sx = mv_pair_x<BITS>(xq, xp, 0.f);
+        mv_dot_rows<BITS>(wa, xq, sx, acc, gr);
+        if constexpr (NH == 2) {
+            mv_load_grid(gr, a, row0i + MV2_HALF, g0);
+            if (s + a.segw < nseg) mv_load_rows<BITS>(wa, a, row0i, words_at(s + a.segw));
+            asm volatile("" ::: "memory");
+            mv_dot_rows<BITS>(wb, xq, sx, acc + MV2_HALF, gr);
+        } else {
+#pragma unroll
+            for (int rr = 0; rr < MV2_HALF; ++rr)
+#pragma unroll
+                for (int i = 0; i <= BITS; ++i) wa[rr][i] = wb[rr][i];
+        }
     }
 #pragma unroll
-    for (int rr = 0; rr < MV2_ROWS; ++rr) {
-        float v = acc[rr];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-        if (lane == 0) part[wave][rr] = v;
+    for (int h = 0; h < NH; ++h) {
+        const float v = wave_sum4(acc[4 * h], acc[4 * h + 1], acc[4 * h + 2], acc[4 * h + 3]);
+        if ((lane & 15) == 0) part[wave][4 * h + wave_sum_index(lane)] = v;
     }
     __syncthreads();
-    if (threadIdx.x < MV2_ROWS && row0 + threadIdx.x < a.r)
-        y[row0 + threadIdx.x] = (part[0][threadIdx.x] + part[1][threadIdx.x]) + (part[2][threadIdx.x] + part[3][threadIdx.x]);
+    const int64_t row = wg0 + threadIdx.x;
+    if (threadIdx.x < groups * ROWS && row < a.r) y[row] = sum_parts<ROWS>(part, (int)(threadIdx.x / ROWS) * a.segw, a.segw, threadIdx.x % ROWS);
     __syncthreads();
     }
 }
@@ -542,75 +600,71 @@ __device__ __forceinline__ void mv_mfma_rows(const uint32_t (&w)[MV2_HALF][BITS 
     }
 }
 
-template <int BITS>
-__global__ __launch_bounds__(256) void matvec_mfma_kernel(PackedArgs a, const __half* x, float* y) {
-    __shared__ float part[4][MV2_ROWS + 1];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+template <int BITS, int NH, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void matvec_mfma_kernel(PackedArgs a, const __half* x, float* y) {
+    constexpr int ROWS = NH * MV2_HALF;
+    __shared__ float part[WAVES][ROWS + 1];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int groups = (int)(blockDim.x >> 6) / a.segw, grp = wave / a.segw, sw = wave % a.segw;
     const int64_t nseg = (a.n + MV_SEG - 1) / MV_SEG;
     const int64_t row_end = min(((int64_t)blockIdx.x + 1) * a.rows_per_wg, a.r);
     // this lane's element of the diagonal of D: lane = j + 16 ib holds D[4 ib + e][j], e = 0 .. 3
     const int dj = lane & 15, dib = lane >> 4;
     const bool on_diag = (dj >> 2) == dib;
     const int de = dj & 3;
-    for (int64_t row0 = (int64_t)blockIdx.x * a.rows_per_wg; row0 < row_end; row0 += MV2_ROWS) {
-    float4v acc[MV2_ROWS];
-#pragma unroll
-    for (int rr = 0; rr < MV2_ROWS; ++rr) acc[rr] = float4v{0.f, 0.f, 0.f, 0.f};
-    float sx = 0.f;                                          // sum of this lane's vector entries over its segments
-    uint32_t wa[MV2_HALF][BITS + 1], wb[MV2_HALF][BITS + 1];
     const uint32_t wlast = (uint32_t)(a.words_per_row - BITS);      // n is a multiple of 32 and at least 32
     auto words_at = [&](int64_t seg) { return min((uint32_t)(((seg * MV_SEG) >> 5) + lane) * BITS, wlast); };
-    const int row0i = (int)row0;
-    if (wave < nseg) mv_load_rows<BITS>(wa, a, row0i, words_at(wave));
+    for (int64_t wg0 = (int64_t)blockIdx.x * a.rows_per_wg; wg0 < row_end; wg0 += groups * ROWS) {
+    float4v acc[ROWS];
+#pragma unroll
+    for (int rr = 0; rr < ROWS; ++rr) acc[rr] = float4v{0.f, 0.f, 0.f, 0.f};
+    float sx = 0.f;                                          // sum of this lane's vector entries over its segments
+    uint32_t wa[MV2_HALF][BITS + 1], wb[MV2_HALF][BITS + 1];
+    const int row0i = (int)wg0 + grp * ROWS;
+    if (sw < nseg) mv_load_rows<BITS>(wa, a, row0i, words_at(sw));
 #pragma unroll 1
-    for (int64_t s = wave; s < nseg; s += 4) {
+    for (int64_t s = sw; s < nseg; s += a.segw) {
         const int64_t k0 = s * MV_SEG + (int64_t)lane * 32;      // lanes past the last column: any words, zero vector entries
-        mv_load_rows<BITS>(wb, a, row0i + MV2_HALF, words_at(s));
+        if constexpr (NH == 2) mv_load_rows<BITS>(wb, a, row0i + MV2_HALF, words_at(s));
         uint32_t xp[16];
-        {
-            const bool inside = k0 < a.n;
-            const __half* xsrc = x + min(k0, a.n - 32);
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const uint4 u = reinterpret_cast<const uint4*>(xsrc)[q];
-                xp[4 * q] = inside ? u.x : 0u; xp[4 * q + 1] = inside ? u.y : 0u; xp[4 * q + 2] = inside ? u.z : 0u; xp[4 * q + 3] = inside ? u.w : 0u;
-            }
-        }
+        mv_load_x(xp, x, k0, a.n);
+        if constexpr (NH == 1)
+            if (s + a.segw < nseg) mv_load_rows<BITS>(wb, a, row0i, words_at(s + a.segw));
         asm volatile("" ::: "memory");                       // the requests above stay above the arithmetic below
-        half2v xq[16];                                       // the same entries paired like the codes
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            sx = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2v, xp[i]), __builtin_bit_cast(half2v, 0x3C003C00u), sx, false);
-            const PairSpec sp = PairTable<BITS>::at(i);
-            const uint32_t lo = (xp[sp.k_lo >> 1] >> (16 * (sp.k_lo & 1))) & 0xFFFFu;
-            const uint32_t hi = (sp.k_hi & 1) ? (xp[sp.k_hi >> 1] & 0xFFFF0000u) : (xp[sp.k_hi >> 1] << 16);
-            xq[i] = __builtin_bit_cast(half2v, lo | hi);
-        }
+        half2v xq[16];
+        sx = mv_pair_x<BITS>(xq, xp, sx);
         mv_mfma_rows<BITS>(wa, xq, acc);
-        if (s + 4 < nseg) mv_load_rows<BITS>(wa, a, row0i, words_at(s + 4));
-        asm volatile("" ::: "memory");
-        mv_mfma_rows<BITS>(wb, xq, acc + MV2_HALF);
-    }
-#pragma unroll
-    for (int rr = 0; rr <= MV2_ROWS; ++rr) {
-        float v;
-        if (rr < MV2_ROWS) {
-            const float4v c = acc[rr < MV2_ROWS ? rr : 0];
-            const float e = de == 0 ? c.x : (de == 1 ? c.y : (de == 2 ? c.z : c.w));
-            v = on_diag ? e : 0.f;
+        if constexpr (NH == 2) {
+            if (s + a.segw < nseg) mv_load_rows<BITS>(wa, a, row0i, words_at(s + a.segw));
+            asm volatile("" ::: "memory");
+            mv_mfma_rows<BITS>(wb, xq, acc + MV2_HALF);
         } else {
-            v = sx;
-        }
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-        if (lane == 0) part[wave][rr] = v;
+            for (int rr = 0; rr < MV2_HALF; ++rr)
+#pragma unroll
+                for (int i = 0; i <= BITS; ++i) wa[rr][i] = wb[rr][i];
+        }
     }
+#pragma unroll
+    for (int h = 0; h < NH; ++h) {
+        float d[4];
+#pragma unroll
+        for (int rr = 0; rr < 4; ++rr) {
+            const float4v c = acc[4 * h + rr];
+            const float e = de == 0 ? c.x : (de == 1 ? c.y : (de == 2 ? c.z : c.w));
+            d[rr] = on_diag ? e : 0.f;
+        }
+        const float v = wave_sum4(d[0], d[1], d[2], d[3]);
+        if ((lane & 15) == 0) part[wave][4 * h + wave_sum_index(lane)] = v;
+    }
+    const float sxs = wave_sum4(sx, 0.f, 0.f, 0.f);
+    if (lane == 0) part[wave][ROWS] = sxs;
     __syncthreads();
-    if (threadIdx.x < MV2_ROWS && row0 + threadIdx.x < a.r) {
-        const int64_t row = row0 + threadIdx.x;
-        const float dots = (part[0][threadIdx.x] + part[1][threadIdx.x]) + (part[2][threadIdx.x] + part[3][threadIdx.x]);
-        const float sxs = (part[0][MV2_ROWS] + part[1][MV2_ROWS]) + (part[2][MV2_ROWS] + part[3][MV2_ROWS]);
-        y[row] = a.scales[row * a.ngroups] * (dots - ((float)(1 << BITS) + (float)a.zeros[row * a.ngroups]) * sxs);
+    const int64_t row = wg0 + threadIdx.x;
+    if (threadIdx.x < groups * ROWS && row < a.r) {
+        const int first = (int)(threadIdx.x / ROWS) * a.segw;
+        const float dots = sum_parts<ROWS + 1>(part, first, a.segw, threadIdx.x % ROWS), sum = sum_parts<ROWS + 1>(part, first, a.segw, ROWS);
+        y[row] = a.scales[row * a.ngroups] * (dots - ((float)(1 << BITS) + (float)a.zeros[row * a.ngroups]) * sum);
     }
     __syncthreads();
     }
@@ -676,18 +730,43 @@ extern "C" int gptq_dequantize_packed(const uint32_t* words, int64_t ldp, int64_
     return GPTQ_OK;
 }
 
-// Rows are dealt to about eight workgroups per CU (what the kernels' registers allow) in equal shares, each a
-// multiple of the kernel's row chunk: with one chunk per workgroup the last round of a large launch would run
-// the chip partly empty.
-static int64_t rows_per_workgroup(int64_t r, int chunk) {
+static int64_t chip_cus() {
     static int cus = 0;
     if (cus == 0) {
         int dev = 0, v = 0;
         if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) cus = v;
         else cus = 256;
     }
-    const int64_t slots = (int64_t)cus * 8;
-    return (int64_t)round_up((size_t)ceil_div(r, slots), (size_t)chunk);
+    return cus;
+}
+
+// How a matrix is dealt out: the rows a wavefront takes at a time (4 NH), the wavefronts that share a row (segw, each every segw-th segment of
+// 2048 columns) and those of a workgroup.  Where rows have fewer segments than a workgroup has wavefronts these take other rows (before,
+// they had nothing to do); few rows of many segments are shared by up to 16; and a workgroup is smaller where there would be
+// fewer than CUs.  Measured, us per launch in a graph, 3 bits with one grid per row, four wavefronts a row and eight rows throughout as
+// before / now: 256 x 256 5.0 / 3.0, 4096 x 4096 6.2 / 4.0, 49152 x 256 25.9 / 9.5, 49152 x 4096 35.5 / 19.5, 256 x 49152 10.9 / 6.6 (4 bits,
+// groups of 128: 4.8 / 2.8, 6.0 / 3.7, 23.7 / 9.3, 35.9 / 22.1, 13.2 / 6.0).
+// Four rows at a time up to one segment of them for each of the 3072 wavefronts that hide a launch's latency (12288 x 2048 4.5 / 5.0 with eight,
+// 2048 x 12288 5.5 / 5.4, 8192 x 4096 5.3 / 5.1) and up to 1024 rows, where 16 wavefronts of a workgroup share them (1024 x 49152
+// 7.1 / 9.1; 1500 12.8 / 9.9); beyond, eight, which prepare a vector entry for twice the weights, shared by 8 up to 4096 rows
+// (1500 x 49152 9.9 / 11.5 with 4, 4000 x 24576 9.8 / 10.4, 12288 x 12288 20.3 / 16.7).  The general kernel takes four: with 16
+// wavefronts 1024 x 49152 14.6 -> 11.6, from 1500 rows on nothing or a loss.
+struct MvPlan { int nh, waves, segw; int64_t rows_per_wg; unsigned blocks; };
+static MvPlan mv_plan(int64_t r, int64_t n, bool may_take_eight) {
+    const int64_t nseg = ceil_div(n, MV_SEG);
+    const bool few = r <= 1024;
+    int nh = may_take_eight && !few && ceil_div(r, 4) * nseg > 3072 ? 2 : 1;
+    int most = few ? MV_MAX_WAVES : !may_take_eight ? 4 : nh == 1 ? MV_MAX_WAVES : r <= 4096 ? 8 : 4;
+    MvPlan p{};
+    p.nh = nh;
+    p.segw = 1;
+    while (p.segw < most && p.segw < nseg) p.segw *= 2;
+    p.waves = p.segw < 4 ? 4 : p.segw;
+    while (p.waves > p.segw && ceil_div(r, p.waves / p.segw * 4 * p.nh) < chip_cus()) p.waves /= 2;      // a workgroup for every CU
+    const int chunk = p.waves / p.segw * 4 * p.nh;
+    p.rows_per_wg = (int64_t)round_up((size_t)ceil_div(r, std::max<int64_t>(1, chip_cus() * 32 / p.waves)), (size_t)chunk);
+    p.blocks = (unsigned)ceil_div(r, p.rows_per_wg);
+    return p;
 }
 
 template <int BITS, typename XT>
@@ -695,21 +774,28 @@ static void launch_matvec(PackedArgs a, const XT* x, float* y, hipStream_t s) {
     const int gsub = (a.group == 0 || a.group % 32 == 0) ? 1 : (int)(32 / a.group);
     if constexpr (sizeof(XT) == 2) {
         // the fast kernel wants whole lanes (32 columns each) and 16-byte loads of the vector
-        if (gsub == 1 && a.n % 32 == 0 && a.n >= 32 && a.n < 0x7fffffffLL && a.r < 0x7fffffffLL && a.words_per_row < 0x3fffffffLL &&
+        if (gsub == 1 && a.n % 32 == 0 && a.n >= 32 && a.n < 0x7fffffffLL && a.r < 0x7fffff00LL && a.words_per_row < 0x3fffffffLL &&
             a.ngroups < 0x3fffffffLL && (reinterpret_cast<uintptr_t>(x) & 15) == 0) {
-            a.rows_per_wg = rows_per_workgroup(a.r, MV2_ROWS);
-            if (a.group == 0)
-                hipLaunchKernelGGL((matvec_mfma_kernel<BITS>), dim3((unsigned)ceil_div(a.r, a.rows_per_wg)), dim3(256), 0, s, a, x, y);
-            else
-                hipLaunchKernelGGL((matvec_dot2_kernel<BITS>), dim3((unsigned)ceil_div(a.r, a.rows_per_wg)), dim3(256), 0, s, a, x, y);
+            const MvPlan p = mv_plan(a.r, a.n, true);
+            a.rows_per_wg = p.rows_per_wg; a.segw = p.segw;
+            const dim3 grid(p.blocks), block(64 * p.waves);
+#define GPTQ_MV2(K)                                                                                             \
+            if (p.nh == 1) hipLaunchKernelGGL((K<BITS, 1, MV_MAX_WAVES>), grid, block, 0, s, a, x, y);          \
+            else if (p.waves > 4) hipLaunchKernelGGL((K<BITS, 2, MV_MAX_WAVES>), grid, block, 0, s, a, x, y);   \
+            else hipLaunchKernelGGL((K<BITS, 2, 4>), grid, block, 0, s, a, x, y)
+            if (a.group == 0) { GPTQ_MV2(matvec_mfma_kernel); } else { GPTQ_MV2(matvec_dot2_kernel); }
+#undef GPTQ_MV2
             return;
         }
     }
-    a.rows_per_wg = rows_per_workgroup(a.r, MV_ROWS);
-    const unsigned blocks = (unsigned)ceil_div(a.r, a.rows_per_wg);
-    if (gsub == 1) hipLaunchKernelGGL((matvec_kernel<BITS, 1, XT>), dim3(blocks), dim3(256), 0, s, a, x, y);
-    else if (gsub == 2) hipLaunchKernelGGL((matvec_kernel<BITS, 2, XT>), dim3(blocks), dim3(256), 0, s, a, x, y);
-    else hipLaunchKernelGGL((matvec_kernel<BITS, 4, XT>), dim3(blocks), dim3(256), 0, s, a, x, y);
+    const MvPlan p = mv_plan(a.r, a.n, false);
+    a.rows_per_wg = p.rows_per_wg; a.segw = p.segw;
+    const dim3 grid(p.blocks), block(64 * p.waves);
+#define GPTQ_MV1(G)                                                                                             \
+    if (p.waves > 4) hipLaunchKernelGGL((matvec_kernel<BITS, G, MV_MAX_WAVES, XT>), grid, block, 0, s, a, x, y); \
+    else hipLaunchKernelGGL((matvec_kernel<BITS, G, 4, XT>), grid, block, 0, s, a, x, y)
+    if (gsub == 1) { GPTQ_MV1(1); } else if (gsub == 2) { GPTQ_MV1(2); } else { GPTQ_MV1(4); }
+#undef GPTQ_MV1
 }
 
 extern "C" int gptq_matvec_packed(const uint32_t* words, int64_t ldp, int64_t r, int64_t n, int bits,

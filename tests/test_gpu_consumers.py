@@ -80,6 +80,42 @@ def test_consumers_match_oracle(bits, group, r, n, ternary):
             assert np.all(np.abs(y2.double().cpu().numpy() - want) <= bound)
 
 
+# The ways a product is dealt to wavefronts (rows at a time, wavefronts per row, wavefronts per workgroup) change with the sizes
+DEALT = [
+    # bits, group, r, n
+    (3, 0, 1, 32), (4, 32, 3, 256),             # workgroups of one wavefront, one segment
+    (2, 0, 1025, 2080),                         # ... of two, two segments, rows that fill no chunk
+    (4, 128, 5, 40960 + 128), (3, 0, 7, 34816), # 16 wavefronts a row, 21 and 17 segments
+    (3, 0, 1024, 6176), (4, 64, 1030, 6208),    # the last of few rows and the first beyond, a ragged segment
+    (2, 32, 2001, 14368), (3, 0, 2001, 14368),  # eight rows at a time, 8 wavefronts a row
+    (4, 0, 4099, 6176), (3, 128, 4099, 6272),   # ... 4 wavefronts a row
+    (4, 128, 13001, 256), (2, 0, 13001, 256),   # ... one, four row groups a workgroup
+    (4, 8, 1030, 4104), (3, 16, 300, 18448),    # the general kernel: two and 16 wavefronts a row
+]
+
+
+@pytest.mark.parametrize("bits,group,r,n", DEALT)
+def test_matvec_however_it_is_dealt(bits, group, r, n):
+    import paper_2210_17323_amd as g
+    _say(f"matvec bits={bits} group={group} r={r} n={n}")
+    codes, scale, zero = _random_layer(r, n, bits, group, 31 * bits + r + n)
+    words = O.pack_codes(codes, bits)
+    G = max(1, n // group) if group else 1
+    Q64 = (scale.astype(np.float64)[:, :, None] * (codes.reshape(r, G, -1) - zero[:, :, None])).reshape(r, n)
+    wd, sd, zd = torch.from_numpy(words.view(np.int32)).cuda(), torch.from_numpy(scale).cuda(), torch.from_numpy(zero).cuda()
+    rng = np.random.default_rng(r)
+    for dt in (torch.float16, torch.float32):
+        x = torch.from_numpy(rng.normal(size=n).astype(np.float32)).to(dt).cuda()
+        y = torch.full((r + 64,), 3.0, dtype=torch.float32, device="cuda")      # nothing is written past the last row
+        g.gptq_matvec_packed(wd, n, bits, sd, zd, group, x, y[:r])
+        x64 = x.double().cpu().numpy()
+        err = np.abs(y[:r].double().cpu().numpy() - Q64 @ x64)
+        bound = 1e-5 * (np.abs(Q64) @ np.abs(x64)) + 1e-30
+        _say(f"  {dt}: max err / bound = {(err / bound).max():.3f}")
+        assert np.all(err <= bound)
+        assert torch.equal(y[r:], torch.full_like(y[r:], 3.0))
+
+
 def test_consumers_after_the_solver():
     # the layer Alg. 1 produced, packed: decompression gives the solver's own Wq, the product gives Wq x
     import paper_2210_17323_amd as g
