@@ -132,10 +132,9 @@ GPTQ_API int gptq_hessian_symmetrize(float* H, int64_t ldh, int64_t n, void* str
  *             is allowed.
  *   Computed as a Cholesky factorisation taken from the last column backwards, H + lambda I = R R^T with R
  *   upper triangular, followed by the triangular inverse U = R^-1 (the same matrix, by uniqueness of
- *   the Cholesky factor), all in float32; the rank-1024 updates that carry most of the flops multiply three-piece
- *   bfloat16 splits of their float32 operands on the bf16 matrix cores when they are large (see
- *   gptq_symmetric_update_split below: the error of a float32 multiply-add), which is also what the second half of
- *   the workspace is for.
+ *   the Cholesky factor), all in float32; above 4096 channels the rank-1024 updates that carry most of the flops multiply
+ *   three-piece bfloat16 splits of their float32 operands on the bf16 matrix cores (see gptq_symmetric_update_split
+ *   below: less than the error of a float32 multiply-add), which is also what the second half of the workspace is for.
  *   Part of the work is enqueued on helper streams owned by the library (created once per host thread and
  *   device, default priority) and joined back with events: when the call returns, everything it enqueued
  *   is ordered on `stream`, and nothing of it starts before the work already on `stream`.
@@ -193,8 +192,8 @@ GPTQ_API int gptq_check_info(const int* info_dev, int* host_info, void* stream);
  *            sum over rows equals (1/2) tr((W-Q)(H + lambda I)(W-Q)^T).  May be NULL.
  *   ws       at least gptq_quantize_layer_workspace_bytes(r, n, block, group) bytes, 256-byte aligned.
  *   The update of column j's block and the rank-128 updates inside an outer block of 1024 columns are float32; the
- *   deferred rank-1024 updates beyond it are float32 matrix-core products or, when large, the split products of
- *   gptq_trailing_update_split below (n % 256 == 0 and n >= 2048, any r > 128: rows are padded to whole tiles in the workspace).
+ *   deferred rank-1024 updates beyond it are the split products of gptq_trailing_update_split below (n % 256 == 0 and
+ *   n >= 2048, any r > 128: rows are padded to whole tiles in the workspace) or float32 matrix-core products.
  *   r == 0 or n == 0 is a valid no-op.  Like step 2, the call puts part of its work on the library's helper
  *   stream and joins it back before returning.
  */
@@ -259,7 +258,7 @@ GPTQ_API int gptq_trailing_update(float* W, int64_t ldw, const float* E, int64_t
  * gptq_damp_cholesky* and gptq_quantize_layer* use for their large updates (Section 3, Steps 2 and 3; Alg. 1, last
  * statement of the outer loop).  Every float32 operand element is the exact sum of three bfloat16 pieces
  * (8 + 8 + 8 significant bits); of the nine piece products of a * b the six with i + j <= 4 are accumulated in
- * float32, smallest first; the three left out are below 2^-23 |a b|, the size of a float32 rounding.
+ * float32, the large ones on their own; the three left out are below 2^-23 |a b|, the size of a float32 rounding.
  *
  * gptq_trailing_update_split:   W[r x ncols] -= E[r x k] * U[k x ncols]       (arguments as gptq_trailing_update)
  * gptq_symmetric_update_split:  H[n x n] -= P[n x k] * P^T on the 256 x 256 tiles that touch the upper triangle
@@ -270,9 +269,9 @@ GPTQ_API int gptq_trailing_update(float* W, int64_t ldw, const float* E, int64_t
  *   Operand elements must be finite and below 2^127 in magnitude.
  */
 /*
- * Which launches take the split products is decided per launch from its count of 256 x 256 tiles: at least 144.
- * gptq_set_split_min_tiles(t) with t > 0 replaces that minimum for every later call of the process (t <= 0 restores
- * it) and returns the previous setting: a tuning and test knob -- the results of a call depend on it only through
+ * Which updates take the split products follows from the call's sizes: above 4096 channels in step 2, wherever the shapes allow
+ * it in step 3.  gptq_set_split_min_tiles(t) with t > 0 makes it launches of at least t tiles of 256 x 256 for every later call of
+ * the process (t <= 0 restores the rule) and returns the previous setting: a tuning and test knob -- the results of a call depend on it only through
  * rounding.  Not meant to be changed while another thread is inside a library call.
  */
 GPTQ_API int gptq_set_split_min_tiles(int tiles);

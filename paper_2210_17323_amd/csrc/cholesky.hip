@@ -92,8 +92,11 @@ using namespace gptq;
 namespace {
 constexpr int OB = 1024;     // outer block: rank-1024 updates keep the big GEMMs compute-bound and their tiles long
 static_assert(OB == SPLIT_K, "the split products take exactly one outer block as K");
-// A rank-1024 update goes through the split-operand kernel (bf16 matrix cores, 256 x 256 tiles) when its tiles fill the
-// chip well (split_pays): the strip of the next outer block has 4 tile columns, the square rest t (t + 1) / 2 tiles.
+// A rank-1024 update goes through the split-operand kernel (gemm_split.hip) above the sizes that the variant without a workspace takes, which
+// has no planes and gives the same bits; with the last outer block's narrower panel too, whose K is no multiple of anything (in float32 that
+// is the guarded kernel, 200 us an update and 189 for the last column block of the inverse at n = 5000).  At 4096 channels the split
+// products would save 5 % of the factorisation and 10 % of the inverse.
+constexpr int64_t SPLIT_ABOVE = GPTQ_NOALLOC_MAX_N;
 
 struct CholWs { float* dinv; float* T; float* T2; int64_t ld2; float* Uoo; float* tri; float* tri2; unsigned char* planes; unsigned char* planes2; int* flags; size_t total; };
 CholWs chol_ws_layout(void* ws, int64_t n, bool with_split = true) {
@@ -239,20 +242,19 @@ static int chol_run(float* H, int64_t ld, int64_t n, float percdamp, void* ws, i
         // may still be read.
         if (int rc = ts.wait(s4, rows_done)) return rc;
         // (the two run beside each other: what counts is whether they fill the chip together)
-        const bool split = w.planes && ow == OB && split_pays((p0 / 256) * (OB / 256) + (p0 / 256) * (p0 / 256 + 1) / 2);
+        const bool split = w.planes && split_pays((p0 / 256) * (OB / 256) + (p0 / 256) * (p0 / 256 + 1) / 2, n > SPLIT_ABOVE);
         unsigned char* planes = (o & 1) ? w.planes2 : w.planes;
         if (split)
-            if (int rc = launch_split_rows(H + o0, ld, o0, planes, s4)) return rc;
+            if (int rc = launch_split_rows(H + o0, ld, o0, planes, s4, ow)) return rc;
         hipEvent_t panel = nullptr;
         if (int rc = ts.mark(s4, &panel)) return rc;
         if (int rc = ts.wait(s4, before)) return rc;     // it wrote the same columns
         SplitGemm sg{};
         sg.A_planes = sg.B_planes = planes;
-        sg.A_zero = sg.B_zero = planes ? split_zero_block(planes, o0) : nullptr;
-        sg.ldc = ld; sg.alpha = -1.f;
+        sg.ldc = ld; sg.alpha = -1.f; sg.M = p0; sg.K = ow;
         if (split) {
             sg.a_panel0 = 0; sg.b_panel0 = (int)(p0 / 256); sg.C = H + p0;
-            sg.tiles_m = (int)(p0 / 256); sg.tiles_n = (int)(OB / 256);
+            sg.N = OB;
             if (int rc = launch_gemm_split(sg, s4)) return rc;
         } else {
             Opt co; co.nk = true;
@@ -262,7 +264,7 @@ static int chol_run(float* H, int64_t ld, int64_t n, float percdamp, void* ws, i
         if (int rc = ts.wait(s2, panel)) return rc;
         if (split) {
             sg.a_panel0 = sg.b_panel0 = 0; sg.C = H;
-            sg.tiles_m = sg.tiles_n = (int)(p0 / 256);
+            sg.N = p0;
             sg.upper_square = true;
             if (int rc = launch_gemm_split(sg, s2)) return rc;
         } else {
@@ -294,16 +296,16 @@ static int chol_run(float* H, int64_t ld, int64_t n, float percdamp, void* ws, i
         if (k1 < n && k0 > 0) {
             // U[0:k0, k1:n] += U[0:k0, k] (-U_kk R[k, k1:n])   (U[0:k0, k] not yet multiplied by U_kk; the second factor is
             // what the factorisation left in the row block)
-            if (w.planes && kw == OB && (n - k1) % 256 == 0 && split_pays((k0 / 256) * ((n - k1) / 256))) {
+            if (w.planes && split_pays((k0 / 256) * ceil_div(n - k1, 256), n > SPLIT_ABOVE)) {
                 // through the split products; the column block has been read once its pieces are made
                 if (int rc = launch_split_rows(H + k0, ld, k0, w.planes, s)) return rc;
                 if (int rc = ts.mark(s, &read_done)) return rc;
                 marked = true;
                 if (int rc = launch_split_cols(H + k0 * ld + k1, ld, n - k1, w.planes2, s)) return rc;
                 SplitGemm sg{};
-                sg.A_planes = w.planes; sg.A_zero = split_zero_block(w.planes, k0);
-                sg.B_planes = w.planes2; sg.B_zero = split_zero_block(w.planes2, n - k1);
-                sg.C = H + k1; sg.ldc = ld; sg.alpha = 1.f; sg.tiles_m = (int)(k0 / 256); sg.tiles_n = (int)((n - k1) / 256);
+                sg.A_planes = w.planes;
+                sg.B_planes = w.planes2;
+                sg.C = H + k1; sg.ldc = ld; sg.alpha = 1.f; sg.M = k0; sg.N = n - k1; sg.K = OB;
                 if (int rc = launch_gemm_split(sg, s)) return rc;
             } else {
                 Opt u;
@@ -318,7 +320,15 @@ static int chol_run(float* H, int64_t ld, int64_t n, float percdamp, void* ws, i
         hipStream_t sp = last ? s : s2;
         float* Tp = last ? w.T2 : w.T;
         if (!last) { if (int rc = ts.wait(s2, read_done)) return rc; }
-        if (k0 > 0) {
+        if (k0 > 0 && last && w.planes && split_pays((k0 / 256) * ceil_div(kw, 256), n > SPLIT_ABOVE)) {
+            // in place: the column block has been read once its pieces are made
+            if (int rc = launch_split_rows(H + k0, ld, k0, w.planes, s, kw)) return rc;
+            if (int rc = launch_split_cols(Ukk, OB, kw, w.planes2, s, kw)) return rc;
+            SplitGemm sg{};
+            sg.A_planes = w.planes; sg.B_planes = w.planes2;
+            sg.C = H + k0; sg.ldc = ld; sg.alpha = 1.f; sg.M = k0; sg.N = kw; sg.K = kw; sg.overwrite = true; sg.b_upper_tri = true;
+            if (int rc = launch_gemm_split(sg, s)) return rc;
+        } else if (k0 > 0) {
             Opt c; c.overwrite = true; c.btri = true;
             if (int rc = gemm_on(sp, H + k0, ld, Ukk, OB, Tp, OB, k0, kw, kw, 1.f, c)) return rc;
             if (int rc = copy2d(sp, H + k0, ld, Tp, OB, k0, kw)) return rc;

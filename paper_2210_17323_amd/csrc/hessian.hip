@@ -420,7 +420,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         float row[4];
-                        mm.rows64(s, hu, i, row);
+                        mfma_rows64(mm.acc[s] + 4 * hu, i, row);
 #pragma unroll
                         for (int q = 0; q < 4; ++q) pb[(i + 4 * q) * BT] = row[q];
                     }
@@ -438,7 +438,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     float row[4];
-                    mm.rows64(s, hu, i, row);
+                    mfma_rows64(mm.acc[s] + 4 * hu, i, row);
 #pragma unroll
                     for (int q = 0; q < 4; ++q)
                         if (inside || (col < g.n && r + i + 4 * q < g.n)) unsafeAtomicAdd(hb + (i + 4 * q) * g.ldh, 2.0f * row[q]);

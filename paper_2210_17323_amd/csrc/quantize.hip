@@ -122,11 +122,9 @@ static bool factor_form_group_supported(int64_t group) { return group == 0 || gr
 // Trailing updates beyond an outer block are deferred and applied as one rank-1024 GEMM.
 static_assert(QOB == SPLIT_K, "the split products take exactly one outer block as K");
 
-// The deferred rank-1024 updates go through the split-operand kernel (bf16 matrix cores, 256 x 256 tiles, one per
-// workgroup) when columns come in whole tiles and the launch fills the chip well (split_pays).  `r` are the padded rows, so any
-// row count above 128 qualifies.  Measured against 64-bit products on operands of Alg. 1's kind, 96 to 1372 tiles: relative error
-// 1.9e-7 (split) against 5.7e-7 (float32 kernel); from 144 tiles on 193 us against 245, at 128 tiles 195 against 150.  Rows'
-// losses against a 64-bit walk, ragged row counts 2000 .. 16000 and 5120 .. 12288 columns, both forms: the same to 1 % with either.
+// The deferred rank-1024 updates go through the split-operand kernel (bf16 matrix cores, gemm_split.hip) when columns come in whole panels
+// of 256.  `r` are the padded rows, so any row count above 128 qualifies.  They are the faster at every size (4096 x 1024 63 us
+// against 70, 256 x 256 41 against 66) and the closer: relative error against 64-bit products 1.3e-7, 5.7e-7 in float32.
 static bool split_shapes_ok(int64_t r, int64_t n) { return r >= 256 && r % 256 == 0 && n % 256 == 0 && n >= 2 * QOB; }
 
 // Rows of the working matrix and of the error panels in the workspace: whole tiles of the deferred updates, so that a layer
@@ -317,11 +315,11 @@ static int alg1_run(bool rf, const void* W, int wdtype, int64_t ldw, int64_t r, 
             rest_done = nullptr;
             const float alpha = 1.f;                 // the U form's panel holds -e
             const bool full = lay.split && ob == QOB && o1 - o0 == QOB;
-            const bool split_strip = full && o2 - o1 == QOB && split_pays((rows / 256) * (QOB / 256));
-            const bool split_rest = full && o2 < n && split_pays((rows / 256) * ((n - o2) / 256));
+            const bool split_strip = full && o2 - o1 == QOB && split_pays((rows / 256) * (QOB / 256), true);
+            const bool split_rest = full && o2 < n && split_pays((rows / 256) * ((n - o2) / 256), true);
             SplitGemm sg{};
-            sg.A_planes = Pa; sg.A_zero = split_zero_block(Pa, rows); sg.a_panel0 = 0;
-            sg.ldc = lay.ldk; sg.alpha = alpha; sg.tiles_m = (int)(rows / 256);
+            sg.A_planes = Pa; sg.a_panel0 = 0;
+            sg.ldc = lay.ldk; sg.alpha = alpha; sg.M = rows; sg.K = SPLIT_K;
             GemmF32 g{};
             g.A = E; g.lda = QOB; g.B = Bm + o0 * ldb + o1; g.ldb = ldb; g.C = Wk + o1; g.ldc = lay.ldk;
             g.M = rows; g.N = o2 - o1; g.K = o1 - o0; g.alpha = alpha; g.b_is_nk = false; g.overwrite = false;
@@ -331,8 +329,8 @@ static int alg1_run(bool rf, const void* W, int wdtype, int64_t ldw, int64_t r, 
                 if (int rc = launch_split_rows(E, QOB, rows, Pa, s)) return rc;
                 if (int rc = launch_split_cols(Bm + o0 * ldb + o1, ldb, QOB, Pb, s)) return rc;
                 if (int rc = ts.mark(s, &quantized)) return rc;
-                sg.B_planes = Pb; sg.B_zero = split_zero_block(Pb, QOB); sg.b_panel0 = 0;
-                sg.C = Wk + o1; sg.tiles_n = QOB / 256;
+                sg.B_planes = Pb; sg.b_panel0 = 0;
+                sg.C = Wk + o1; sg.N = QOB;
                 if (int rc = launch_gemm_split(sg, s)) return rc;
             } else {
                 if (int rc = launch_gemm_f32(g, s)) return rc;
@@ -346,8 +344,8 @@ static int alg1_run(bool rf, const void* W, int wdtype, int64_t ldw, int64_t r, 
                 if (int rc = ts.wait(s2, quantized)) return rc;
                 if (split_rest) {
                     if (!split_strip) { if (int rc = launch_split_rows(E, QOB, rows, Pa, s2)) return rc; }
-                    sg.B_planes = Pr; sg.B_zero = split_zero_block(Pr, n - o2); sg.b_panel0 = 0;
-                    sg.C = Wk + o2; sg.tiles_n = (int)((n - o2) / 256);
+                    sg.B_planes = Pr; sg.b_panel0 = 0;
+                    sg.C = Wk + o2; sg.N = n - o2;
                     if (int rc = launch_gemm_split(sg, s2)) return rc;
                 } else {
                     g.B = Bm + o0 * ldb + o2; g.C = Wk + o2; g.N = n - o2;

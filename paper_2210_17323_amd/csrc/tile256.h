@@ -31,6 +31,22 @@ __device__ __forceinline__ void mfma_settle(floatx4& a, floatx4& b, floatx4& c, 
     asm volatile("s_nop 15\n\ts_nop 3" : "+a"(a), "+a"(b), "+a"(c), "+a"(d));
 }
 
+// Rows i, i + 4, i + 8, i + 12 of a 16 x 64 strip of results, four accumulators side by side, a row over the 64 lanes: 256 bytes in a row for
+// the memory system, where the accumulators as they lie are four rows of 64.
+__device__ __forceinline__ void mfma_rows64(const floatx4* acc, int i, float (&row)[4]) {
+    uint32_t x[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) x[q] = __float_as_uint(acc[q][i]);
+    const auto a = __builtin_amdgcn_permlane16_swap(x[0], x[1], false, false);      // columns 0 .. 31: rows i and i + 8, i + 4 and i + 12
+    const auto b = __builtin_amdgcn_permlane16_swap(x[2], x[3], false, false);      // columns 32 .. 63
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const auto c = __builtin_amdgcn_permlane32_swap(a[q], b[q], false, false);
+        row[q] = __uint_as_float(c[0]);
+        row[q + 2] = __uint_as_float(c[1]);
+    }
+}
+
 // A stage holds a step of 32 k of both operands, A's panel of 256 rows and behind it B's: rows of 64 bytes, the 16-byte chunk c of
 // row r at position c ^ ((r / 4) % 4), so that 16 consecutive rows, what 16 lanes of a 16-byte read touch together, fall on
 // all 16 bank quads.
@@ -89,21 +105,6 @@ struct Tile256Lane {
         quarter(1, 0, [&](int i) { fetchB(cur, 4 + i); }, [&](int i) { copy(2 + i); });
         quarter(0, 1, [&](int i) { fetchB(nxt, i); }, [&](int i) { copy(4 + i); });
         quarter(1, 1, [&](int i) { fetchA(nxt, i); }, [&](int i) { copy(6 + i); });
-    }
-    // Rows i, i + 4, i + 8, i + 12 of the 16 x 64 results (s, columns 64 hu ...), a row over the 64 lanes: 256 bytes in a row for the
-    // memory system, where the accumulators as they lie are four rows of 64.
-    __device__ __forceinline__ void rows64(int s, int hu, int i, float (&row)[4]) {
-        uint32_t x[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) x[q] = __float_as_uint(acc[s][4 * hu + q][i]);
-        const auto a = __builtin_amdgcn_permlane16_swap(x[0], x[1], false, false);      // columns 0 .. 31: rows i and i + 8, i + 4 and i + 12
-        const auto b = __builtin_amdgcn_permlane16_swap(x[2], x[3], false, false);      // columns 32 .. 63
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const auto c = __builtin_amdgcn_permlane32_swap(a[q], b[q], false, false);
-            row[q] = __uint_as_float(c[0]);
-            row[q + 2] = __uint_as_float(c[1]);
-        }
     }
     // before the accumulators are read: the last quarter's results
     __device__ __forceinline__ void settle() {
