@@ -260,13 +260,15 @@ static int alg1_run(bool rf, const void* W, int wdtype, int64_t ldw, int64_t r, 
         Bm = Rt; ldb = lay.ldk;
     }
 
-    unsigned char* Pa = reinterpret_cast<unsigned char*>(base + lay.pa);
-    unsigned char* Pb = reinterpret_cast<unsigned char*>(base + lay.pb);
-    unsigned char* Pr = reinterpret_cast<unsigned char*>(base + lay.pr);
     // Lazy batching at two levels (Section 3, Step 2 applied twice): inside an outer block of 1024 columns
     // each 128-column block updates only the rest of the outer block (rank 128, inside the strip kernel); the columns
     // beyond it get one rank-1024 update per outer block.  Same sums as Alg. 1, associated differently.
     const int64_t ob = alg1_outer_block(group);
+    // With the split products the strip kernel writes the error panel as their pieces, in turn into two places (the room of the float32
+    // panels is one of them), and the pieces of an outer block's rows of U are made ahead on the helper stream.  One decision for the call.
+    const bool split = lay.split && ob == QOB && n > QOB && split_pays((rows / 256) * (QOB / 256), true);
+    unsigned char* Pe[2] = {reinterpret_cast<unsigned char*>(base + lay.pa), reinterpret_cast<unsigned char*>(base + lay.e)};
+    unsigned char* Pu = reinterpret_cast<unsigned char*>(base + lay.pr);
     // Look-ahead: after an outer block is quantized, the columns of the next outer block are updated first, on
     // the caller's stream, which goes straight on to quantize them (short, serial kernels); all columns
     // beyond are updated on the helper stream meanwhile.  The two updates and the next block's kernels touch
@@ -276,6 +278,11 @@ static int alg1_run(bool rf, const void* W, int wdtype, int64_t ldw, int64_t r, 
     if (int rc = ts.open(s, n > 2 * ob ? 1 : 0)) return rc;        // up to two outer blocks nothing is updated beyond the next one
     hipStream_t s2 = ts.side[0];
     hipEvent_t rest_done = nullptr;         // the helper stream's last trailing update, if one is pending
+    hipEvent_t factor_split = nullptr;      // ... and the pieces of U's rows for the updates that come next
+    if (split) {
+        if (int rc = launch_split_cols(Bm + ob, ldb, n - ob, Pu, s2)) return rc;
+        if (int rc = ts.mark(s2, &factor_split)) return rc;
+    }
     const bool outer_groups = group > QB && (ob == QB || group > QOB);      // groups that the strip kernel does not see whole
     float* packed = reinterpret_cast<float*>(base + lay.pk);
     StripArgs strip{};
@@ -305,7 +312,8 @@ static int alg1_run(bool rf, const void* W, int wdtype, int64_t ldw, int64_t r, 
         strip.pairs = packed + STRIP_PACK_DIAG_BYTES / sizeof(float) + (in_pack / QOB) * (int64_t)(STRIP_PAIR_BYTES / sizeof(float));
         strip.o0 = o0; strip.o1 = o1;
         strip.S = (rf && o0 == 0) ? nullptr : Wk;               // the accumulators start at zero
-        strip.E = o1 < n ? E : nullptr;
+        strip.E = o1 < n && !split ? E : nullptr;
+        strip.E_planes = o1 < n && split ? Pe[eb] : nullptr;
         if (int rc = launch_alg1_strip(rf, hybrid, strip, s)) return rc;
         if (o1 < n) {
             const int64_t o2 = std::min<int64_t>(o1 + ob, n);
@@ -314,37 +322,25 @@ static int alg1_run(bool rf, const void* W, int wdtype, int64_t ldw, int64_t r, 
             if (int rc = ts.wait(s, rest_done)) return rc;      // it wrote the columns from o1 on
             rest_done = nullptr;
             const float alpha = 1.f;                 // the U form's panel holds -e
-            const bool full = lay.split && ob == QOB && o1 - o0 == QOB;
-            const bool split_strip = full && o2 - o1 == QOB && split_pays((rows / 256) * (QOB / 256), true);
-            const bool split_rest = full && o2 < n && split_pays((rows / 256) * ((n - o2) / 256), true);
             SplitGemm sg{};
-            sg.A_planes = Pa; sg.a_panel0 = 0;
+            sg.A_planes = Pe[eb]; sg.B_planes = Pu;
             sg.ldc = lay.ldk; sg.alpha = alpha; sg.M = rows; sg.K = SPLIT_K;
             GemmF32 g{};
             g.A = E; g.lda = QOB; g.B = Bm + o0 * ldb + o1; g.ldb = ldb; g.C = Wk + o1; g.ldc = lay.ldk;
             g.M = rows; g.N = o2 - o1; g.K = o1 - o0; g.alpha = alpha; g.b_is_nk = false; g.overwrite = false;
-            if (split_strip) {
-                // the pieces of the error panel are made here, for both parts (the helper stream's last reader of the
-                // buffer is what the wait above was for); those of U's rows for the next outer block's columns as well
-                if (int rc = launch_split_rows(E, QOB, rows, Pa, s)) return rc;
-                if (int rc = launch_split_cols(Bm + o0 * ldb + o1, ldb, QOB, Pb, s)) return rc;
-                if (int rc = ts.mark(s, &quantized)) return rc;
-                sg.B_planes = Pb; sg.b_panel0 = 0;
-                sg.C = Wk + o1; sg.N = QOB;
+            hipEvent_t next_done = nullptr;
+            if (split) {
+                if (int rc = ts.wait(s, factor_split)) return rc;
+                sg.C = Wk + o1; sg.N = o2 - o1;
                 if (int rc = launch_gemm_split(sg, s)) return rc;
+                if (int rc = ts.mark(s, &next_done)) return rc;
             } else {
                 if (int rc = launch_gemm_f32(g, s)) return rc;
             }
             if (o2 < n) {
-                if (split_rest) {
-                    // U's rows for all columns beyond depend on nothing of this outer block: they are split before the helper
-                    // stream waits for it (the buffer's last reader, the previous rest update, precedes this on the stream)
-                    if (int rc = launch_split_cols(Bm + o0 * ldb + o2, ldb, n - o2, Pr, s2)) return rc;
-                }
                 if (int rc = ts.wait(s2, quantized)) return rc;
-                if (split_rest) {
-                    if (!split_strip) { if (int rc = launch_split_rows(E, QOB, rows, Pa, s2)) return rc; }
-                    sg.B_planes = Pr; sg.b_panel0 = 0;
+                if (split) {
+                    sg.b_panel0 = (int)((o2 - o1) / 256);
                     sg.C = Wk + o2; sg.N = n - o2;
                     if (int rc = launch_gemm_split(sg, s2)) return rc;
                 } else {
@@ -352,6 +348,12 @@ static int alg1_run(bool rf, const void* W, int wdtype, int64_t ldw, int64_t r, 
                     if (int rc = launch_gemm_f32(g, s2)) return rc;
                 }
                 if (int rc = ts.mark(s2, &rest_done)) return rc;
+                if (split) {
+                    // the next outer block's, into the same place: both of its readers are through
+                    if (int rc = ts.wait(s2, next_done)) return rc;
+                    if (int rc = launch_split_cols(Bm + o1 * ldb + o2, ldb, n - o2, Pu, s2)) return rc;
+                    if (int rc = ts.mark(s2, &factor_split)) return rc;
+                }
             }
         }
     }

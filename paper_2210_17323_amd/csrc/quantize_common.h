@@ -44,6 +44,7 @@ struct StripArgs {
     int64_t wide_group;             // group size if groups span 2, 4 or 8 blocks of an outer block, else 0
     uint8_t* codes; int64_t ldc;
     float* E; int64_t lde;          // out: -e (U form) or d = w - q of this outer block [r x 1024]; null: not wanted
+    unsigned char* E_planes;        // ... as the pieces of the split products instead (split_planes.h); null: not wanted
     double* half_e2;
 };
 // Packs the outer blocks from column j_first on (a multiple of STRIP_PACK_OUTER * 1024) into STRIP_PACK_BYTES bytes: diagonal

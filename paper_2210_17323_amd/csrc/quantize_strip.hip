@@ -19,6 +19,7 @@
 // forms).  With updates and walk one behind the other and a multiply-add per lane and column in the walk it took 144 / 181 / 232: Alg. 1 on a
 // 4096 x 4096 layer 1.07 -> 0.84 ms, 3000 x 5120 in groups of 1024 1.48 -> 1.17 ms, 14336 x 14336 in groups of 128 20.9 -> 20.2 ms.
 #include "quantize_common.h"
+#include "split_planes.h"
 
 #include <utility>
 
@@ -617,6 +618,18 @@ __global__ __launch_bounds__(64 * STRIP_WAVES) void alg1_strip_kernel(StripArgs 
             for (int rt = 0; rt < RT; ++rt) acc[j + base][rt] += sum[rt];
         }
     };
+    // a block's errors to memory, as they are or as the pieces that the update beyond the outer block multiplies
+    auto write_errors = [&](int b) {
+        if (!g.E && !g.E_planes) return;
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            const int q = utid + 64 * UPDATERS * t, rr = q >> 5, k = (q & 31) * 4;
+            if (row0 + rr >= g.r) continue;
+            const floatx4 e = *reinterpret_cast<const floatx4*>(&ebuf[b & 1][rr * PW + k]);
+            if (g.E_planes) store_pieces(g.E_planes, row0 + rr, b * QB + k, make_float4(e[0], e[1], e[2], e[3]));
+            else *reinterpret_cast<floatx4*>(g.E + (row0 + rr) * g.lde + b * QB + k) = e;
+        }
+    };
     if (u == 0 && lane < RT) walked[lane] = 0;
     load_diag(0);
     load_orig(g.o0);
@@ -657,13 +670,7 @@ __global__ __launch_bounds__(64 * STRIP_WAVES) void alg1_strip_kernel(StripArgs 
             load_orig(j0 + QB);
         }
         // block b - 1's errors to memory
-        if (b > 0 && g.E) {
-#pragma unroll
-            for (int t = 0; t < RT; ++t) {
-                const int q = utid + 64 * UPDATERS * t, rr = q >> 5, k = (q & 31) * 4;
-                if (row0 + rr < g.r) *reinterpret_cast<floatx4*>(g.E + (row0 + rr) * g.lde + (b - 1) * QB + k) = *reinterpret_cast<const floatx4*>(&ebuf[(b - 1) & 1][rr * PW + k]);
-            }
-        }
+        if (b > 0) write_errors(b - 1);
         // the deferred products, then, as they come, the walked tiles' into the next block; those of the last are left for behind the walk
         units(b - 1, std::integral_constant<int, 0>{}, n_units);
         if (later > 0)
@@ -690,13 +697,7 @@ __global__ __launch_bounds__(64 * STRIP_WAVES) void alg1_strip_kernel(StripArgs 
             __builtin_amdgcn_s_waitcnt(0x0F70);         // vmcnt(0): the next block's matrix is in LDS (the next barrier publishes it)
         }
     }
-    if (g.E) {                                          // the last block's errors
-#pragma unroll
-        for (int t = 0; t < RT; ++t) {
-            const int q = utid + 64 * UPDATERS * t, rr = q >> 5, k = (q & 31) * 4;
-            if (row0 + rr < g.r) *reinterpret_cast<floatx4*>(g.E + (row0 + rr) * g.lde + (nblocks - 1) * QB + k) = *reinterpret_cast<const floatx4*>(&ebuf[(nblocks - 1) & 1][rr * PW + k]);
-        }
-    }
+    write_errors(nblocks - 1);
 }
 
 template <int FORM, int RT>
