@@ -176,6 +176,18 @@ static int chol_run(float* H, int64_t ld, int64_t n, float percdamp, void* ws, i
         return GPTQ_OK;
     };
     const int64_t nouter = ceil_div(n, OB);
+    // The products of the inverse as split products: the column blocks' pieces lie in turn in the planes of the factorisation and in the
+    // two float32 panels, which have room for those of a diagonal block's inverse behind them (from 4096 channels on always).  The pieces of a
+    // column block are made once, for the update and for the product with U_kk, which with overwriting needs no copy back: that product was 70
+    // to 150 us of float32 on the other stream, which ended last, and T of the first outer block 50 us before the inverse could start.
+    // Inverse, us, with the update alone split / all: n = 5000 2090 / 1900, 6144 2770 / 2510, 8192 4260 / 4090, 12288 9920 / 9500; error
+    // against 64 bits at n = 5000 4.1e-7 / 3.2e-7.
+    unsigned char* const panels = reinterpret_cast<unsigned char*>(w.T);
+    const size_t panel_planes = round_up(split_planes_bytes((nouter - 1) * OB), 256);
+    const bool inverse_split = want_inverse && w.planes && nouter > 1 && split_pays(4 * (nouter - 1), n > SPLIT_ABOVE) &&
+                               panel_planes + split_planes_bytes(OB) <= (size_t)(reinterpret_cast<unsigned char*>(w.Uoo) - panels);
+    unsigned char* const column_planes[2] = {w.planes, panels};
+    unsigned char* const diag_planes = panels + panel_planes;
     HelperStreams ts;
     if (int rc = ts.open(s, lookahead && nouter > 1 ? (want_inverse ? 3 : 2) : 0)) return rc;
     hipStream_t s2 = ts.side[0];    // rank-1024 updates left of the next outer block but one
@@ -212,7 +224,15 @@ static int chol_run(float* H, int64_t ld, int64_t n, float percdamp, void* ws, i
             if (int rc = ts.wait(s3, chain)) return rc;
             if (int rc = launch_pack_triangle(H, ld, n, dinv, o, w.tri, s3)) return rc;
             if (int rc = launch_triangle_inverse(w.tri, n, o, Ublk, s3)) return rc;
-            if (o1 < n) {
+            if (o1 < n && o == 0 && inverse_split) {
+                // the last one, which the inverse waits for; the planes' readers are behind the chain just walked
+                if (int rc = launch_split_rows(Ublk, OB, ow, w.planes, s3)) return rc;
+                if (int rc = launch_split_cols(H + o1, ld, n - o1, w.planes2, s3)) return rc;
+                SplitGemm sg{};
+                sg.A_planes = w.planes; sg.B_planes = w.planes2;
+                sg.C = H + o1; sg.ldc = ld; sg.alpha = -1.f; sg.M = ow; sg.N = n - o1; sg.K = OB; sg.overwrite = true;
+                if (int rc = launch_gemm_split(sg, s3)) return rc;
+            } else if (o1 < n) {
                 Opt a; a.overwrite = true; a.atri = true;
                 if (int rc = gemm_on(s3, Ublk, OB, H + o0 * ld + o1, ld, w.T2, w.ld2, ow, n - o1, ow, -1.f, a)) return rc;
                 if (int rc = ts.wait(s3, strip_done)) return rc;
@@ -288,50 +308,55 @@ static int chol_run(float* H, int64_t ld, int64_t n, float percdamp, void* ws, i
 
     // ---- U = R^-1 in place, right-looking over the outer block columns --------------------------------------------
     hipEvent_t panel_done = nullptr;     // s2: the last column panel, which reuses T
+    hipEvent_t planes_free[2] = {};      // s2: the last product that reads the column planes
     for (int64_t k = 0; k < nouter; ++k) {
         const int64_t k0 = k * OB, k1 = std::min<int64_t>(k0 + OB, n), kw = k1 - k0;
         const float* Ukk = w.Uoo + k * (int64_t)OB * OB;
+        unsigned char* const cp = column_planes[k & 1];
         hipEvent_t read_done = nullptr;  // s: the column block above k has been read by this step's update
-        bool marked = false;
-        if (k1 < n && k0 > 0) {
-            // U[0:k0, k1:n] += U[0:k0, k] (-U_kk R[k, k1:n])   (U[0:k0, k] not yet multiplied by U_kk; the second factor is
-            // what the factorisation left in the row block)
-            if (w.planes && split_pays((k0 / 256) * ceil_div(n - k1, 256), n > SPLIT_ABOVE)) {
-                // through the split products; the column block has been read once its pieces are made
-                if (int rc = launch_split_rows(H + k0, ld, k0, w.planes, s)) return rc;
-                if (int rc = ts.mark(s, &read_done)) return rc;
-                marked = true;
-                if (int rc = launch_split_cols(H + k0 * ld + k1, ld, n - k1, w.planes2, s)) return rc;
-                SplitGemm sg{};
-                sg.A_planes = w.planes;
-                sg.B_planes = w.planes2;
-                sg.C = H + k1; sg.ldc = ld; sg.alpha = 1.f; sg.M = k0; sg.N = n - k1; sg.K = OB;
-                if (int rc = launch_gemm_split(sg, s)) return rc;
-            } else {
+        if (k0 > 0 && inverse_split) {
+            // its pieces serve the update and the product with U_kk
+            if (int rc = ts.wait(s, planes_free[k & 1])) return rc;
+            if (int rc = launch_split_rows(H + k0, ld, k0, cp, s, kw)) return rc;
+        }
+        if (k0 > 0 && inverse_split && k1 < n) {
+            if (int rc = ts.mark(s, &read_done)) return rc;
+            if (int rc = launch_split_cols(H + k0 * ld + k1, ld, n - k1, w.planes2, s)) return rc;
+            SplitGemm sg{};
+            sg.A_planes = cp; sg.B_planes = w.planes2;
+            sg.C = H + k1; sg.ldc = ld; sg.alpha = 1.f; sg.M = k0; sg.N = n - k1; sg.K = OB;
+            if (int rc = launch_gemm_split(sg, s)) return rc;
+        } else {
+            if (k1 < n && k0 > 0) {
+                // U[0:k0, k1:n] += U[0:k0, k] (-U_kk R[k, k1:n])   (U[0:k0, k] not yet multiplied by U_kk; the second factor is
+                // what the factorisation left in the row block)
                 Opt u;
                 if (int rc = gemm_on(s, H + k0, ld, H + k0 * ld + k1, ld, H + k1, ld, k0, n - k1, kw, 1.f, u)) return rc;
             }
+            if (int rc = ts.mark(s, &read_done)) return rc;
         }
-        if (!marked) { if (int rc = ts.mark(s, &read_done)) return rc; }
-        // On the other stream: U[0:k0, k] <- U[0:k0, k] U_kk through T, and the diagonal block.  Nothing later reads them.
-        // The last column block has no update after it: it stays on the caller's stream, with the row-panel buffer (free
-        // by now) for its product, beside the last but one on the other stream.
+        // On the other stream: U[0:k0, k] <- U[0:k0, k] U_kk, and the diagonal block.  Nothing later reads them.
+        // The last column block has no update after it: it stays on the caller's stream (in float32 through the row-panel buffer, free
+        // by now), beside the last but one on the other stream.
         const bool last = (k == nouter - 1) && nouter > 1;
         hipStream_t sp = last ? s : s2;
-        float* Tp = last ? w.T2 : w.T;
-        if (!last) { if (int rc = ts.wait(s2, read_done)) return rc; }
-        if (k0 > 0 && last && w.planes && split_pays((k0 / 256) * ceil_div(kw, 256), n > SPLIT_ABOVE)) {
-            // in place: the column block has been read once its pieces are made
-            if (int rc = launch_split_rows(H + k0, ld, k0, w.planes, s, kw)) return rc;
-            if (int rc = launch_split_cols(Ukk, OB, kw, w.planes2, s, kw)) return rc;
+        if (k0 > 0 && inverse_split) {
+            unsigned char* const up = last ? w.planes2 : diag_planes;
+            if (int rc = launch_split_cols(Ukk, OB, kw, up, sp, kw)) return rc;
+            if (!last) { if (int rc = ts.wait(s2, read_done)) return rc; }
             SplitGemm sg{};
-            sg.A_planes = w.planes; sg.B_planes = w.planes2;
+            sg.A_planes = cp; sg.B_planes = up;
             sg.C = H + k0; sg.ldc = ld; sg.alpha = 1.f; sg.M = k0; sg.N = kw; sg.K = kw; sg.overwrite = true; sg.b_upper_tri = true;
-            if (int rc = launch_gemm_split(sg, s)) return rc;
-        } else if (k0 > 0) {
-            Opt c; c.overwrite = true; c.btri = true;
-            if (int rc = gemm_on(sp, H + k0, ld, Ukk, OB, Tp, OB, k0, kw, kw, 1.f, c)) return rc;
-            if (int rc = copy2d(sp, H + k0, ld, Tp, OB, k0, kw)) return rc;
+            if (int rc = launch_gemm_split(sg, sp)) return rc;
+            if (!last) { if (int rc = ts.mark(s2, &planes_free[k & 1])) return rc; }
+        } else {
+            if (!last) { if (int rc = ts.wait(s2, read_done)) return rc; }
+            if (k0 > 0) {
+                float* Tp = last ? w.T2 : w.T;
+                Opt c; c.overwrite = true; c.btri = true;
+                if (int rc = gemm_on(sp, H + k0, ld, Ukk, OB, Tp, OB, k0, kw, kw, 1.f, c)) return rc;
+                if (int rc = copy2d(sp, H + k0, ld, Tp, OB, k0, kw)) return rc;
+            }
         }
         hipLaunchKernelGGL(copy_block_kernel, dim3(256), dim3(256), 0, sp, H + k0 * ld + k0, ld, Ukk, (int64_t)OB, kw, (int)kw, 1);
         GPTQ_LAUNCH_CHECK();

@@ -102,6 +102,32 @@ def test_rows_above_an_outer_block(n):
     assert worst <= 4 * EPS * np.sqrt(n)    # ... each at most the product of two rows' norms, the roots of the diagonal
 
 
+@pytest.mark.parametrize("n", [5120, 7172])
+def test_inverse_over_many_outer_blocks(n):
+    """Outer blocks enough for every buffer of the inverse's products to be taken again, the last one whole or of 4 columns: U (H + lambda I)
+    U^T against the identity, in float64 on the GPU."""
+    from paper_2210_17323_amd import solver as S
+    print(f"inverse n={n}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    A = torch.randn((n, 512), generator=gen, device="cuda", dtype=torch.float64)
+    Hd = A @ A.T
+    Hd.diagonal().add_(512.0)
+    U = Hd.float()
+    Hd = U.double()
+    S.cholesky_inverse(U, 0.0)
+    U = U.double()
+    assert int(torch.tril(U, -1).count_nonzero()) == 0
+    res = U @ Hd @ U.T
+    res.diagonal().sub_(1.0)
+    # the factor's and the inverse's rounding, each a sum of up to n terms in units of the diagonal, through the matrix's condition number
+    ev = torch.linalg.eigvalsh((A.T @ A).cpu())
+    cond = float((ev[-1] + 512.0) / 512.0)
+    worst, rel = float(res.abs().max()), float(res.norm() / np.sqrt(n))
+    print(f"  worst element {worst:.3e}, rms by row {rel:.3e}, condition {cond:.1f}", flush=True)
+    assert worst <= 4 * EPS * np.sqrt(n) * cond
+    assert rel <= EPS * np.sqrt(n) * cond
+
+
 @pytest.mark.parametrize("n,column", [(300, 0), (300, 127), (300, 128), (300, 299), (1100, 1024), (1100, 1023), (1100, 17)])
 def test_first_non_positive_pivot(n, column):
     """The pivots are taken from the last column backwards; the first bad one is reported, counted from 1."""
