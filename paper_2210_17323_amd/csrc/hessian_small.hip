@@ -3,14 +3,15 @@
 // A matrix of few tiles leaves most of the chip idle and walks all tokens in one long chain per tile (256 channels:
 // 2 tiles of 256 x 128 on 256 CUs, 4096 float32 tokens in 471 us).  Here the tile is small -- T x T, T = 64, 32 or 16 -- and the
 // wavefronts of a workgroup share the tokens of ONE tile: wavefront w multiplies chunks w, w + WAVES, .. of CHUNK tokens,
-// operands straight from memory into registers (the next chunk's loads are in flight while this one is multiplied), and
+// the next chunk's operands on their way while this one is multiplied, and
 // the partial tiles are added through LDS in a fixed order, so a call gives the same bits every time.
-// Bound: the vector cache.  A matrix operand has a different row in every neighbouring lane, so a load instruction touches
-// 16 rows x 64 bytes and moves ~20 bytes per cycle and CU (215 TFLOP/s at 2000 float16 channels, 70 at float32); tiles shared
-// through LDS reach three times that rate but need the tiles of ~2000 channels to fill the chip, and a workspace to split the
-// token range any further.
-// Measured (a call, before -> after): float32 256 channels x 4096 tokens 472 -> 20 us, 1000 x 16384 1483 -> 480, 3000 x 8192
-// 1240 -> 1150; float16 512 x 32768 551 -> 119, 1000 x 131072 2140 -> 890, 1536 x 65536 1080 -> 900.
+// Bound: the vector cache.  A matrix operand has a different row in every neighbouring lane, so a load straight into registers touches
+// 16 rows x 64 bytes, half cache lines, and moves ~20 bytes per cycle and CU.  So a wavefront copies whole lines of its chunk, 8
+// rows x 128 bytes an instruction, into LDS of its own and takes the operands from there; the order of the sums, and the bits, are the same.
+// Measured, us, straight / through LDS: float16 256 channels x 4096 tokens 11.8 / 6.2, 512 x 16384 62 / 26, 1000 x 16384 117 / 51, 1536 x 16384
+// 234 / 115 (350 TFLOP/s on its whole tiles' flops); float32 256 x 4096 19.3 / 13.1, 352 x 16384 62 / 41.  Straight stays the float32 tiles of 32 and
+// 64 (512 x 16384 140 / 153, 1000 x 16384 478 / 571: they are held by the float32 instructions, one chunk in LDS is too little ahead), and calls of
+// up to three chunks, most of them their own latency (1536 x 128 9.1 / 9.7, x 64 7.8 / 9.0, x 256 12.5 / 10.2).
 #include "hessian_small.h"
 
 namespace gptq {
@@ -32,7 +33,11 @@ __global__ __launch_bounds__(64 * WAVES) void syrk_small_kernel(SmallArgs g) {
     constexpr int CHUNK = PER * 4 * EL;                      // 64 tokens, or 32 of float32
     constexpr int S = T / 16;                                // 16 x 16 tiles per side
     constexpr int SLOT = T * T * 4;
-    __shared__ __attribute__((aligned(16))) unsigned char part[WAVES * SLOT];
+    constexpr bool THROUGH_LDS = SZ == 2 || T == 16;
+    constexpr int U = T == 16 ? 2 : 1;                       // chunks of a wavefront that are copied at a time
+    constexpr int OPERAND = T * 128, STAGE = THROUGH_LDS ? U * 2 * OPERAND : SLOT;    // 128 bytes of T rows; A and B
+    static_assert(SLOT <= STAGE, "the partial tiles take the place of the operands");
+    __shared__ __attribute__((aligned(16))) unsigned char lds[WAVES * STAGE];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l16 = lane & 15, kq = lane >> 4;
@@ -40,15 +45,51 @@ __global__ __launch_bounds__(64 * WAVES) void syrk_small_kernel(SmallArgs g) {
     int bj = 0, bi = (int)blockIdx.x;
     while (bi > bj) { bi -= bj + 1; ++bj; }
 
+    // Rows past n repeat the last one: they only feed outputs that are not stored.
+    const char* base = static_cast<const char*>(g.X);
+    auto row_at = [&](int64_t row) { return base + min(row, g.n - 1) * g.ldx * SZ; };
     const char* rowA[S];
     const char* rowB[S];
 #pragma unroll
-    for (int s = 0; s < S; ++s) {                            // rows past n repeat the last one: they only feed outputs that are not stored
-        rowA[s] = static_cast<const char*>(g.X) + min((int64_t)bi * T + 16 * s + l16, g.n - 1) * g.ldx * SZ + kq * 16;
-        rowB[s] = static_cast<const char*>(g.X) + min((int64_t)bj * T + 16 * s + l16, g.n - 1) * g.ldx * SZ + kq * 16;
+    for (int s = 0; s < S; ++s) {
+        rowA[s] = row_at((int64_t)bi * T + 16 * s + l16) + kq * 16;
+        rowB[s] = row_at((int64_t)bj * T + 16 * s + l16) + kq * 16;
     }
+    // A copy moves 8 rows x 128 bytes, whole cache lines, lane l position l % 8 of row l / 8: the chunk (l % 8) ^ (row / 2 % 8), so that 16
+    // rows at the same chunk, what 16 lanes of a read touch together, lie in different banks
+    const char* srcA[2 * S];
+    const char* srcB[2 * S];
+#pragma unroll
+    for (int j = 0; j < 2 * S; ++j) {
+        const int r = 8 * j + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
+        srcA[j] = row_at((int64_t)bi * T + r) + c * 16;
+        srcB[j] = row_at((int64_t)bj * T + r) + c * 16;
+    }
+    unsigned char* const stage = lds + __builtin_amdgcn_readfirstlane(wave) * STAGE;
+    auto copy = [&](int64_t chunk, int u) {
+        const int64_t off = chunk * (CHUNK * SZ);
+#pragma unroll
+        for (int j = 0; j < 2 * S; ++j) {
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(srcA[j] + off),
+                                             (__attribute__((address_space(3))) void*)(stage + 2 * u * OPERAND + j * 1024), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(srcB[j] + off),
+                                             (__attribute__((address_space(3))) void*)(stage + (2 * u + 1) * OPERAND + j * 1024), 16, 0, 0);
+        }
+    };
     uint4 a[2][S][PER], b[2][S][PER];
-    // a whole chunk; no branch around it, so that the wait for one buffer does not wait for the other's loads
+    auto fetch = [&]() {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+#pragma unroll
+                for (int i = 0; i < PER; ++i) {
+                    const int at = (16 * s + l16) * 128 + (((4 * i + kq) ^ ((l16 >> 1) & 7)) << 4);
+                    a[u][s][i] = *reinterpret_cast<const uint4*>(stage + 2 * u * OPERAND + at);
+                    b[u][s][i] = *reinterpret_cast<const uint4*>(stage + (2 * u + 1) * OPERAND + at);
+                }
+    };
+    // ... or straight into registers: a whole chunk, no branch around it, so that the wait for one buffer does not wait for the other's loads
     auto load = [&](int64_t chunk, int buf) {
         const int64_t off = chunk * (CHUNK * SZ);
 #pragma unroll
@@ -113,28 +154,52 @@ __global__ __launch_bounds__(64 * WAVES) void syrk_small_kernel(SmallArgs g) {
             }
         }
     };
-    auto multiply = [&](int buf) { products(a[buf], b[buf]); };
     const int64_t chunks = g.t / CHUNK;
-    if (wave < chunks) {
+    const bool through_lds = THROUGH_LDS && chunks > 3;
+    // A wavefront's copies are its own business, no barrier: it waits for them, takes the operands into registers, and has the next ones
+    // on their way while it multiplies.  (Past its last chunk the last of all is copied again.)
+    if (!through_lds && wave < chunks) {
         const int64_t last = chunks - 1;
         load(wave, 0);
         for (int64_t c = wave; c < chunks; c += 2 * WAVES) {
             load(min(c + WAVES, last), 1);
             __builtin_amdgcn_sched_barrier(0);
-            multiply(0);
+            products(a[0], b[0]);
             if (c + WAVES >= chunks) break;
             __builtin_amdgcn_sched_barrier(0);
             load(min(c + 2 * WAVES, last), 0);
             __builtin_amdgcn_sched_barrier(0);
-            multiply(1);
+            products(a[1], b[1]);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
+    if (through_lds && wave < chunks) {
+        const int64_t last = chunks - 1;
+#pragma unroll
+        for (int u = 0; u < U; ++u) copy(min((int64_t)wave + u * WAVES, last), u);
+        for (int64_t c = wave; c < chunks; c += U * WAVES) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            fetch();
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+            for (int u = 0; u < U; ++u) copy(min(c + (U + u) * WAVES, last), u);
+            __builtin_amdgcn_sched_barrier(0);
+            products(a[0], b[0]);
+            if (U > 1 && c + WAVES < chunks) products(a[U - 1], b[U - 1]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
     if (g.t % CHUNK != 0 && wave == WAVES - 1) {
 #pragma unroll
-        for (int s = 0; s < S; ++s) { load_tail(rowA[s], chunks * CHUNK, a[0][s]); load_tail(rowB[s], chunks * CHUNK, b[0][s]); }
-        multiply(0);
+        for (int s = 0; s < S; ++s) {
+            load_tail(rowA[s], chunks * CHUNK, a[0][s]);
+            load_tail(rowB[s], chunks * CHUNK, b[0][s]);
+        }
+        products(a[0], b[0]);
     }
+    if (through_lds) __syncthreads();                        // everybody has read the operands whose place the partial tiles take
+    unsigned char* const part = lds;
     // every wavefront leaves its partial tile in LDS, then takes its share of the tile: the partial sums of an element are
     // added in the order of the wavefronts
     floatx4* mine = reinterpret_cast<floatx4*>(part + wave * SLOT);
@@ -165,9 +230,11 @@ template <int TYPE>
 int launch(const SmallArgs& a, hipStream_t s) {
     const int64_t n64 = ceil_div(a.n, 64), n32 = ceil_div(a.n, 32);
     const int64_t n16 = ceil_div(a.n, 16);
-    // The smallest tile while every CU has at most one: half the bytes a tile reads.  us, 16 x 16 / 32 x 32, float32 (float16): 4096 tokens of 64 channels 18.7 / 37.2
-    // (11.8 / 19.9), 352 19.9 / 39.5 (12.5 / 20.4), 400 35.6 / 39.7 (21.4 / 20.8), 512 52 / 40; 16384 of 352 61 / 141 (34 / 62), 400 118 / 141 (63 / 62).
-    if (n64 * (n64 + 1) / 2 >= 128) {
+    // The smallest tile while every CU has at most one: half the bytes a tile reads.  us, 16 x 16 / 32 x 32, both straight, float32 (float16): 4096 tokens of 64 channels
+    // 18.7 / 37.2 (11.8 / 19.9), 352 19.9 / 39.5 (12.5 / 20.4), 400 35.6 / 39.7 (21.4 / 20.8), 512 52 / 40; 16384 of 352 61 / 141 (34 / 62), 400 118 / 141 (63 / 62).
+    // Tiles of 64, 16-bit: as soon as those of 32 are more than one a CU (32 x 32 / 64 x 64: 8192 tokens of 712 28.2 / 26.7, 800 30.4 / 26.8, 960 36.8 / 27.9, 64 tokens of 900
+    // 7.2 / 6.0; at 700, 253 tiles of 32, these are ahead).
+    if (TYPE == GPTQ_F32 ? n64 * (n64 + 1) / 2 >= 128 : n32 * (n32 + 1) / 2 > 256) {
         hipLaunchKernelGGL((syrk_small_kernel<TYPE, 64, 8>), dim3((unsigned)(n64 * (n64 + 1) / 2)), dim3(512), 0, s, a);
     } else if (n16 * (n16 + 1) / 2 <= 256) {
         hipLaunchKernelGGL((syrk_small_kernel<TYPE, 16, 16>), dim3((unsigned)(n16 * (n16 + 1) / 2)), dim3(1024), 0, s, a);

@@ -50,3 +50,26 @@ def test_hessian_of_few_channels(dtype, n, t, workspace):
     print(f"  rel_fro={err:.3e}", flush=True)
     assert err <= 1e-5
     assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("dtype,n,t", [
+    (torch.float16, 33, 255), (torch.float16, 33, 256), (torch.bfloat16, 352, 64 * 17 + 3), (torch.float16, 353, 64 * 33),          # three chunks, four; a second pass of one wavefront
+    (torch.float32, 33, 127), (torch.float32, 33, 128), (torch.float32, 352, 32 * 17 + 3), (torch.float32, 17, 32 * 33 + 31),
+    (torch.bfloat16, 961, 64 * 9 + 5), (torch.float16, 1537, 128), (torch.bfloat16, 2304, 64 * 8 + 63), (torch.float16, 2305, 200),  # the largest, and past it
+])
+def test_operands_through_lds(dtype, n, t):
+    """Chunks copied into LDS by the wavefront that multiplies them, at the edges of what a wavefront takes at a time."""
+    import paper_2210_17323_amd as g
+    print(f"hessian through LDS {dtype} n={n} t={t}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(n + t)
+    ld = (t + 7) // 8 * 8 + 8
+    X = torch.full((n, ld), float("nan"), dtype=dtype, device="cuda")[:, :t]
+    X.copy_(torch.randn((n, t), generator=gen, device="cuda"))
+    H = torch.ones((n, n), dtype=torch.float32, device="cuda")
+    g.gptq_hessian_accumulate(H, X, None)
+    x = X.double()
+    want, size = 1.0 + 2.0 * (x @ x.T), 1.0 + 2.0 * (x.abs() @ x.abs().T)
+    # products are exact or rounded once, sums of t of them in float32 in any order: gamma_t of the sum of magnitudes at most
+    worst = float(torch.triu((H.double() - want).abs() / size).max())
+    print(f"  worst element {worst:.3e} of its magnitudes", flush=True)
+    assert worst <= (t + 4) * 2.0 ** -24
