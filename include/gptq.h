@@ -270,8 +270,8 @@ GPTQ_API int gptq_trailing_update(float* W, int64_t ldw, const float* E, int64_t
  */
 /*
  * Which updates take the split products follows from the call's sizes: above 4096 channels in step 2, wherever the shapes allow
- * it in step 3.  gptq_set_split_min_tiles(t) with t > 0 makes it launches of at least t tiles of 256 x 256 for every later call of
- * the process (t <= 0 restores the rule) and returns the previous setting: a tuning and test knob -- the results of a call depend on it only through
+ * it in step 3.  gptq_set_split_min_tiles(t) with t > 0 makes it launches of at least t tiles of 256 x 256 (in step 3 and in the inverse one
+ * decision for the whole call, by the columns of one outer block) for every later call of the process (t <= 0 restores the rule) and returns the previous setting: a tuning and test knob -- the results of a call depend on it only through
  * rounding.  Not meant to be changed while another thread is inside a library call.
  */
 GPTQ_API int gptq_set_split_min_tiles(int tiles);

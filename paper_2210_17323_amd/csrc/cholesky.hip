@@ -15,8 +15,8 @@
 //     H[0:o0, 0:o0] -= R[0:o0, o] R[0:o0, o]^T     (rank 1024, carries the flops)
 // The chain of an outer block takes 184 us while nothing else runs, up to 310 beside the updates of a 12288 x 12288 matrix, whose workgroups
 // hold the CUs it has to start on.  With two launches per block of 128 columns, 8 x (28 + 15) us alone and 8 x (36 + 26) beside the updates, and
-// with the whole panel and the update of the next 1024 columns between two chains, n = 12288 took 9.26 ms (now 6.76) and the inverse at
-// n = 5000 3.41 (2.23).
+// with the whole panel and the update of the next 1024 columns between two chains, n = 12288 took 9.26 ms and the inverse at
+// n = 5000 3.41; 6.76 and 2.23 before the updates and the inverse's products went to the split products, 5.3 and 1.90 since.
 //
 //   one outer block behind, on a stream of its own (only when the inverse is wanted): U_oo = R_oo^-1, kept dense for the
 //     inverse (chol_strip.hip).

@@ -243,7 +243,7 @@ __global__ __launch_bounds__(256) void repack_token_major_kernel(const uint16_t*
 }
 
 // ---- 256 x 256 tile, 4 wavefronts of 128 x 128, panels copied global -> LDS directly ----------------
-// Each wavefront keeps a 4 x 4 grid of 32x32 accumulators (256 registers), which halves the LDS reads
+// Each wavefront keeps an 8 x 8 grid of 16x16 accumulators (256 registers), which halves the LDS reads
 // per MFMA compared with 128 x 64 wavefront tiles.  The two panels of a 32-token step (2 x 16 KB) go
 // straight from global memory into LDS with global_load_lds_dwordx4 (no staging registers, no
 // ds_write): one such instruction moves 16 rows x 64 bytes and lays the 64 lanes down linearly in LDS,
@@ -483,7 +483,7 @@ __global__ __launch_bounds__(256) void syrk_reduce_kernel(SyrkArgs g) {
 // Matrices with fewer than four 256 x 256 tiles per CU leave much of the chip idle at the end of a launch (or
 // all along: n = 4096 has 136 tiles for 256 CUs), so their token range is split into up to 8 parts -- up to as many as
 // fill the chip once where there are no more than 32 tiles.  The split
-// count minimises a simple cost: rounds of 256 workgroups x (steps per part x 0.76 us + a fixed cost per work
+// count minimises a simple cost: rounds of 256 workgroups x (steps per part x 0.76 us (0.72 since the smaller instructions) + a fixed cost per work
 // item: ~8 us to start and to add a tile to H, ~30 us when a partial tile is written, read back and reduced).
 struct SyrkPlan { int splits; int64_t nsteps; size_t repack_bytes, partial_bytes; };
 constexpr int64_t REPACK_MAX_STEPS = 65535;                // steps of 32 tokens, a dimension of the repack's grid

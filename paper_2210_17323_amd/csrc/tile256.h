@@ -1,5 +1,5 @@
 // One step of a 256 x 256 tile by four wavefronts of 128 x 128, 16-bit operands in LDS, 256 float32 accumulators a lane: what the
-// Hessian's kernel and that of the split products do between two barriers.
+// Hessian's kernel does between two barriers.  Its instructions and how its results leave are those of the split products too.
 //
 // Bound by the power the matrix cores may draw, which sets the clock.  A 32x32x16 instruction reads and writes four times the
 // accumulators of a 16x16x32 one for twice the products; a loop of registers holds, on normal data, 1600 TFLOP/s (float16) and 1740
