@@ -24,8 +24,9 @@ namespace {
 
 struct SmallArgs { float* H; int64_t ldh; const void* X; int64_t ldx, n, t; };
 
-// TYPE: GPTQ_F16, GPTQ_BF16 or GPTQ_F32
-template <int TYPE, int T, int WAVES>
+// TYPE: GPTQ_F16, GPTQ_BF16 or GPTQ_F32.  CHAINS: sums that a wavefront's chunks go to in turn; the sums are added in the order of their
+// first chunks, so that 8 wavefronts of two give the bits of 16 of one.
+template <int TYPE, int T, int WAVES, int CHAINS = 1>
 __global__ __launch_bounds__(64 * WAVES) void syrk_small_kernel(SmallArgs g) {
     constexpr int SZ = TYPE == GPTQ_F32 ? 4 : 2;
     constexpr int EL = 16 / SZ;                              // tokens per load
@@ -121,14 +122,16 @@ __global__ __launch_bounds__(64 * WAVES) void syrk_small_kernel(SmallArgs g) {
             d[i] = make_uint4(w[0], w[1], w[2], w[3]);
         }
     };
-    floatx4 acc[S][S];
+    floatx4 sums[CHAINS][S][S];
 #pragma unroll
-    for (int s = 0; s < S; ++s)
+    for (int h = 0; h < CHAINS; ++h)
 #pragma unroll
-        for (int u = 0; u < S; ++u)
+        for (int s = 0; s < S; ++s)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) acc[s][u][i] = 0.f;
-    auto products = [&](const uint4 (&x)[S][PER], const uint4 (&y)[S][PER]) {
+            for (int u = 0; u < S; ++u)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) sums[h][s][u][i] = 0.f;
+    auto products = [&](floatx4 (&acc)[S][S], const uint4 (&x)[S][PER], const uint4 (&y)[S][PER]) {
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             if constexpr (TYPE == GPTQ_F32) {
@@ -155,21 +158,27 @@ __global__ __launch_bounds__(64 * WAVES) void syrk_small_kernel(SmallArgs g) {
         }
     };
     const int64_t chunks = g.t / CHUNK;
-    const bool through_lds = THROUGH_LDS && chunks > 3;
+    constexpr int SHORT = 3;                                 // chunks of the calls that go straight all the same: a wavefront has one at most
+    static_assert(SHORT < WAVES, "");
+    const bool through_lds = THROUGH_LDS && chunks > SHORT;
     // A wavefront's copies are its own business, no barrier: it waits for them, takes the operands into registers, and has the next ones
     // on their way while it multiplies.  (Past its last chunk the last of all is copied again.)
-    if (!through_lds && wave < chunks) {
+    if (THROUGH_LDS && !through_lds && wave < chunks) {
+        load(wave, 0);
+        products(sums[0], a[0], b[0]);
+    }
+    if (!THROUGH_LDS && wave < chunks) {
         const int64_t last = chunks - 1;
         load(wave, 0);
         for (int64_t c = wave; c < chunks; c += 2 * WAVES) {
             load(min(c + WAVES, last), 1);
             __builtin_amdgcn_sched_barrier(0);
-            products(a[0], b[0]);
+            products(sums[0], a[0], b[0]);
             if (c + WAVES >= chunks) break;
             __builtin_amdgcn_sched_barrier(0);
             load(min(c + 2 * WAVES, last), 0);
             __builtin_amdgcn_sched_barrier(0);
-            products(a[1], b[1]);
+            products(sums[0], a[1], b[1]);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -177,16 +186,20 @@ __global__ __launch_bounds__(64 * WAVES) void syrk_small_kernel(SmallArgs g) {
         const int64_t last = chunks - 1;
 #pragma unroll
         for (int u = 0; u < U; ++u) copy(min((int64_t)wave + u * WAVES, last), u);
-        for (int64_t c = wave; c < chunks; c += U * WAVES) {
+        auto trip = [&](int64_t c, floatx4 (&acc)[S][S]) {
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             fetch();
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
             for (int u = 0; u < U; ++u) copy(min(c + (U + u) * WAVES, last), u);
             __builtin_amdgcn_sched_barrier(0);
-            products(a[0], b[0]);
-            if (U > 1 && c + WAVES < chunks) products(a[U - 1], b[U - 1]);
+            products(acc, a[0], b[0]);
+            if (U > 1 && c + WAVES < chunks) products(acc, a[U - 1], b[U - 1]);
             __builtin_amdgcn_sched_barrier(0);
+        };
+        for (int64_t c = wave; c < chunks; c += CHAINS * U * WAVES) {
+            trip(c, sums[0]);
+            if (CHAINS > 1 && c + WAVES < chunks) trip(c + WAVES, sums[CHAINS - 1]);
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
@@ -196,22 +209,37 @@ __global__ __launch_bounds__(64 * WAVES) void syrk_small_kernel(SmallArgs g) {
             load_tail(rowA[s], chunks * CHUNK, a[0][s]);
             load_tail(rowB[s], chunks * CHUNK, b[0][s]);
         }
-        products(a[0], b[0]);
+        products(sums[CHAINS - 1], a[0], b[0]);
     }
     if (through_lds) __syncthreads();                        // everybody has read the operands whose place the partial tiles take
     unsigned char* const part = lds;
     // every wavefront leaves its partial tile in LDS, then takes its share of the tile: the partial sums of an element are
     // added in the order of the wavefronts
     floatx4* mine = reinterpret_cast<floatx4*>(part + wave * SLOT);
+    constexpr int SHARE = (S * S + WAVES - 1) / WAVES;
+    floatx4 total[SHARE];
 #pragma unroll
-    for (int s = 0; s < S; ++s)
+    for (int h = 0; h < CHAINS; ++h) {
+        if (h > 0) __syncthreads();
 #pragma unroll
-        for (int u = 0; u < S; ++u) mine[(s * S + u) * 64 + lane] = acc[s][u];
-    __syncthreads();
-    for (int p = wave; p < S * S; p += WAVES) {              // 16 x 16 tile p: rows 16 (p / S) + 4 kq + e, column 16 (p % S) + l16
-        floatx4 v = {0.f, 0.f, 0.f, 0.f};
+        for (int s = 0; s < S; ++s)
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) v += reinterpret_cast<const floatx4*>(part + w * SLOT)[p * 64 + lane];
+            for (int u = 0; u < S; ++u) mine[(s * S + u) * 64 + lane] = sums[h][s][u];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < SHARE; ++i) {
+            const int p = wave + i * WAVES;
+            if (p >= S * S) break;
+            if (h == 0) total[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) total[i] += reinterpret_cast<const floatx4*>(part + w * SLOT)[p * 64 + lane];
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < SHARE; ++i) {
+        const int p = wave + i * WAVES;                      // 16 x 16 tile p: rows 16 (p / S) + 4 kq + e, column 16 (p % S) + l16
+        if (p >= S * S) break;
+        const floatx4 v = total[i];
         const int64_t col = (int64_t)bj * T + 16 * (p % S) + l16;
         const int64_t row = (int64_t)bi * T + 16 * (p / S) + 4 * kq;
         if (col < g.n) {
@@ -234,7 +262,16 @@ int launch(const SmallArgs& a, hipStream_t s) {
     // 18.7 / 37.2 (11.8 / 19.9), 352 19.9 / 39.5 (12.5 / 20.4), 400 35.6 / 39.7 (21.4 / 20.8), 512 52 / 40; 16384 of 352 61 / 141 (34 / 62), 400 118 / 141 (63 / 62).
     // Tiles of 64, 16-bit: as soon as those of 32 are more than one a CU (32 x 32 / 64 x 64: 8192 tokens of 712 28.2 / 26.7, 800 30.4 / 26.8, 960 36.8 / 27.9, 64 tokens of 900
     // 7.2 / 6.0; at 700, 253 tiles of 32, these are ahead).
-    if (TYPE == GPTQ_F32 ? n64 * (n64 + 1) / 2 >= 128 : n32 * (n32 + 1) / 2 > 256) {
+    // (Up to 960 channels, where those of 32 have 16 wavefronts and an element's tokens 16 sums, with two sums a wavefront: the same bits.
+    // With 8 sums 65536 tokens had a relative error of 1.8e-7, not 1.1e-7, 16384 one of 1.0e-7, not 0.8e-7; 8192 tokens of 960 take 30 us either way.)
+    if constexpr (TYPE != GPTQ_F32) {
+        if (n32 * (n32 + 1) / 2 > 256 && n64 * (n64 + 1) / 2 < 128) {
+            hipLaunchKernelGGL((syrk_small_kernel<TYPE, 64, 8, 2>), dim3((unsigned)(n64 * (n64 + 1) / 2)), dim3(512), 0, s, a);
+            GPTQ_LAUNCH_CHECK();
+            return GPTQ_OK;
+        }
+    }
+    if (n64 * (n64 + 1) / 2 >= 128) {
         hipLaunchKernelGGL((syrk_small_kernel<TYPE, 64, 8>), dim3((unsigned)(n64 * (n64 + 1) / 2)), dim3(512), 0, s, a);
     } else if (n16 * (n16 + 1) / 2 <= 256) {
         hipLaunchKernelGGL((syrk_small_kernel<TYPE, 16, 16>), dim3((unsigned)(n16 * (n16 + 1) / 2)), dim3(1024), 0, s, a);

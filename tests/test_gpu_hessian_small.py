@@ -73,3 +73,18 @@ def test_operands_through_lds(dtype, n, t):
     worst = float(torch.triu((H.double() - want).abs() / size).max())
     print(f"  worst element {worst:.3e} of its magnitudes", flush=True)
     assert worst <= (t + 4) * 2.0 ** -24
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("n,t", [(705, 64 * 3 + 5), (705, 64 * 4), (720, 64 * 17 + 3), (768, 64 * 33), (800, 16384), (960, 64 * 41 + 63)])
+def test_an_element_has_the_same_bits_whatever_the_tile(dtype, n, t):
+    """Up to 960 channels the tokens of an element go to 16 sums, in tiles of 32 channels (up to 704) and of 64."""
+    import paper_2210_17323_amd as g
+    print(f"hessian bits {dtype} n={n} t={t}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(n + t)
+    X = torch.empty((n, (t + 7) // 8 * 8), dtype=dtype, device="cuda")[:, :t]
+    X.copy_(torch.randn((n, t), generator=gen, device="cuda"))
+    H, first = torch.zeros((n, n), device="cuda"), torch.zeros((704, 704), device="cuda")
+    g.gptq_hessian_accumulate(H, X, None)
+    g.gptq_hessian_accumulate(first, X[:704], None)
+    assert torch.equal(torch.triu(H[:704, :704]), torch.triu(first))
