@@ -101,9 +101,24 @@ __global__ __launch_bounds__(64 * WAVES) void syrk_small_kernel(SmallArgs g) {
                 b[buf][s][i] = *reinterpret_cast<const uint4*>(rowB[s] + off + 64 * i);
             }
     };
-    // the tokens past the last whole chunk, zeros past the last token: 16 bytes at a time but for a row's last few (element by
-    // element throughout, a call of 8 tokens of 1536 channels took 19 us; 15 through the larger tiles)
+    // The tokens past the last whole chunk, zeros past the last token: the 16 bytes that hold a lane's, or the last 16 that hold any, masked
+    // -- without a branch, so that all loads are on their way at once (with one around each, 8 tokens of 2048 channels took 15.0 us; 13.5 through
+    // the larger tiles).  What a row's last 16 bytes hold past its last token is in the row (its distance to the next is whole 16 bytes) but
+    // for the last row's: the 16 rows with it are taken element by element.
     auto load_tail = [&](const char* row, int64_t k0, uint4 (&d)[PER]) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int64_t k = k0 + (4 * i + kq) * EL;
+            const uint4 v = *reinterpret_cast<const uint4*>(row - kq * 16 + min(k, (g.t - 1) / EL * EL) * SZ);
+            const int64_t left = g.t - k;
+            auto keep = [&](uint32_t w, int j) {             // word j of the 16 bytes
+                if constexpr (SZ == 4) return left > j ? w : 0u;
+                else return left >= 2 * j + 2 ? w : left == 2 * j + 1 ? w & 0xFFFFu : 0u;
+            };
+            d[i] = make_uint4(keep(v.x, 0), keep(v.y, 1), keep(v.z, 2), keep(v.w, 3));
+        }
+    };
+    auto load_tail_of_last_row = [&](const char* row, int64_t k0, uint4 (&d)[PER]) {
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
             const int64_t k = k0 + (4 * i + kq) * EL;
@@ -204,10 +219,26 @@ __global__ __launch_bounds__(64 * WAVES) void syrk_small_kernel(SmallArgs g) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
     if (g.t % CHUNK != 0 && wave == WAVES - 1) {
+        auto load_rows = [&](const char* row, int64_t first, uint4 (&d)[PER]) {
+            if (first + 16 < g.n) load_tail(row, chunks * CHUNK, d);
+            else if (first < g.n) load_tail_of_last_row(row, chunks * CHUNK, d);
+            else {
 #pragma unroll
-        for (int s = 0; s < S; ++s) {
-            load_tail(rowA[s], chunks * CHUNK, a[0][s]);
-            load_tail(rowB[s], chunks * CHUNK, b[0][s]);
+                for (int i = 0; i < PER; ++i) d[i] = make_uint4(0u, 0u, 0u, 0u);
+            }
+        };
+        if (g.t % EL == 0 || (int64_t)bj * T + T < g.n) {     // (rows lie above columns)
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                load_tail(rowA[s], chunks * CHUNK, a[0][s]);
+                load_tail(rowB[s], chunks * CHUNK, b[0][s]);
+            }
+        } else {
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                load_rows(rowA[s], (int64_t)bi * T + 16 * s, a[0][s]);
+                load_rows(rowB[s], (int64_t)bj * T + 16 * s, b[0][s]);
+            }
         }
         products(sums[CHAINS - 1], a[0], b[0]);
     }
@@ -217,7 +248,18 @@ __global__ __launch_bounds__(64 * WAVES) void syrk_small_kernel(SmallArgs g) {
     // added in the order of the wavefronts
     floatx4* mine = reinterpret_cast<floatx4*>(part + wave * SLOT);
     constexpr int SHARE = (S * S + WAVES - 1) / WAVES;
-    floatx4 total[SHARE];
+    floatx4 total[SHARE], old[SHARE];
+    // 16 x 16 tile wave + i WAVES of this tile: rows row_of(i) + e, column col_of(i); H as it is is asked for before the sums are added
+    auto mine_too = [&](int i) { return S * S % WAVES == 0 || wave + i * WAVES < S * S; };
+    auto col_of = [&](int i) { return (int64_t)bj * T + 16 * ((wave + i * WAVES) % S) + l16; };
+    auto row_of = [&](int i) { return (int64_t)bi * T + 16 * ((wave + i * WAVES) / S) + 4 * kq; };
+#pragma unroll
+    for (int i = 0; i < SHARE; ++i) {
+        total[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            old[i][e] = mine_too(i) && col_of(i) < g.n && row_of(i) + e < g.n ? g.H[(row_of(i) + e) * g.ldh + col_of(i)] : 0.f;
+    }
 #pragma unroll
     for (int h = 0; h < CHAINS; ++h) {
         if (h > 0) __syncthreads();
@@ -227,31 +269,20 @@ __global__ __launch_bounds__(64 * WAVES) void syrk_small_kernel(SmallArgs g) {
             for (int u = 0; u < S; ++u) mine[(s * S + u) * 64 + lane] = sums[h][s][u];
         __syncthreads();
 #pragma unroll
-        for (int i = 0; i < SHARE; ++i) {
-            const int p = wave + i * WAVES;
-            if (p >= S * S) break;
-            if (h == 0) total[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < SHARE; ++i)
+            if (mine_too(i)) {
 #pragma unroll
-            for (int w = 0; w < WAVES; ++w) total[i] += reinterpret_cast<const floatx4*>(part + w * SLOT)[p * 64 + lane];
-        }
+                for (int w = 0; w < WAVES; ++w) total[i] += reinterpret_cast<const floatx4*>(part + w * SLOT)[(wave + i * WAVES) * 64 + lane];
+            }
     }
 #pragma unroll
-    for (int i = 0; i < SHARE; ++i) {
-        const int p = wave + i * WAVES;                      // 16 x 16 tile p: rows 16 (p / S) + 4 kq + e, column 16 (p % S) + l16
-        if (p >= S * S) break;
-        const floatx4 v = total[i];
-        const int64_t col = (int64_t)bj * T + 16 * (p % S) + l16;
-        const int64_t row = (int64_t)bi * T + 16 * (p / S) + 4 * kq;
-        if (col < g.n) {
-            float* h = g.H + row * g.ldh + col;
-            float old[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) old[e] = row + e < g.n ? h[e * g.ldh] : 0.f;
+    for (int i = 0; i < SHARE; ++i)
+        if (mine_too(i) && col_of(i) < g.n) {
+            float* h = g.H + row_of(i) * g.ldh + col_of(i);
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                if (row + e < g.n) h[e * g.ldh] = old[e] + 2.0f * v[e];
+                if (row_of(i) + e < g.n) h[e * g.ldh] = old[i][e] + 2.0f * total[i][e];
         }
-    }
 }
 
 template <int TYPE>

@@ -88,3 +88,23 @@ def test_an_element_has_the_same_bits_whatever_the_tile(dtype, n, t):
     g.gptq_hessian_accumulate(H, X, None)
     g.gptq_hessian_accumulate(first, X[:704], None)
     assert torch.equal(torch.triu(H[:704, :704]), torch.triu(first))
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
+@pytest.mark.parametrize("n", [33, 352, 384, 704, 705, 768, 961, 1024])
+@pytest.mark.parametrize("t", [1, 8, 39, 64 * 4 + 7, 64 * 5 + 24])
+def test_tokens_past_the_last_chunk(dtype, n, t):
+    """Fewer tokens than a chunk, whole and broken 16 bytes of them, in each size of tile, the last row alone or not in its 16; the matrix ends
+    with its last token."""
+    import paper_2210_17323_amd as g
+    print(f"hessian tail {dtype} n={n} t={t}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(n + t)
+    ld = (t + 7) // 8 * 8
+    X = torch.full(((n - 1) * ld + t,), float("nan"), dtype=dtype, device="cuda").as_strided((n, t), (ld, 1))
+    X.copy_(torch.randn((n, t), generator=gen, device="cuda"))
+    H = torch.ones((n, n), dtype=torch.float32, device="cuda")
+    g.gptq_hessian_accumulate(H, X, None)
+    x = X.double()
+    want, size = 1.0 + 2.0 * (x @ x.T), 1.0 + 2.0 * (x.abs() @ x.abs().T)
+    worst = float(torch.triu((H.double() - want).abs() / size).max())
+    assert worst <= (t + 4) * 2.0 ** -24        # sums of t products in float32, in any order
