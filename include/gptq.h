@@ -135,6 +135,8 @@ GPTQ_API int gptq_hessian_symmetrize(float* H, int64_t ldh, int64_t n, void* str
  *   the Cholesky factor), all in float32; above 4096 channels the rank-1024 updates that carry most of the flops multiply
  *   three-piece bfloat16 splits of their float32 operands on the bf16 matrix cores (see gptq_symmetric_update_split
  *   below: less than the error of a float32 multiply-add), which is also what the second half of the workspace is for.
+ *   Range: any scale of H that the float32 arithmetic of the factorisation itself takes (the factor's elements are roots of H's).  Where
+ *   *info_dev is not 0, what is not finite may cover other elements of the result than it would in float32 throughout.
  *   Part of the work is enqueued on helper streams owned by the library (created once per host thread and
  *   device, default priority) and joined back with events: when the call returns, everything it enqueued
  *   is ordered on `stream`, and nothing of it starts before the work already on `stream`.
@@ -194,6 +196,10 @@ GPTQ_API int gptq_check_info(const int* info_dev, int* host_info, void* stream);
  *   The update of column j's block and the rank-128 updates inside an outer block of 1024 columns are float32; the
  *   deferred rank-1024 updates beyond it are the split products of gptq_trailing_update_split below (n % 256 == 0 and
  *   n >= 2048, any r > 128: rows are padded to whole tiles in the workspace) or float32 matrix-core products.
+ *   Range: the split products keep all 24 bits of the scaled errors and of U from 2^-100 to 2^127 in magnitude, which weights from about
+ *   2^-90 to 2^110 stay in; below, the last bits of the errors are lost (weights of 2^-115 and less: some codes are another of two near ones),
+ *   and an error beyond the float32 range makes the rest of its row NaN where float32 products make it infinite.  A weight that is
+ *   infinite or NaN spoils its own row from its group's first column on and no other row.
  *   r == 0 or n == 0 is a valid no-op.  Like step 2, the call puts part of its work on the library's helper
  *   stream and joins it back before returning.
  */

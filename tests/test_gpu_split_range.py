@@ -164,3 +164,47 @@ def test_layers_of_ragged_columns(r, n, factor):
     print(f"  rows with other codes {int(differ.sum())}, loss of the others {float(rel[~differ].max()):.2e}", flush=True)
     assert float(differ.float().mean()) <= 0.05
     assert float(rel[~differ].max()) <= 1e-5 and float(rel.max()) <= 5e-2
+
+
+@pytest.mark.parametrize("factor,group", [(False, 0), (False, 64), (False, 128), (False, 256), (True, 0), (True, 32)])
+def test_weights_that_are_not_finite(factor, group):
+    """A weight that is infinite or NaN costs its own row, and there only what float32 updates would have cost; finite weights up to the
+    largest leave nothing else behind either."""
+    import paper_2210_17323_amd as g
+    r, n = 200, 2304                                        # three outer blocks, split products throughout
+    gen = torch.Generator(device="cuda").manual_seed(group + factor)
+    X = torch.randn((n, 2 * n), device="cuda", generator=gen)
+    H = X @ X.T
+    info = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ws = torch.empty(g.gptq_damp_cholesky_inverse_workspace_bytes(n), dtype=torch.uint8, device="cuda")
+    (g.gptq_damp_cholesky if factor else g.gptq_damp_cholesky_inverse)(H, 0.01, ws, info)
+    W = 0.02 * torch.randn((r, n), device="cuda", generator=gen)
+    bad = W.clone()
+    inf = float("inf")
+    places = [(3, 5, inf), (4, 100, -inf), (5, 0, float("nan")), (6, n - 1, inf), (7, n - 1, -inf), (8, 1500, inf), (9, 2050, float("nan")), (10, 1030, -inf)]
+    for row, column, value in places:
+        bad[row, column] = value
+    G = n // group if group else 1
+
+    def quantize(W, tiles):
+        codes, half = torch.zeros((r, n), dtype=torch.uint8, device="cuda"), torch.zeros(r, dtype=torch.float64, device="cuda")
+        scales, zeros = torch.zeros((r, G), device="cuda"), torch.zeros((r, G), dtype=torch.int32, device="cuda")
+        ws = torch.full((g.gptq_quantize_layer_workspace_bytes(r, n, 128, group),), 0xFF, dtype=torch.uint8, device="cuda")
+        prev = g.gptq_set_split_min_tiles(tiles)
+        try:
+            g.gptq_quantize_layer(W, H, 3, g.GPTQ_GRID_MINMAX, 128, group, codes, scales, zeros, ws, half_E2_rows=half, from_factor=factor)
+        finally:
+            g.gptq_set_split_min_tiles(prev)
+        return codes, scales.nan_to_num(nan=-1.0, posinf=-2.0, neginf=-3.0), zeros, half.nan_to_num(nan=-1.0, posinf=-2.0)
+
+    print(f"weights that are not finite, factor={factor} group={group}", flush=True)
+    clean, split, float32 = quantize(W, 0), quantize(bad, 0), quantize(bad, 1 << 30)
+    rows = torch.tensor(sorted({p[0] for p in places}), device="cuda")
+    others = torch.ones(r, dtype=torch.bool, device="cuda")
+    others[rows] = False
+    for name, a, b, c in zip(("codes", "scales", "zeros"), split, float32, clean):
+        assert torch.equal(a[others], c[others]), name
+        if name != "scales":
+            assert torch.equal(a[rows], b[rows]), (name, (a != b).any(1).nonzero().flatten().tolist())
+    assert torch.equal(split[3][others], clean[3][others])
+    assert torch.equal(split[3][rows] < 0, float32[3][rows] < 0) and bool((split[3][rows] < 0).all())
