@@ -10,6 +10,8 @@
 
 #include <hip/hip_fp16.h>
 
+#include <atomic>
+
 namespace gptq {
 
 struct PackedArgs {
@@ -730,13 +732,15 @@ extern "C" int gptq_dequantize_packed(const uint32_t* words, int64_t ldp, int64_
     return GPTQ_OK;
 }
 
+// CUs of the current device, asked for once per device; several threads may ask at a time.
 static int64_t chip_cus() {
-    static int cus = 0;
-    if (cus == 0) {
-        int dev = 0, v = 0;
-        if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) cus = v;
-        else cus = 256;
-    }
+    constexpr int MAXDEV = 64, USUAL = 256;
+    static std::atomic<int> known[MAXDEV];
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAXDEV) return USUAL;
+    if ((cus = known[dev].load(std::memory_order_relaxed)) > 0) return cus;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return USUAL;
+    known[dev].store(cus, std::memory_order_relaxed);
     return cus;
 }
 
@@ -757,14 +761,15 @@ static MvPlan mv_plan(int64_t r, int64_t n, bool may_take_eight) {
     const bool few = r <= 1024;
     int nh = may_take_eight && !few && ceil_div(r, 4) * nseg > 3072 ? 2 : 1;
     int most = few ? MV_MAX_WAVES : !may_take_eight ? 4 : nh == 1 ? MV_MAX_WAVES : r <= 4096 ? 8 : 4;
+    const int64_t cus = chip_cus();
     MvPlan p{};
     p.nh = nh;
     p.segw = 1;
     while (p.segw < most && p.segw < nseg) p.segw *= 2;
     p.waves = p.segw < 4 ? 4 : p.segw;
-    while (p.waves > p.segw && ceil_div(r, p.waves / p.segw * 4 * p.nh) < chip_cus()) p.waves /= 2;      // a workgroup for every CU
+    while (p.waves > p.segw && ceil_div(r, p.waves / p.segw * 4 * p.nh) < cus) p.waves /= 2;      // a workgroup for every CU
     const int chunk = p.waves / p.segw * 4 * p.nh;
-    p.rows_per_wg = (int64_t)round_up((size_t)ceil_div(r, std::max<int64_t>(1, chip_cus() * 32 / p.waves)), (size_t)chunk);
+    p.rows_per_wg = (int64_t)round_up((size_t)ceil_div(r, std::max<int64_t>(1, cus * 32 / p.waves)), (size_t)chunk);
     p.blocks = (unsigned)ceil_div(r, p.rows_per_wg);
     return p;
 }
