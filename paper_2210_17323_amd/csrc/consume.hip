@@ -21,7 +21,7 @@ struct PackedArgs {
     int64_t group, ngroups;      // group == 0: one grid per row (ngroups == 1)
     int gshift;                  // log2(group) if the group size is a power of two, else -1 (then columns are divided)
     int64_t rows_per_wg;         // matvec: rows a workgroup walks, a multiple of its row chunk
-    int segw;                    // matvec: wavefronts that share a row, each every segw-th segment of columns
+    int segw, segshift;          // matvec: wavefronts that share a row, each every segw-th segment of columns; segw = 1 << segshift
 };
 
 template <int BITS>
@@ -308,7 +308,7 @@ template <int BITS, int GSUB, int WAVES, typename XT>
 __global__ __launch_bounds__(64 * WAVES) void matvec_kernel(PackedArgs a, const XT* x, float* y) {
     __shared__ float part[WAVES][MV_ROWS];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int groups = (int)(blockDim.x >> 6) / a.segw, grp = wave / a.segw, sw = wave % a.segw;
+    const int groups = (int)(blockDim.x >> 6) >> a.segshift, grp = wave >> a.segshift, sw = wave & (a.segw - 1);
     const int64_t nseg = (a.n + MV_SEG - 1) / MV_SEG;
     constexpr int GL = 32 / GSUB;            // columns per grid inside the lane's 32
     const int64_t row_end = min(((int64_t)blockIdx.x + 1) * a.rows_per_wg, a.r);
@@ -484,7 +484,7 @@ __global__ __launch_bounds__(64 * WAVES) void matvec_dot2_kernel(PackedArgs a, c
     constexpr int ROWS = NH * MV2_HALF;
     __shared__ float part[WAVES][ROWS];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int groups = (int)(blockDim.x >> 6) / a.segw, grp = wave / a.segw, sw = wave % a.segw;
+    const int groups = (int)(blockDim.x >> 6) >> a.segshift, grp = wave >> a.segshift, sw = wave & (a.segw - 1);
     const int64_t nseg = (a.n + MV_SEG - 1) / MV_SEG;
     const int64_t row_end = min(((int64_t)blockIdx.x + 1) * a.rows_per_wg, a.r);
     const uint32_t wlast = (uint32_t)(a.words_per_row - BITS);      // n is a multiple of 32 and at least 32
@@ -607,7 +607,7 @@ __global__ __launch_bounds__(64 * WAVES) void matvec_mfma_kernel(PackedArgs a, c
     constexpr int ROWS = NH * MV2_HALF;
     __shared__ float part[WAVES][ROWS + 1];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int groups = (int)(blockDim.x >> 6) / a.segw, grp = wave / a.segw, sw = wave % a.segw;
+    const int groups = (int)(blockDim.x >> 6) >> a.segshift, grp = wave >> a.segshift, sw = wave & (a.segw - 1);
     const int64_t nseg = (a.n + MV_SEG - 1) / MV_SEG;
     const int64_t row_end = min(((int64_t)blockIdx.x + 1) * a.rows_per_wg, a.r);
     // this lane's element of the diagonal of D: lane = j + 16 ib holds D[4 ib + e][j], e = 0 .. 3
@@ -782,7 +782,7 @@ static void launch_matvec(PackedArgs a, const XT* x, float* y, hipStream_t s) {
         if (gsub == 1 && a.n % 32 == 0 && a.n >= 32 && a.n < 0x7fffffffLL && a.r < 0x7fffff00LL && a.words_per_row < 0x3fffffffLL &&
             a.ngroups < 0x3fffffffLL && (reinterpret_cast<uintptr_t>(x) & 15) == 0) {
             const MvPlan p = mv_plan(a.r, a.n, true);
-            a.rows_per_wg = p.rows_per_wg; a.segw = p.segw;
+            a.rows_per_wg = p.rows_per_wg; a.segw = p.segw; a.segshift = __builtin_ctz(p.segw);
             const dim3 grid(p.blocks), block(64 * p.waves);
 #define GPTQ_MV2(K)                                                                                             \
             if (p.nh == 1) hipLaunchKernelGGL((K<BITS, 1, MV_MAX_WAVES>), grid, block, 0, s, a, x, y);          \
@@ -794,7 +794,7 @@ static void launch_matvec(PackedArgs a, const XT* x, float* y, hipStream_t s) {
         }
     }
     const MvPlan p = mv_plan(a.r, a.n, false);
-    a.rows_per_wg = p.rows_per_wg; a.segw = p.segw;
+    a.rows_per_wg = p.rows_per_wg; a.segw = p.segw; a.segshift = __builtin_ctz(p.segw);
     const dim3 grid(p.blocks), block(64 * p.waves);
 #define GPTQ_MV1(G)                                                                                             \
     if (p.waves > 4) hipLaunchKernelGGL((matvec_kernel<BITS, G, MV_MAX_WAVES, XT>), grid, block, 0, s, a, x, y); \
