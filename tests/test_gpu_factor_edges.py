@@ -119,13 +119,38 @@ def test_inverse_over_many_outer_blocks(n):
     assert int(torch.tril(U, -1).count_nonzero()) == 0
     res = U @ Hd @ U.T
     res.diagonal().sub_(1.0)
-    # the factor's and the inverse's rounding, each a sum of up to n terms in units of the diagonal, through the matrix's condition number
-    ev = torch.linalg.eigvalsh((A.T @ A).cpu())
-    cond = float((ev[-1] + 512.0) / 512.0)
     worst, rel = float(res.abs().max()), float(res.norm() / np.sqrt(n))
-    print(f"  worst element {worst:.3e}, rms by row {rel:.3e}, condition {cond:.1f}", flush=True)
-    assert worst <= 4 * EPS * np.sqrt(n) * cond
-    assert rel <= EPS * np.sqrt(n) * cond
+    print(f"  worst element {worst:.3e}, rms by row {rel:.3e}", flush=True)
+    # Measured 5.1e-7 to 6.3e-7 and 5.5e-7 to 7.0e-7.  Products without third pieces (a1 b3, a2 b2, a3 b1 left out, all else exact) come to
+    # 2.6e-6 and 6.0e-6 at n = 5120 and must not pass.
+    assert worst <= 1.5e-6
+    assert rel <= 2e-6
+
+
+@pytest.mark.parametrize("n", [4097, 4099, 5001])
+def test_inverse_of_columns_that_are_no_multiple_of_four(n):
+    """Split products over one column, three, and 905 (an odd number of steps of 32), into columns that end inside 16 bytes; what lies
+    between the rows is NaN, reaches nothing and stays. U (H + lambda I) U^T against the identity, in float64 on the GPU."""
+    from paper_2210_17323_amd import solver as S
+    print(f"inverse, ragged, n={n}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    A = torch.randn((n, 512), generator=gen, device="cuda", dtype=torch.float64)
+    Hd = A @ A.T
+    Hd.diagonal().add_(512.0)
+    ld = (n + 3) // 4 * 4 + 4
+    whole = torch.full((n, ld), float("nan"), device="cuda")
+    U = whole[:, :n]
+    U.copy_(Hd)
+    Hd = U.double()
+    S.cholesky_inverse(U, 0.0)
+    assert bool(torch.isnan(whole[:, n:]).all())
+    U = U.double()
+    assert int(torch.tril(U, -1).count_nonzero()) == 0
+    res = U @ Hd @ U.T
+    res.diagonal().sub_(1.0)
+    worst, rel = float(res.abs().max()), float(res.norm() / np.sqrt(n))
+    print(f"  worst element {worst:.3e}, rms by row {rel:.3e}", flush=True)
+    assert worst <= 1.5e-6 and rel <= 2e-6                  # as above
 
 
 @pytest.mark.parametrize("n,column", [(300, 0), (300, 127), (300, 128), (300, 299), (1100, 1024), (1100, 1023), (1100, 17)])
