@@ -565,9 +565,9 @@ def test_quantize_from_factor_with_unaligned_weight_rows():
 
 
 # ------------------------------------------------------------------ the solvers with their deferred updates on the split products
-# On matrices this small the library's own rule keeps every update on the float32 kernel; with the rule replaced by
+# Up to 4096 channels the library's own rule keeps the factorisation's updates on the float32 kernel; with the rule replaced by
 # "every launch of whole tiles" the same calls run their rank-1024 updates through the split kernel and must still give
-# what the oracle gives, to the same bars.
+# what the oracle gives, to the same bars.  Alg. 1 takes it at these sizes either way (from 129 rows and 2048 columns in whole tiles on).
 
 @pytest.fixture
 def forced_split():
