@@ -133,7 +133,7 @@ static bool split_shapes_ok(int64_t r, int64_t n) { return r >= 256 && r % 256 =
 // written by anything but these updates and never read by anything else.
 static int64_t padded_rows(int64_t r) { return r >= 64 ? (int64_t)round_up((size_t)r, r <= 128 ? 128 : 256) : std::max<int64_t>(r, 1); }
 
-struct QuantWs { size_t wk, e, pk, ub, rt, pa, pb, pr, total; int64_t ldk, rows; bool split; };
+struct QuantWs { size_t wk, e, pk, ub, rt, pa, pr, total; int64_t ldk, rows; bool split; };
 static QuantWs quant_ws_layout(int64_t r, int64_t n, int64_t group) {
     QuantWs l;
     l.ldk = (int64_t)round_up((size_t)std::max<int64_t>(n, 1), 4);
@@ -147,12 +147,12 @@ static QuantWs quant_ws_layout(int64_t r, int64_t n, int64_t group) {
     if (inner_groups) off += round_up((size_t)ceil_div(std::max<int64_t>(n, 1), QB) * QB * QB * sizeof(float), 256);
     l.rt = off;                                                                                       // ... and R with its column blocks scaled by them
     if (inner_groups) off += round_up((size_t)std::max<int64_t>(n, 1) * l.ldk * sizeof(float), 256);
-    // split products (gemm_split.hip): the bf16 pieces of an error panel, of the next outer block's rows of U and of all rows beyond
+    // split products (gemm_split.hip): the bf16 pieces of an error panel (every other one's lie in place of the two float32 panels) and of
+    // an outer block's rows of U
     l.split = split_shapes_ok(l.rows, n);
-    l.pa = l.pb = l.pr = off;
+    l.pa = l.pr = off;
     if (l.split) {
         l.pa = off; off += round_up(split_planes_bytes(l.rows), 256);
-        l.pb = off; off += round_up(split_planes_bytes(QOB), 256);
         l.pr = off; off += round_up(split_planes_bytes(n), 256);
     }
     l.total = off + 256;

@@ -21,7 +21,7 @@ def test_library_loads_and_exports_every_declared_symbol():
 def test_workspace_sizes():
     assert g.gptq_damp_cholesky_inverse_workspace_bytes(256) >= 2 * 128 * 128 * 4 + 256 * 128 * 4
     big = g.gptq_quantize_layer_workspace_bytes(12288, 49152)
-    planes = (12288 + 1024 + 49152) * 6144 + 3 * 16384      # bf16 pieces of an error panel, of 1024 and of all columns of U's rows
+    planes = (12288 + 49152) * 6144     # bf16 pieces of an error panel and of all columns of an outer block's rows of U
     assert 12288 * 49152 * 4 + planes < big < 12288 * 49152 * 4 * 1.05 + planes + (1 << 24)      # W copy + two r x 1024 error panels
     assert g.gptq_quantize_layer_workspace_bytes(0, 0) > 0
     assert g.gptq_hessian_accumulate_workspace_bytes(49152, 32768) == 49152 * 32800 * 2
@@ -106,7 +106,7 @@ def test_argument_validation_happens_on_the_host():
     assert tus(one, 256, one, 1024, one, 256, 256, 256, 1024, None, 0, None) == WORKSPACE
     assert tus(one, 128, one, 1024, one, 256, 256, 256, 1024, one, 1 << 30, None) == INVALID                           # ldw < ncols
     assert tus(one, 256, one, 1024, one, 256, 0, 256, 1024, one, 1 << 30, None) == OK
-    assert g.gptq_trailing_update_split_workspace_bytes(256, 512) == 3 * (3 * 32 * 16384) + 2 * 16384 + 256
+    assert g.gptq_trailing_update_split_workspace_bytes(256, 512) == 3 * (3 * 32 * 16384) + 256
     prev = g.gptq_set_split_min_tiles(9)
     assert g.gptq_set_split_min_tiles(-3) == 9 and g.gptq_set_split_min_tiles(prev) == 0      # a value <= 0 is the library's own rule
     sus = L.gptq_symmetric_update_split
@@ -142,7 +142,7 @@ def test_quantize_workspace_of_few_rows():
     base = g.gptq_quantize_layer_workspace_bytes(1, n) - (n + panels) * 4
     for r, rows in ((3, 3), (63, 63), (64, 128), (128, 128), (129, 256)):
         need = g.gptq_quantize_layer_workspace_bytes(r, n) - base - (n + panels) * 4 * rows
-        planes = (rows + 1024 + n) * 6144 + 3 * 16384 if rows % 256 == 0 else 0
+        planes = (rows + n) * 6144 if rows % 256 == 0 else 0
         assert need == planes, (r, need, planes)
 
 
