@@ -18,7 +18,8 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 // c += a b, the accumulator in place.  As a statement of its own and not the builtin: with 256 accumulator registers in groups of
 // four the compiler gives the builtin's result another place than its addend and copies and spills between them.  What it
 // cannot see is that this is a matrix-core instruction: the callers see to it that no vector instruction writes an operand
-// right before, and wait before the first read of an accumulator (mfma_settle).
+// right before, and wait before the first read of an accumulator (mfma_settle); tests/test_matrix_instruction_waits.py looks for both in
+// the assembly.
 template <bool IS_BF16>
 __device__ __forceinline__ void mfma16x16_acc(floatx4& c, uint4 a, uint4 b) {
     if constexpr (IS_BF16)
