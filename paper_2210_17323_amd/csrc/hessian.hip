@@ -1,8 +1,9 @@
 // Step 1: H += 2 X X^T  (Section 2, the Hessian of the layer-wise objective; Alg. 1 caption).
 //
 // X is [n x t] with tokens contiguous, so both operands of X X^T are K-contiguous.  Only tiles of
-// the upper triangle of H are computed.  fp16 / bf16 inputs go to v_mfma_f32_32x32x16_{f16,bf16}
-// (products exact in float32, float32 accumulation); float32 inputs use the float32 GEMM.
+// the upper triangle of H are computed.  fp16 / bf16 inputs go to the matrix cores' 16-bit instructions
+// (products exact in float32, float32 accumulation): 16x16x32 in the kernel of 256 x 256 tiles that most calls take (below, and tile256.h), 32x32x16
+// in the guarded kernel, which is what the next paragraph describes; float32 inputs use the float32 GEMM.
 //
 // Kernel layout (fp16/bf16): a workgroup owns a BT x BT tile of H and walks the token axis in steps
 // of 64.  Per step it stages BT x 64 halves of the row panel and of the column panel in LDS (row

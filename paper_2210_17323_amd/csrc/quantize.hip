@@ -123,8 +123,8 @@ static bool factor_form_group_supported(int64_t group) { return group == 0 || gr
 static_assert(QOB == SPLIT_K, "the split products take exactly one outer block as K");
 
 // The deferred rank-1024 updates go through the split-operand kernel (bf16 matrix cores, gemm_split.hip) when columns come in whole panels
-// of 256.  `r` are the padded rows, so any row count above 128 qualifies.  They are the faster at every size (4096 x 1024 63 us
-// against 70, 256 x 256 41 against 66) and the closer: relative error against 64-bit products 1.3e-7, 5.7e-7 in float32.
+// of 256.  `r` are the padded rows, so any row count above 128 qualifies.  They are the faster at every size (4096 x 1024 57 us
+// against 70, 256 x 256 42 against 66) and the closer: relative error against 64-bit products 1.3e-7, 5.7e-7 in float32.
 static bool split_shapes_ok(int64_t r, int64_t n) { return r >= 256 && r % 256 == 0 && n % 256 == 0 && n >= 2 * QOB; }
 
 // Rows of the working matrix and of the error panels in the workspace: whole tiles of the deferred updates, so that a layer

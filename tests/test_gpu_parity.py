@@ -429,9 +429,9 @@ def test_trailing_update_split_matches_oracle(r, ncols):
     g.gptq_trailing_update(W32, Ed, Ud)
     err, err32 = _rel_fro(got - W0, -prod), _rel_fro(W32.double().cpu().numpy() - W0, -prod)
     # element by element against what the arithmetic allows: each of the k products is off by at most 2^-23 of its
-    # size (the piece products left out), and each of the 384 float32 additions of a 16-term group by 2^-24 of the
-    # partial sum, which a dominant term can bring close to the sum of magnitudes (a random walk of 384 such steps, the
-    # worst of a million elements): 2^-18 of that sum bounds both.  A piece product left out by mistake is what the
+    # size (the piece products left out), and each of the 64 float32 additions of either sum of a1 b1 (8 products at a time) by 2^-24 of the
+    # partial sum, which a dominant term can bring close to the sum of magnitudes (a random walk of 128 such steps, the
+    # worst of a million elements; the 640 additions of the small products are at 2^-8 of that): 2^-18 of that sum bounds both.  A piece product left out by mistake is what the
     # Frobenius figure catches: 2^-17 of the typical product, i.e. about 4e-6 there.
     bound = 2.0 ** -18 * (np.abs(E).astype(np.float64) @ np.abs(U).astype(np.float64)) + 2.0 ** -22 * np.abs(W0)
     worst = float(np.max(np.abs(got - want) / bound))
