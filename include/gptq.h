@@ -196,10 +196,10 @@ GPTQ_API int gptq_check_info(const int* info_dev, int* host_info, void* stream);
  *   The update of column j's block and the rank-128 updates inside an outer block of 1024 columns are float32; the
  *   deferred rank-1024 updates beyond it are the split products of gptq_trailing_update_split below (n % 256 == 0 and
  *   n >= 2048, any r > 128: rows are padded to whole tiles in the workspace) or float32 matrix-core products.
- *   Range: the split products keep all 24 bits of the scaled errors and of U from 2^-100 to 2^127 in magnitude, which weights from about
- *   2^-90 to 2^110 stay in; below, the last bits of the errors are lost (weights of 2^-115 and less: some codes are another of two near ones),
- *   and an error beyond the float32 range makes the rest of its row NaN where float32 products make it infinite.  A weight that is
- *   infinite or NaN spoils its own row from its group's first column on and no other row.
+ *   Range: the split products keep all 24 bits of their operands -- E and U, or W - Q and R where R drives the call -- from 2^-100 to
+ *   2^127 in magnitude.  Below, the last bits are lost (with a Hessian of ordinary size weights of 2^-110 and less: some codes are the other
+ *   of two near ones), and an error beyond makes the rest of its row NaN where float32 products make it infinite.  A weight that
+ *   is infinite or NaN spoils its own row from its group's first column on and no other row.
  *   r == 0 or n == 0 is a valid no-op.  Like step 2, the call puts part of its work on the library's helper
  *   stream and joins it back before returning.
  */
